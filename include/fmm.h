@@ -114,7 +114,8 @@ int fmm_plan_set_m2l_fold_interval(fmm_plan_t plan, int offsets);
  * buffers would exceed 2 GiB).  Different splits sum in different orders:
  * results agree to rounding.  Returns FMM_ERR_ARG outside 0..4. */
 int fmm_plan_set_m2l_split(fmm_plan_t plan, int parts);
-/* The split in use (1 in the dense modes). */
+/* The split in use (1 in the dense modes, which choose their own offset
+ * ranges from the tile count). */
 int fmm_plan_m2l_split(fmm_plan_t plan, int* parts);
 
 /* Compressed-M2L facts of the plan's current order and tolerance (host

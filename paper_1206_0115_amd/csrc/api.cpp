@@ -55,6 +55,35 @@ static int auto_parts(int64_t items, int64_t slots, size_t part_bytes) {
   return best;
 }
 
+// Offset ranges per tile of the dense M2L.  A small plan's tiles leave most of
+// the GPU idle (4,000 particles at height 4: 16 items on 512 workgroup slots,
+// each a chain of 189 offsets), and a larger one's last round is partly
+// empty; K ranges make K times the items.  The partial sums of K ranges are
+// written once and read once, in FP64 whatever the mode, so K minimises
+//     rounds(items K) / K * (an item's time) + K * (2 passes over the parts),
+// with an item's time at 70% of its slot's share of the matrix cores (the
+// rate measured at 1M particles) and the passes at 3 TB/s.
+static int dense_parts(int64_t items, int mt, bool fp32, size_t part_bytes, int cus) {
+  constexpr int kMax = 32;                      // about six offsets a range
+  constexpr size_t kBudget = size_t(256) << 20;  // of partial sums
+  const double slots = 2.0 * cus;
+  const double rate = 0.7 * (fp32 ? 157.3e12 : 78.6e12) / (2.0 * 256);
+  const double item = kSlots * m2l_item_flops(mt) / rate;
+  const double pass = double(part_bytes) / 3e12;
+  int best = 1;
+  double best_cost = std::ceil(double(items) / slots) * item;
+  for (int k = 2; k <= kMax; ++k) {
+    if (size_t(k - 1) * part_bytes > kBudget) break;
+    const double cost =
+        std::ceil(double(items) * k / slots) / k * item + 2.0 * k * pass + 4e-6;
+    if (cost < 0.98 * best_cost) {
+      best = k;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 void upload_job(fmm_plan_s* p, hipStream_t s) {
   const int h = p->height;
   const OpSet* op = p->ops;
@@ -110,6 +139,11 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
     parts = p->m2l_split > 0 ? p->m2l_split
                              : auto_parts(int64_t(p->ntiles) * J.nmb,
                                           m2l_svd_slots(p->order, fp32, J.xs), part_bytes);
+  } else if (!p->svd && h >= 3 && p->W) {
+    int cus = 0;
+    FMM_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    parts = dense_parts(int64_t(p->ntiles) * J.nmb, op->mt, fp32, part_bytes, cus);
+    if (p->dense_parts_max > 0) parts = std::min(parts, p->dense_parts_max);
   }
   const size_t want = size_t(parts - 1) * part_bytes;
   bool split_oom = false;  // reported once the job below is consistent
@@ -123,11 +157,11 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
         p->locx_bytes = want;
       } catch (const FmmError&) {
         parts = 1;
-        split_oom = p->m2l_split > 1;
+        split_oom = p->svd && p->m2l_split > 1;
       }
     }
   }
-  p->m2l_parts = parts;
+  p->m2l_parts = p->svd ? parts : 1;
   J.m2l_parts = parts;
   J.locx_first = h >= 3 ? int64_t(p->lev[2].off) : 0;
   J.locx_rows = lrows;

@@ -161,6 +161,7 @@ enum {
 };
 
 int m2l_nmb(int mt);      // M-blocks per M2L tile for mt 16-row tiles (dense)
+double m2l_item_flops(int mt);  // ... and the flops of one item at one far offset
 // Compressed M2L for mt 16-row tiles and a slab stride of xs values (the
 // kernel's shape depends on both): work items per tile, and 16-column
 // N-tiles per item (launches of one order and precision that batch several
@@ -247,7 +248,8 @@ struct fmm_plan_s {
   int near_mode = FMM_NEAR_ONE_SIDED;  // fmm_plan_set_near
   int* mutual_list = nullptr;      // leaves of the mutual pair lists (built on first use)
   int64_t mutual_off[2 * fmm::kMutualSlots + 1] = {0};  // list (slot 14 + k, colour c) at 2k + c
-  int m2l_parts = 1;               // the split in use
+  int m2l_parts = 1;               // the compressed M2L's split in use (1: dense modes)
+  int dense_parts_max = 0;         // bound on the dense M2L's own split (0: none)
   double* LocX = nullptr;          // partial local expansions of parts 1..
   size_t locx_bytes = 0;
   hipStream_t side = nullptr;      // the near-field branch of the forked schedule

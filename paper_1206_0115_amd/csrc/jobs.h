@@ -47,7 +47,7 @@ struct JobDev {
   // leaves hold few particles on average: L2P spreads each particle's l^3
   // terms over a wavefront's lanes (l2p_sparse_kernel)
   int l2p_sparse;
-  // compressed M2L split: each tile's far offsets in m2l_parts consecutive
+  // M2L split: each tile's far offsets in m2l_parts consecutive
   // ranges, one work item each; part 0 writes Loc, part p > 0 the rows
   // (p - 1) * locx_rows + (target row - locx_first) of LocX
   int m2l_parts;

@@ -390,6 +390,12 @@ __device__ inline f4 mfma16x16x4(float a, float b, f4 c) {
 // lane group g = lane/16 holds k = 16c + 4g + s at step s, so both operands
 // are fetched as 4 consecutive values per lane.  FOLD: FP32 partial sums are
 // added into FP64 accumulators after every far offset.
+// The matrix cores bound it (70% of their FP64 peak at 1M particles, order
+// 7), so what a small plan lacks is items: the job's m2l_parts cuts each
+// tile's offsets into ranges, one item each (4,000 particles, height 4,
+// order 5: evaluation 2250 -> 210 us; the 1M cube's last round: 38.2 -> 34.7
+// ms), and 16-target groups without a source at an offset are skipped (the
+// last tiles of a parity, the coarse levels, points on surfaces).
 // Build-time tuning of the dense kernel: wavefronts per SIMD the register
 // allocation must allow, and whether FP64 double-buffers the B fragments.
 #ifndef FMM_M2L_WAVES_PER_SIMD
@@ -398,6 +404,13 @@ __device__ inline f4 mfma16x16x4(float a, float b, f4 c) {
 #ifndef FMM_M2L_F64_PREFETCH_B
 #define FMM_M2L_F64_PREFETCH_B 1
 #endif
+
+// The FP64 row that target cell t of offset range `part` accumulates into: the
+// cell's local expansion for part 0, else the part's own row of LocX.
+__device__ inline double* m2l_out_row(const JobDev& J, int part, int64_t t) {
+  if (part == 0) return J.Loc + t * J.ld;
+  return J.LocX + (int64_t(part - 1) * J.locx_rows + (t - J.locx_first)) * J.ld;
+}
 
 template <typename T, int MTW, bool FOLD>
 __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
@@ -417,7 +430,13 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
     }
     const int k = step_find(*tab, b);
     const JobDev& J = jobs[tab->job[k]];
-    const int local = b - tab->start[k] + tab->first[k];
+    // parts outermost: consecutive items take the same offset range of
+    // neighbouring tiles, so the workgroups of an XCD share its operators in L2
+    const int parts = J.m2l_parts;
+    const int per_part = (tab->start[k + 1] - tab->start[k]) / parts;
+    const int rel = b - tab->start[k];
+    const int part = rel / per_part;
+    const int local = rel % per_part + tab->first[k] / parts;
     const int tile = local / J.nmb, mb = local % J.nmb;
     const int MT = J.mt, KC = J.kc, ld = J.ld;
     const int mt0 = (mb * 4 + wave) * MTW;
@@ -438,13 +457,18 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
       }
 
     const int nact = wuni(gld(J.tile_nact + tile));
+    const int ia0 = int(int64_t(part) * nact / parts), ia1 = int(int64_t(part + 1) * nact / parts);
     const unsigned char* act = J.tile_act + int64_t(tile) * kSlots;
+    const unsigned char* gmask = J.tile_gmask + int64_t(tile) * kSlots;
     const int* srcb = J.tile_src + int64_t(tile) * kSlots * kTileN;
     const int* kidp = J.slot_kid + tl.parity * kSlots;
 
-    for (int ia = 0; ia < nact; ++ia) {
+    for (int ia = ia0; ia < ia1; ++ia) {
       const int s = wuni(int(gld(act + ia)));
       const int kid = wuni(gld(kidp + s));
+      // the 16-target groups with a source at this offset; the others'
+      // products are zero (a wavefront-uniform branch per group and chunk)
+      const int gm = wuni(int(gld(gmask + ia)));
       const T* bptr[4];
       for (int j = 0; j < 4; ++j)
         bptr[j] = Wp + int64_t(gld(srcb + s * kTileN + 16 * j + c16)) * ld + 4 * g;
@@ -473,11 +497,13 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
                             : T4{0, 0, 0, 0};
         }
 #pragma unroll
-        for (int st = 0; st < 4; ++st)
+        for (int j = 0; j < 4; ++j) {
+          if (!((gm >> j) & 1)) continue;
 #pragma unroll
-          for (int i = 0; i < MTW; ++i)
+          for (int st = 0; st < 4; ++st)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
+            for (int i = 0; i < MTW; ++i) acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
+        }
         if (more) {
           if (kPrefetchB)
             for (int j = 0; j < 4; ++j) bv[j] = bn[kPrefetchB ? j : 0];
@@ -501,7 +527,7 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
     for (int j = 0; j < 4; ++j) {
       const int col = 16 * j + c16;
       if (col >= tl.count) continue;
-      double* out = J.Loc + int64_t(gld(J.tgt + tl.first + col)) * ld;
+      double* out = m2l_out_row(J, part, gld(J.tgt + tl.first + col));
 #pragma unroll
       for (int i = 0; i < MTW; ++i) {
         if (i >= nmt) continue;  // constant trip count keeps acc[] in registers
@@ -552,6 +578,8 @@ int m2l_nmb(int mt) {
   const int w = m2l_mtw(mt);
   return (mt + 4 * w - 1) / (4 * w);
 }
+
+double m2l_item_flops(int mt) { return 2.0 * kTileN * (64.0 * m2l_mtw(mt)) * (16.0 * mt); }
 
 // Every job in `tab` must have the same order (same packed operator shape).
 void launch_m2l_step(int order, bool fp32, const JobDev* jobs, const StepTab* tab, int grid,
@@ -1216,13 +1244,9 @@ __device__ inline void svd_meta_fill(const SvdItem& I, int nact, SvdMeta* meta) 
   __syncthreads();
 }
 
-// The FP64 row that target column col of the item accumulates into: the
-// cell's local expansion for part 0, else the part's own row of LocX.
+// The FP64 row that target column col of the item accumulates into.
 __device__ inline double* svd_out_row(const SvdItem& I, int col) {
-  const JobDev& J = *I.J;
-  const int64_t t = gld(J.tgt + I.tl.first + col);
-  if (I.part == 0) return J.Loc + t * J.ld;
-  return J.LocX + (int64_t(I.part - 1) * J.locx_rows + (t - J.locx_first)) * J.ld;
+  return m2l_out_row(*I.J, I.part, gld(I.J->tgt + I.tl.first + col));
 }
 
 // Item `it` of the launch; false when its N-group holds no target column

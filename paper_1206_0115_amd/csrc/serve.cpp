@@ -241,6 +241,11 @@ bool fmm_server_s::admit() {
       any = true;
       continue;
     }
+    if (size_t(p->bytes) > budget && !p->svd && p->job_h.m2l_parts > 1) {
+      // the split's partial sums are optional: never a reason to refuse
+      p->dense_parts_max = 1;
+      upload_job(p, plan_stream);
+    }
     r->bytes = int64_t(p->bytes);
     if (size_t(r->bytes) > budget) {
       fmm_release(p);
