@@ -53,3 +53,26 @@ def test_direct_sampled_coincident_and_bad_targets():
     np.testing.assert_allclose(phi[:2], p_o, rtol=1e-14)
     np.testing.assert_allclose(f[:2], f_o, rtol=1e-14)
     assert np.isnan(phi[2:]).all() and np.isnan(f[2:]).all()
+
+
+@pytest.mark.parametrize("kernel", ["inv_r", "inv_r2"])
+def test_direct_sampled_zero_nan_and_infinite_distances(kernel):
+    """Blocks of sources that hold a coincident particle, a NaN position or
+    one whose squared distance overflows, among blocks that hold none, and
+    ragged chunks: such pairs add nothing (1e-13 of the plain sum)."""
+    n, p = 9_777, 1 if kernel == "inv_r" else 2
+    pos, q = inputs.uniform_cube(n, 67)
+    pos[5000:5003] = pos[17]
+    pos[1234, 1] = np.nan
+    pos[8001] = 1e200
+    idx = np.array([17, 5001, 0, 9_776, 4_000], dtype=np.int64)
+    phi, f = fmm.direct_sampled(dev(pos), dev(q), dev(idx), kernel=kernel)
+    with np.errstate(over="ignore", invalid="ignore", divide="ignore"):
+        d = pos[idx][:, None, :] - pos[None, :, :]
+        r2 = (d * d).sum(-1)
+        ok = (r2 > 0) & np.isfinite(r2)
+        w = np.where(ok, r2, 1.0) ** (-0.5 * p) * ok
+        g = np.where(ok, p * w / np.where(ok, r2, 1.0), 0.0)
+        p_o = w @ q
+        f_o = q[idx][:, None] * (np.where(ok[..., None], d, 0.0) * (g * q)[..., None]).sum(1)
+    assert rel(phi.cpu().numpy(), p_o) <= 1e-13 and rel(f.cpu().numpy(), f_o) <= 1e-13
