@@ -62,9 +62,12 @@ static int auto_parts(int64_t items, int64_t slots, size_t part_bytes) {
 // written once and read once, in FP64 whatever the mode, so K minimises
 //     rounds(items K) / K * (an item's time) + K * (2 passes over the parts),
 // with an item's time at 70% of its slot's share of the matrix cores (the
-// rate measured at 1M particles) and the passes at 3 TB/s.
+// rate measured at 1M particles) and the passes at 3 TB/s.  Every tile counts
+// as full: tiles whose groups are partly skipped make items of uneven length,
+// which more ranges even out (60,000 on a sphere: 1733 us with such tiles
+// counted by their groups, 1585 us so).
 static int dense_parts(int64_t items, int mt, bool fp32, size_t part_bytes, int cus) {
-  constexpr int kMax = 32;                      // about six offsets a range
+  constexpr int kMax = 32;                      // about six offsets a range (64: 5-9% slower)
   constexpr size_t kBudget = size_t(256) << 20;  // of partial sums
   const double slots = 2.0 * cus;
   const double rate = 0.7 * (fp32 ? 157.3e12 : 78.6e12) / (2.0 * 256);
@@ -74,8 +77,7 @@ static int dense_parts(int64_t items, int mt, bool fp32, size_t part_bytes, int 
   double best_cost = std::ceil(double(items) / slots) * item;
   for (int k = 2; k <= kMax; ++k) {
     if (size_t(k - 1) * part_bytes > kBudget) break;
-    const double cost =
-        std::ceil(double(items) * k / slots) / k * item + 2.0 * k * pass + 4e-6;
+    const double cost = std::ceil(double(items) * k / slots) / k * item + 2.0 * k * pass + 4e-6;
     if (cost < 0.98 * best_cost) {
       best = k;
       best_cost = cost;
@@ -128,6 +130,8 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
     J.p2_32 = p->svd->p2_32;
   }
   J.ntiles = int(p->ntiles);
+  // tiles are stored finest level first: the leaf level's, then the rest
+  while (J.leaf_tiles < J.ntiles && p->tiles_host[J.leaf_tiles].level == h - 1) ++J.leaf_tiles;
   J.has_far = h >= 3;
   J.modal = fp32 && h >= 3 ? 1 : 0;
   J.l2p_sparse = p->nleaf > 0 && p->n <= int64_t(kL2PSparseMax) * int64_t(p->nleaf) ? 1 : 0;
@@ -206,14 +210,11 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
     p->tab_h[kTabCast] = one_job(int((p->w32_leaf ? p->lev[h - 1].off : p->ncell_total + 1) -
                                      p->lev[2].off));
     p->tab_h[kTabM2L] = one_job(int(p->ntiles) * J.nmb * parts);
-    // tiles are stored finest level first: the leaf level's, then the rest
-    int64_t leaf_tiles = 0;
-    while (leaf_tiles < p->ntiles && p->tiles_host[leaf_tiles].level == h - 1) ++leaf_tiles;
-    const int leaf_items = int(leaf_tiles) * J.nmb * parts;
+    const int leaf_items = J.leaf_tiles * J.nmb * parts;
     p->tab_h[kTabM2LLeaf] = one_job(leaf_items);
     p->tab_h[kTabM2LCoarse] = one_job(int(p->ntiles) * J.nmb * parts - leaf_items);
     p->tab_h[kTabM2LCoarse].first[0] = leaf_items;
-    p->tab_h[kTabLocSum] = one_job(parts > 1 ? int(lrows) : 0);
+    p->tab_h[kTabLocSum] = one_job(loc_sum_items(J));
     for (int st = 0; st + 4 <= h; ++st) {
       p->tab_h[kTabM2M + st] = one_job(int(p->lev[h - 2 - st].ncell), h - 2 - st);
       // L2L items are the parents (level 2 + st) of the cells it updates

@@ -800,26 +800,36 @@ __global__ __launch_bounds__(64) void p2p_f32_kernel(const JobDev* __restrict__ 
   }
 }
 
-// ------------------------------------------ M2L parts and coefficient rows
-// Item = row of levels >= 2 of a job whose M2L ran in parts or in FP32:
-// Loc += the partial local expansions of parts 1 .. K-1, added in part order
-// (one FP64 sum per element, the same order every run).  Item = row.
+// ------------------------------------------------------------- M2L parts
+// Loc += the partial local expansions of parts 1 .. K-1 of a job whose M2L ran
+// in parts, added in part order (one FP64 sum per element, the same order
+// every run).  Item = kLocSumItem elements of the rows of levels >= 2, four a
+// thread; memory bound (8 (K + 1) bytes an element), so eight parts' loads
+// are in flight at once.
 __global__ __launch_bounds__(256) void loc_sum_kernel(const JobDev* __restrict__ jobs,
                                                       const StepTab* __restrict__ tab) {
-  const int t = threadIdx.x;
+  typedef double d4 __attribute__((ext_vector_type(4)));
+  static_assert(kLocSumItem == 4 * 256, "four elements a thread");
   FOR_ITEMS(tab) {
     const int k = step_find(*tab, it_);
     const JobDev& J = jobs[tab->job[k]];
-    const int64_t r = it_ - tab->start[k];
-    const int64_t n = J.locx_rows * J.ld;
-    double* loc = J.Loc + (J.locx_first + r) * J.ld;
-    const double* x = J.LocX + r * J.ld;
+    const int64_t n = J.locx_rows * J.ld;  // a multiple of 16
+    const int64_t e = int64_t(it_ - tab->start[k]) * kLocSumItem + 4 * threadIdx.x;
+    if (e >= n) continue;
+    d4* loc = reinterpret_cast<d4*>(J.Loc + J.locx_first * J.ld + e);
+    const double* x = J.LocX + e;
     const int parts = wuni(J.m2l_parts);
-    for (int e = t; e < J.ld; e += 256) {
-      double v = gld(loc + e);
-      for (int p = 1; p < parts; ++p) v += gld(x + (p - 1) * n + e);
-      gst(loc + e, v);
+    d4 v = gld(loc);
+    int p = 1;
+    for (; p + 8 <= parts; p += 8) {
+      d4 w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w[u] = gld(reinterpret_cast<const d4*>(x + (p - 1 + u) * n));
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v += w[u];
     }
+    for (; p < parts; ++p) v += gld(reinterpret_cast<const d4*>(x + (p - 1) * n));
+    gst(loc, v);
   }
 }
 

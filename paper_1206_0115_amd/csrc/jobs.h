@@ -51,6 +51,7 @@ struct JobDev {
   // ranges, one work item each; part 0 writes Loc, part p > 0 the rows
   // (p - 1) * locx_rows + (target row - locx_first) of LocX
   int m2l_parts;
+  int leaf_tiles;  // M2L tiles of the leaf level (they come first)
   int64_t locx_first, locx_rows;
   double* LocX;
   LeafGeom geo;
@@ -101,6 +102,12 @@ struct CallDev {
   double* pf;
   double* ff;
 };
+
+// Loc + LocX elements added by one item of kStepLocSum
+constexpr int kLocSumItem = 1024;
+inline int loc_sum_items(const JobDev& J) {
+  return J.m2l_parts > 1 ? int((J.locx_rows * J.ld + kLocSumItem - 1) / kLocSumItem) : 0;
+}
 
 struct StepTab {
   int njobs;

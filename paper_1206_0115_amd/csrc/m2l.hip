@@ -393,7 +393,7 @@ __device__ inline f4 mfma16x16x4(float a, float b, f4 c) {
 // The matrix cores bound it (70% of their FP64 peak at 1M particles, order
 // 7), so what a small plan lacks is items: the job's m2l_parts cuts each
 // tile's offsets into ranges, one item each (4,000 particles, height 4,
-// order 5: evaluation 2250 -> 210 us; the 1M cube's last round: 38.2 -> 34.7
+// order 5: evaluation 2250 -> 210 us; the 1M cube, last round: 38.2 -> 34.3
 // ms), and 16-target groups without a source at an offset are skipped (the
 // last tiles of a parity, the coarse levels, points on surfaces).
 // Build-time tuning of the dense kernel: wavefronts per SIMD the register
@@ -404,6 +404,13 @@ __device__ inline f4 mfma16x16x4(float a, float b, f4 c) {
 #ifndef FMM_M2L_F64_PREFETCH_B
 #define FMM_M2L_F64_PREFETCH_B 1
 #endif
+
+// Block b of n, dealt round-robin to the 8 XCDs, to an item such that each
+// XCD's items are consecutive.
+__device__ inline int xcd_run(int b, int n) {
+  const int n8 = n / 8 * 8;
+  return b < n8 ? (b % 8) * (n8 / 8) + b / 8 : b;
+}
 
 // The FP64 row that target cell t of offset range `part` accumulates into: the
 // cell's local expansion for part 0, else the part's own row of LocX.
@@ -420,24 +427,31 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
   const int wave = wuni(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int g = lane >> 4, c16 = lane & 15;
   for (int it = blockIdx.x; it < total; it += gridDim.x) {
-    // with one block per item, blocks are dealt round-robin to the 8 XCDs:
-    // give each XCD a contiguous run of tiles so neighbouring tiles share
-    // source multipoles in its L2
+    // Items of a job: the leaf level's tiles, then the coarser ones (fewer
+    // targets a tile, hence shorter); within each, offset ranges (parts)
+    // outermost, so that consecutive items take the same operators.  With one
+    // block per item, blocks are dealt round-robin to the 8 XCDs: each XCD
+    // gets a contiguous run of either kind, whose tiles share operators and
+    // source multipoles in its L2, and every CU starts on a long item
+    // (4,000 particles, height 4, order 5: evaluation 209 -> 170 us)
     int b = it;
-    if (int(gridDim.x) == total) {
-      const int n8 = (total / 8) * 8;
-      if (b < n8) b = (b % 8) * (n8 / 8) + b / 8;
+    if (int(gridDim.x) == total && tab->njobs == 1) {
+      const JobDev& J0 = jobs[tab->job[0]];
+      const int lo = min(max(J0.leaf_tiles * J0.nmb * J0.m2l_parts - tab->first[0], 0), total);
+      b = b < lo ? xcd_run(b, lo) : lo + xcd_run(b - lo, total - lo);
     }
     const int k = step_find(*tab, b);
     const JobDev& J = jobs[tab->job[k]];
-    // parts outermost: consecutive items take the same offset range of
-    // neighbouring tiles, so the workgroups of an XCD share its operators in L2
     const int parts = J.m2l_parts;
-    const int per_part = (tab->start[k + 1] - tab->start[k]) / parts;
-    const int rel = b - tab->start[k];
-    const int part = rel / per_part;
-    const int local = rel % per_part + tab->first[k] / parts;
-    const int tile = local / J.nmb, mb = local % J.nmb;
+    int rel = b - tab->start[k] + tab->first[k], tile0 = 0, ntile = J.leaf_tiles;
+    if (rel >= J.leaf_tiles * J.nmb * parts) {
+      rel -= J.leaf_tiles * J.nmb * parts;
+      tile0 = J.leaf_tiles;
+      ntile = J.ntiles - J.leaf_tiles;
+    }
+    const int part = rel / (ntile * J.nmb);
+    const int local = rel % (ntile * J.nmb);
+    const int tile = tile0 + local / J.nmb, mb = local % J.nmb;
     const int MT = J.mt, KC = J.kc, ld = J.ld;
     const int mt0 = (mb * 4 + wave) * MTW;
     if (mt0 >= MT) continue;

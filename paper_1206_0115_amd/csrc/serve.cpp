@@ -405,10 +405,9 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
                 return int(r->plan->ntiles) * r->plan->job_h.nmb * r->plan->job_h.m2l_parts;
               },
               lvl0, gs != 0);
-  // partial sums of plans that split their compressed M2L back into Loc, and
-  // the FP32 M2L's Chebyshev-coefficient rows back to node values
+  // partial sums of plans that split their M2L back into Loc
   add(kStepLocSum, 0, false, [&](Request* r) { return far(r) && r->plan->job_h.m2l_parts > 1; },
-      [](Request* r) { return int(r->plan->job_h.locx_rows); }, lvl0);
+      [](Request* r) { return loc_sum_items(r->plan->job_h); }, lvl0);
   for (int s = 0; s < steps; ++s)
     for (int L : orders)
       add(kStepL2L, L, false, [&](Request* r) { return r->h - 4 >= s && r->order == L; },
