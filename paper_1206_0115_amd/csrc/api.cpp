@@ -94,7 +94,7 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
   J.px = p->px;
   J.py = p->py;
   J.pz = p->pz;
-  J.prel = p->prel;
+  J.q32 = p->q32;
   J.qs = p->qs;
   J.perm = p->perm;
   J.leaf_start = p->leaf_start;
@@ -222,10 +222,18 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
     }
   }
   ++p->job_version;  // a captured evaluation graph no longer matches
-  if (!p->job_d) p->job_d = static_cast<JobDev*>(p->alloc(sizeof(JobDev)));
-  if (!p->tab_d) p->tab_d = static_cast<StepTab*>(p->alloc(sizeof(StepTab) * kTabCount));
-  FMM_HIP_CHECK(hipMemcpyAsync(p->job_d, &p->job_h, sizeof(JobDev), hipMemcpyHostToDevice, s));
-  FMM_HIP_CHECK(hipMemcpyAsync(p->tab_d, p->tab_h, sizeof(p->tab_h), hipMemcpyHostToDevice, s));
+  // the job and its tables in one block, one transfer from pinned memory
+  constexpr size_t kTabsAt = (sizeof(JobDev) + 255) / 256 * 256;
+  constexpr size_t kBytes = kTabsAt + sizeof(StepTab) * kTabCount;
+  if (!p->job_d) {
+    char* d = static_cast<char*>(p->alloc(kBytes));
+    p->job_d = reinterpret_cast<JobDev*>(d);
+    p->tab_d = reinterpret_cast<StepTab*>(d + kTabsAt);
+  }
+  char* stage = static_cast<char*>(pinned_staging(kBytes));
+  std::memcpy(stage, &p->job_h, sizeof(JobDev));
+  std::memcpy(stage + kTabsAt, p->tab_h, sizeof(p->tab_h));
+  FMM_HIP_CHECK(hipMemcpyAsync(p->job_d, stage, kBytes, hipMemcpyHostToDevice, s));
   FMM_HIP_CHECK(hipStreamSynchronize(s));
   if (split_oom)
     throw FmmError{FMM_ERR_OOM, "no device memory for the partial buffers of the M2L split; "
@@ -347,8 +355,9 @@ fmm_plan_t fmm_plan_stream(const double* positions, int64_t n, int height, int o
       p->Loc = static_cast<double*>(p->alloc(sizeof(double) * rows * ld));
       // the multipole buffers depend on the precision mode: ensure_w
     }
-    fmm::upload_job(p, stream);  // ends with a synchronisation of the stream
-    fmm::plan_stats(p);
+    // the job description follows with the precision mode, which sizes the
+    // multipole buffers it names (there are none below height 3)
+    if (height < 3) fmm::upload_job(p, stream);
     p->done = fmm::event_get(p->device);
     p->ev_fork = fmm::event_get(p->device);
     p->ev_join = fmm::event_get(p->device);
@@ -610,7 +619,7 @@ static int eval_common(fmm_plan_t p, const double* q, double* phi, double* f, do
     FMM_HIP_CHECK(hipGetDevice(&dev));
     if (dev != p->device) return fail(FMM_ERR_ARG, "plan belongs to another device");
     // the first evaluation of a plan whose mode was never set allocates here
-    if (ensure_w(p, s)) fmm::upload_job(p, s);
+    if (ensure_w(p, s) || !p->job_d) fmm::upload_job(p, s);
     if (p->graph_on && phi && !fmm::timing_hooks_set())
       fmm::evaluate_graph(p, q, phi, f, s);
     else

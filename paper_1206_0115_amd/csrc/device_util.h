@@ -76,6 +76,17 @@ __device__ __forceinline__ void gst(T* p, const T& v) {
   *(FMM_GLOBAL T*)(p) = v;
 }
 
+// Orders the LDS accesses of every lane of this wavefront before the call
+// ahead of those after it.  The hardware performs a wavefront's LDS accesses
+// in order; the fences keep the compiler from reusing a value loaded before
+// them or moving an access across them, which it may otherwise do whenever
+// it can show that no access of the lane itself conflicts.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A value known to be the same in every lane of the wavefront, as a scalar:
 // branches on it are scalar branches (no lane masking) and loops on it run
 // on the scalar unit.

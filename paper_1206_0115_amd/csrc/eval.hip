@@ -134,18 +134,6 @@ __global__ FMM_P2M_BOUNDS void p2m_kernel(const JobDev* __restrict__ jobs,
 // form.
 constexpr int kTransThreads = 512;  // one wavefront per child of a cell
 
-// Orders the LDS accesses of every lane of this wavefront before the call
-// ahead of those after it.  The hardware performs a wavefront's LDS accesses
-// in order; the fences keep the compiler from reusing a value loaded before
-// them or moving an access across them, which it may otherwise do whenever
-// it can show that no access of the lane itself conflicts (the rotated
-// contraction below reads what other lanes wrote).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // out[m][a][b] = sum_q M[m][q] in[a][b][q] for one L^3 cube: a contraction
 // along the last index whose result has its indices rotated, so that the
 // next one again runs along the last index (three restore the order).  M is
@@ -692,8 +680,7 @@ __device__ __forceinline__ void p2p_leaf(const JobDev& J, int a, src4* src) {
   }
   // the source charge as stored (FP32 or FP64), widened when staged
   typedef typename std::conditional<F32, float, double>::type QT;
-  const QT* qsrc = F32 ? reinterpret_cast<const QT*>(J.prel) : reinterpret_cast<const QT*>(J.qs);
-  const int qstride = F32 ? 4 : 1, qoff = F32 ? 3 : 0;
+  const QT* qsrc = F32 ? reinterpret_cast<const QT*>(J.q32) : reinterpret_cast<const QT*>(J.qs);
   for (int tb = 0; tb < nt; tb += 64) {
     const int ti = tb + (lane % P);
     const bool valid = ti < nt;
@@ -710,7 +697,7 @@ __device__ __forceinline__ void p2p_leaf(const JobDev& J, int a, src4* src) {
       rx = gld(px + jb + lane);
       ry = gld(py + jb + lane);
       rz = gld(pz + jb + lane);
-      rq = gld(qsrc + int64_t(jb + lane) * qstride + qoff);
+      rq = gld(qsrc + jb + lane);
     }
     while (have) {
       const int ccnt = cnt, csl = sl;
@@ -725,7 +712,7 @@ __device__ __forceinline__ void p2p_leaf(const JobDev& J, int a, src4* src) {
         rx = gld(px + jb + lane);
         ry = gld(py + jb + lane);
         rz = gld(pz + jb + lane);
-        rq = gld(qsrc + int64_t(jb + lane) * qstride + qoff);
+        rq = gld(qsrc + jb + lane);
       }
       const int npass = (ccnt + S - 1) / S;
       if (F32) {
@@ -842,7 +829,7 @@ __device__ inline void gather_chunk(const JobDev& J, const double* q, int chunk)
   if (i >= J.n) return;
   const double v = q[J.perm[i]];
   J.qs[i] = v;
-  J.prel[i].w = float(v);
+  J.q32[i] = float(v);
 }
 
 // out[perm[i]] = near[i] + far[i] in FP64; far is absent below height 3.

@@ -2,7 +2,7 @@
 //
 // Data layout in HBM (all device arrays, one plan):
 //   particles   sorted by (Morton key, input index); SoA px/py/pz (f64),
-//               prel (float4: leaf-local x,y,z + charge) for the FP32 near field
+//               qs (f64) and q32 (f32, for the FP32 near field)
 //   cells       level-major "global cell ids": gid = lev_off[l] + i, i the
 //               Morton rank within level l; one extra all-zero row at
 //               gid = ncell_total stands in for absent M2L sources
@@ -195,7 +195,7 @@ struct fmm_plan_s {
 
   // particles
   double *px = nullptr, *py = nullptr, *pz = nullptr;
-  float4* prel = nullptr;
+  float* q32 = nullptr;
   int* perm = nullptr;
   uint64_t* keys = nullptr;
   int64_t nleaf = 0;
@@ -224,7 +224,6 @@ struct fmm_plan_s {
   int64_t m2l_groups = 0;          // 16-target groups at active slots
   int64_t m2l_groups_empty = 0;    // ... of them without a source
   bool m2l_gskip = false;          // the compressed M2L skips the empty groups
-  const unsigned long long* stats_stage = nullptr;  // unread statistics (plan_stats)
   int64_t pairs_by_kid[fmm::kOffsets] = {0};  // far pairs per packed operator
 
   // evaluation buffers
@@ -279,10 +278,6 @@ struct fmm_plan_s {
 namespace fmm {
 // plan construction (plan.hip)
 void build_plan(fmm_plan_s* p, const double* positions, hipStream_t stream);
-// The plan's statistics (pair counts), copied to the calling thread's
-// pinned staging by build_plan without a wait: read them once the stream
-// has been synchronised, before that staging is used again.
-void plan_stats(fmm_plan_s* p);
 // evaluation (eval.hip)
 void evaluate(fmm_plan_s* p, const double* q, double* phi, double* f,
               double* phi_n, double* f_n, double* phi_f, double* f_f,

@@ -31,7 +31,7 @@ struct JobDev {
   const double* px;
   const double* py;
   const double* pz;
-  float4* prel;
+  float* q32;
   double* qs;
   const int* perm;
   const int* leaf_start;

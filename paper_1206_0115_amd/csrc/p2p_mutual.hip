@@ -141,7 +141,7 @@ __device__ __forceinline__ void mutual_item(const JobDev& J, int a, int b, src4*
       xa = gld(px + i);
       ya = gld(py + i);
       za = gld(pz + i);
-      qa = F32 ? T(gld(&J.prel[i].w)) : T(gld(J.qs + i));
+      qa = F32 ? T(gld(J.q32 + i)) : T(gld(J.qs + i));
     }
     Acc<double> A64{0.0, 0.0, 0.0, 0.0};
     for (int jb = 0; jb < nb; jb += 64) {
@@ -152,7 +152,7 @@ __device__ __forceinline__ void mutual_item(const JobDev& J, int a, int b, src4*
         u.x = gld(px + j);
         u.y = gld(py + j);
         u.z = gld(pz + j);
-        u.w = F32 ? q_slot(gld(&J.prel[j].w)) : gld(J.qs + j);
+        u.w = F32 ? q_slot(gld(J.q32 + j)) : gld(J.qs + j);
       }
       __syncthreads();  // the previous chunk's reads (and output updates) are done
       src[lane] = u;

@@ -72,27 +72,82 @@ __global__ void scan_add_kernel(T* __restrict__ out, const T* __restrict__ offs,
   if (i < n) out[i] += offs[i / kScanTile];
 }
 
+// n <= kScanSmall values in one workgroup (one launch instead of three).
+constexpr int64_t kScanSmall = 16384;
+constexpr int kScanSmallThreads = 1024, kScanSmallItems = 8;
+
+template <typename T>
+__global__ __launch_bounds__(kScanSmallThreads) void scan_small_kernel(const T* __restrict__ in,
+                                                                       T* __restrict__ out,
+                                                                       int n) {
+  __shared__ T wave_sum[kScanSmallThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  T carry = 0;
+  for (int base = 0; base < n; base += kScanSmallThreads * kScanSmallItems) {
+    const int i0 = base + threadIdx.x * kScanSmallItems;
+    T v[kScanSmallItems], sum = 0;
+    for (int k = 0; k < kScanSmallItems; ++k) {
+      v[k] = i0 + k < n ? in[i0 + k] : T(0);
+      sum += v[k];
+    }
+    T x = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+      const T y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) wave_sum[wave] = x;
+    __syncthreads();
+    T run = carry + x - sum, all = 0;
+    for (int w = 0; w < kScanSmallThreads / 64; ++w) {
+      if (w < wave) run += wave_sum[w];
+      all += wave_sum[w];
+    }
+    carry += all;
+    for (int k = 0; k < kScanSmallItems; ++k) {
+      if (i0 + k < n) out[i0 + k] = run;
+      run += v[k];
+    }
+    __syncthreads();
+  }
+}
+
 // Exclusive scan of n values (in may equal out).  Temporary blocks are kept
 // in `tmp` and released by the caller after the stream has drained.
 template <typename T>
 void exclusive_scan(const T* in, T* out, int64_t n, hipStream_t s,
                     std::vector<void*>& tmp) {
   if (n <= 0) return;
+  if (n <= kScanSmall) {
+    scan_small_kernel<T><<<1, kScanSmallThreads, 0, s>>>(in, out, int(n));
+    FMM_HIP_CHECK(hipGetLastError());
+    return;
+  }
   const int64_t tiles = (n + kScanTile - 1) / kScanTile;
   T* sums = static_cast<T*>(dev_alloc(sizeof(T) * tiles));
   tmp.push_back(sums);
   scan_tiles_kernel<T><<<dim3(unsigned(tiles)), kScanThreads, 0, s>>>(in, out, sums, n);
   FMM_HIP_CHECK(hipGetLastError());
-  if (tiles > 1) {
-    exclusive_scan<T>(sums, sums, tiles, s, tmp);
-    scan_add_kernel<T><<<dim3(unsigned((n + 255) / 256)), 256, 0, s>>>(out, sums, n);
-    FMM_HIP_CHECK(hipGetLastError());
-  }
+  exclusive_scan<T>(sums, sums, tiles, s, tmp);
+  scan_add_kernel<T><<<dim3(unsigned((n + 255) / 256)), 256, 0, s>>>(out, sums, n);
+  FMM_HIP_CHECK(hipGetLastError());
 }
 
 // ------------------------------------------------------------- bounding box
+// Statistics gathered while a plan is built: far pairs per level, near pairs,
+// active M2L slots, far pairs per operator, 16-target groups and empty ones.
+constexpr int kStats = kMaxHeight + 4 + kOffsets;
+
+// What the host needs to size the plan, read back once.
+struct PlanHead {
+  double box[6];  // per-axis minima, then maxima
+  int bad;        // a position is NaN or infinite
+  int pad;
+  int cells[8 * kMaxHeight];  // cells of level l and child parity c at 8 l + c
+};
+
 constexpr int kBoxBlocks = 512;
 
+// Per block: minima, maxima and whether a position is not finite.
 __global__ __launch_bounds__(256) void bbox_partial_kernel(
     const double* __restrict__ pos, int64_t n, double* __restrict__ part,
     int* __restrict__ bad) {
@@ -109,7 +164,7 @@ __global__ __launch_bounds__(256) void bbox_partial_kernel(
       mx[d] = fmax(mx[d], v);
     }
   }
-  if (nonfinite) atomicOr(bad, 1);
+  nonfinite = __syncthreads_or(nonfinite);
   for (int d = 0; d < 3; ++d) {
     smin[d][threadIdx.x] = mn[d];
     smax[d][threadIdx.x] = mx[d];
@@ -123,30 +178,12 @@ __global__ __launch_bounds__(256) void bbox_partial_kernel(
       }
     __syncthreads();
   }
-  if (threadIdx.x == 0)
+  if (threadIdx.x == 0) {
     for (int d = 0; d < 3; ++d) {
       part[6 * blockIdx.x + d] = smin[d][0];
       part[6 * blockIdx.x + 3 + d] = smax[d][0];
     }
-}
-
-__global__ __launch_bounds__(256) void bbox_final_kernel(const double* __restrict__ part,
-                                                         int nb, double* __restrict__ out) {
-  __shared__ double s[256];
-  for (int d = 0; d < 6; ++d) {
-    double v = d < 3 ? INFINITY : -INFINITY;
-    for (int b = threadIdx.x; b < nb; b += 256)
-      v = d < 3 ? fmin(v, part[6 * b + d]) : fmax(v, part[6 * b + d]);
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (threadIdx.x < o)
-        s[threadIdx.x] = d < 3 ? fmin(s[threadIdx.x], s[threadIdx.x + o])
-                               : fmax(s[threadIdx.x], s[threadIdx.x + o]);
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[d] = s[0];
-    __syncthreads();
+    bad[blockIdx.x] = nonfinite;
   }
 }
 
@@ -162,24 +199,65 @@ __device__ __host__ inline double root_side(const double* box) {
   return L == 0.0 ? 1.0 : L;
 }
 
-__global__ void keys_kernel(const double* __restrict__ pos, int64_t n,
-                            const double* __restrict__ box, int bits,
-                            uint64_t* __restrict__ keys, int* __restrict__ idx) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+// kKeyItems particles a workgroup.  Every workgroup reduces the nb partial
+// boxes itself (at most 24 KiB, from L2), which saves a launch; the first
+// also writes the result to the head and clears the statistics.
+constexpr int kKeyItems = 2048;
+
+__global__ __launch_bounds__(256) void keys_kernel(
+    const double* __restrict__ pos, int64_t n, const double* __restrict__ part,
+    const int* __restrict__ bad, int nb, int bits, uint64_t* __restrict__ keys,
+    int* __restrict__ idx, PlanHead* __restrict__ head,
+    unsigned long long* __restrict__ stats) {
+  __shared__ double red[6][4];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  double v[6];
+  for (int d = 0; d < 6; ++d) v[d] = d < 3 ? INFINITY : -INFINITY;
+  int nonfinite = 0;
+  for (int b = t; b < nb; b += 256) {
+    for (int d = 0; d < 6; ++d) {
+      const double x = part[6 * b + d];
+      v[d] = d < 3 ? fmin(v[d], x) : fmax(v[d], x);
+    }
+    nonfinite |= bad[b];
+  }
+  for (int o = 32; o > 0; o >>= 1)
+    for (int d = 0; d < 6; ++d) {
+      const double x = __shfl_xor(v[d], o, 64);
+      v[d] = d < 3 ? fmin(v[d], x) : fmax(v[d], x);
+    }
+  if (lane == 0)
+    for (int d = 0; d < 6; ++d) red[d][wave] = v[d];
+  nonfinite = __syncthreads_or(nonfinite);
+  double box[6];
+  for (int d = 0; d < 6; ++d) {
+    box[d] = red[d][0];
+    for (int w = 1; w < 4; ++w) box[d] = d < 3 ? fmin(box[d], red[d][w]) : fmax(box[d], red[d][w]);
+  }
+  if (blockIdx.x == 0) {
+    if (t == 0) {
+      for (int d = 0; d < 6; ++d) head->box[d] = box[d];
+      head->bad = nonfinite;
+    }
+    for (int e = t; e < kStats; e += 256) stats[e] = 0;
+  }
   const double side = double(int64_t(1) << bits);
   const int64_t kmax = (int64_t(1) << bits) - 1;
-  const double lo[3] = {box[0], box[1], box[2]};
   const double L = root_side(box);
-  uint32_t k3[3];
-  for (int d = 0; d < 3; ++d) {
-    double u = (pos[3 * i + d] - lo[d]) / L;
-    int64_t k = int64_t(floor(u * side));
-    k = k > kmax ? kmax : (k < 0 ? 0 : k);
-    k3[d] = uint32_t(k);
+  const int64_t base = int64_t(blockIdx.x) * kKeyItems;
+  for (int e = t; e < kKeyItems; e += 256) {
+    const int64_t i = base + e;
+    if (i >= n) break;
+    uint32_t k3[3];
+    for (int d = 0; d < 3; ++d) {
+      double u = (pos[3 * i + d] - box[d]) / L;
+      int64_t k = int64_t(floor(u * side));
+      k = k > kmax ? kmax : (k < 0 ? 0 : k);
+      k3[d] = uint32_t(k);
+    }
+    keys[i] = morton3(k3[0], k3[1], k3[2], bits);
+    idx[i] = int(i);
   }
-  keys[i] = morton3(k3[0], k3[1], k3[2], bits);
-  idx[i] = int(i);
 }
 
 // ------------------------------------------------------- stable radix sort
@@ -188,18 +266,20 @@ __global__ void keys_kernel(const double* __restrict__ pos, int64_t n,
 // input index.  Per pass: tile histograms, one exclusive scan over the
 // digit-major histogram, then a scatter that ranks equal digits in input
 // order with wavefront ballots.
+// A tile is 256 IT particles, IT = 4 up to kRsSmall of them (a tile is a
+// chain of IT ranked steps: 1,000 particles 11 -> 4.6 us a scatter) and 16 above.
 constexpr int kRsThreads = 256;
-constexpr int kRsItems = 16;
-constexpr int kRsTile = kRsThreads * kRsItems;
+constexpr int64_t kRsSmall = 262144;
 
+template <int IT>
 __global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(
     const uint64_t* __restrict__ keys, int64_t n, int shift, int mask,
     int ntiles, int* __restrict__ hist) {
   __shared__ int h[256];
   h[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t base = int64_t(blockIdx.x) * kRsTile;
-  for (int it = 0; it < kRsItems; ++it) {
+  const int64_t base = int64_t(blockIdx.x) * (kRsThreads * IT);
+  for (int it = 0; it < IT; ++it) {
     int64_t i = base + int64_t(it) * kRsThreads + threadIdx.x;
     if (i < n) atomicAdd(&h[int((keys[i] >> shift) & uint64_t(mask))], 1);
   }
@@ -207,6 +287,7 @@ __global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(
   hist[int64_t(threadIdx.x) * ntiles + blockIdx.x] = h[threadIdx.x];
 }
 
+template <int IT>
 __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
     const uint64_t* __restrict__ kin, const int* __restrict__ vin,
     uint64_t* __restrict__ kout, int* __restrict__ vout, int64_t n, int shift,
@@ -216,8 +297,8 @@ __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   base_d[tid] = offs[int64_t(tid) * ntiles + blockIdx.x];
   const uint64_t lt = (uint64_t(1) << lane) - 1;
-  const int64_t tbase = int64_t(blockIdx.x) * kRsTile;
-  for (int it = 0; it < kRsItems; ++it) {
+  const int64_t tbase = int64_t(blockIdx.x) * (kRsThreads * IT);
+  for (int it = 0; it < IT; ++it) {
     for (int k = lane; k < 256; k += 64) wcnt[wave][k] = 0;
     const int64_t i = tbase + int64_t(it) * kRsThreads + tid;
     const bool valid = i < n;
@@ -253,238 +334,236 @@ __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
   }
 }
 
-// Sorts n pairs by the digits of (key >> shift) & mask over `bits` bits.
-// Returns the buffers holding the result (either the inputs or the outputs).
-static void radix_sort(uint64_t*& k, int*& v, uint64_t*& k2, int*& v2,
-                       int64_t n, int bits, hipStream_t s,
-                       std::vector<void*>& tmp) {
-  if (n <= 1 || bits <= 0) return;
-  const int ntiles = ceil_div(n, kRsTile);
+// Passes of a sort by `bits` key bits.
+static int radix_passes(int64_t n, int bits) { return n <= 1 ? 0 : (bits + 7) / 8; }
+
+// Sorts n pairs by the low `bits` bits of the key, from (k, v) through
+// (k2, v2) and back: after an odd number of passes the result is in the
+// second pair of buffers.
+template <int IT>
+static void radix_sort(uint64_t* k, int* v, uint64_t* k2, int* v2, int64_t n, int bits,
+                       hipStream_t s, std::vector<void*>& tmp) {
+  const int ntiles = ceil_div(n, kRsThreads * IT);
   int* hist = static_cast<int*>(dev_alloc(sizeof(int) * 256 * size_t(ntiles)));
   tmp.push_back(hist);
-  for (int shift = 0; shift < bits; shift += 8) {
-    const int db = std::min(8, bits - shift);
+  for (int p = 0; p < radix_passes(n, bits); ++p) {
+    const int shift = 8 * p, db = std::min(8, bits - shift);
     const int mask = (1 << db) - 1;
-    radix_hist_kernel<<<ntiles, kRsThreads, 0, s>>>(k, n, shift, mask, ntiles, hist);
+    radix_hist_kernel<IT><<<ntiles, kRsThreads, 0, s>>>(k, n, shift, mask, ntiles, hist);
     FMM_HIP_CHECK(hipGetLastError());
     exclusive_scan<int>(hist, hist, int64_t(256) * ntiles, s, tmp);
-    radix_scatter_kernel<<<ntiles, kRsThreads, 0, s>>>(k, v, k2, v2, n, shift, mask,
-                                                       ntiles, hist);
+    radix_scatter_kernel<IT><<<ntiles, kRsThreads, 0, s>>>(k, v, k2, v2, n, shift, mask,
+                                                           ntiles, hist);
     FMM_HIP_CHECK(hipGetLastError());
     std::swap(k, k2);
     std::swap(v, v2);
   }
 }
 
-// ------------------------------------------------------------- segments
-// Unique values of (keys >> shift) over a sorted array: segment flags, their
-// exclusive scan, then the unique keys, each segment's first index, and the
-// segment of every element.
-__global__ void seg_flags_kernel(const uint64_t* __restrict__ keys, int64_t m,
-                                 int shift, int* __restrict__ flags) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  flags[i] = (i == 0 || (keys[i] >> shift) != (keys[i - 1] >> shift)) ? 1 : 0;
+// ------------------------------------------------- the cells of every level
+// Particle i of the sorted keys k starts a new cell at level l exactly when
+// (k[i] >> 3(h-1-l)) != (k[i-1] >> 3(h-1-l)), i.e. at every level from
+// first(i) = h-1-floor(t/3) on, t the highest bit in which k[i] and k[i-1]
+// differ (level 0 for i = 0, none if the keys are equal).  Two passes over the
+// particles build every level at once: cells_count_kernel counts, per
+// workgroup, the cells starting at each level and child parity,
+// cells_scan_kernel scans those counts over the workgroups (and totals them
+// for the host), and cells_emit_kernel ranks the starting particles with
+// wavefront ballots and writes the cells' keys, first particles, children,
+// parents, lookup entries and places among the M2L targets.  All of it is
+// bound by launches and memory latency; level by level from the leaves it
+// took three times the launches and a second read-back (whole step: 1,000
+// particles 427 -> 236 us, 20,000 612 -> 446 us, 1M 5.17 -> 4.92 ms).
+constexpr int kCellThreads = 256, kCellWaves = kCellThreads / 64;
+
+// 64-particle rounds a wavefront takes in a row
+static int cell_rounds(int64_t n) {
+  return n <= (int64_t(1) << 18) ? 4 : n <= (int64_t(1) << 24) ? 16 : 64;
 }
 
-__global__ void seg_emit_kernel(const uint64_t* __restrict__ keys, int64_t m,
-                                int shift, const int* __restrict__ flags,
-                                const int* __restrict__ pos,
-                                uint64_t* __restrict__ ukeys,
-                                int* __restrict__ first, int* __restrict__ seg) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const int id = pos[i] + flags[i] - 1;
-  if (seg) seg[i] = id;
-  if (flags[i]) {
-    ukeys[id] = keys[i] >> shift;
-    first[id] = int(i);
-  }
+__device__ inline int first_level(const uint64_t* __restrict__ keys, int64_t i, uint64_t key,
+                                  int h) {
+  if (i == 0) return 0;
+  const uint64_t x = key ^ keys[i - 1];
+  return x ? h - 1 - (63 - __clzll(x)) / 3 : h;
 }
 
-__global__ void seg_count_kernel(const int* __restrict__ flags,
-                                 const int* __restrict__ pos, int64_t m,
-                                 int* __restrict__ count) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *count = pos[m - 1] + flags[m - 1];
-}
-
-__global__ void set_int_kernel(int* __restrict__ p, int v) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
-}
-
-// ------------------------------------------------- all coarser levels at once
-// Leaf i of the sorted unique leaf keys k starts a new cell at level l exactly
-// when (k[i] >> 3(h-1-l)) != (k[i-1] >> 3(h-1-l)), i.e. at every level from
-// h-1-floor(t/3) on, t the highest bit in which k[i] and k[i-1] differ.  One
-// pass therefore gives the segment flags of every level l = 0 .. h-2, stored
-// level-major: flags[l * nl + i].
-// Also counts the cells of every level >= 2 by child parity (the M2L tile
-// layout), so that one read-back after the scan brings both.
-__global__ __launch_bounds__(256) void level_flags_kernel(const uint64_t* __restrict__ lk,
-                                                          int64_t nl, int h,
-                                                          int64_t* __restrict__ flags,
-                                                          int* __restrict__ pcount) {
-  __shared__ int hist[8 * kMaxHeight];
-  for (int e = threadIdx.x; e < 8 * kMaxHeight; e += blockDim.x) hist[e] = 0;
+// count[c * nblocks + b]: cells of level c / 8 and child parity c % 8 that
+// start in workgroup b.  Also gathers the sorted positions.
+__global__ __launch_bounds__(kCellThreads) void cells_count_kernel(
+    const uint64_t* __restrict__ keys, const int* __restrict__ perm,
+    const double* __restrict__ pos, int64_t n, int h, int rounds, double* __restrict__ px,
+    double* __restrict__ py, double* __restrict__ pz, int* __restrict__ count) {
+  __shared__ int cnt[8 * kMaxHeight];
+  for (int e = threadIdx.x; e < 8 * h; e += kCellThreads) cnt[e] = 0;
   __syncthreads();
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < nl) {
-    int first = 0;  // leaf 0 starts a cell at every level
-    if (i > 0) first = h - 1 - (63 - __clzll(lk[i] ^ lk[i - 1])) / 3;
-    for (int l = 0; l < h - 1; ++l) flags[int64_t(l) * nl + i] = l >= first ? 1 : 0;
-    // cells starting at this leaf, levels 2 .. h-1 (every leaf is a cell)
-    for (int l = first > 2 ? first : 2; l < h; ++l)
-      atomicAdd(&hist[8 * l + int((lk[i] >> (3 * (h - 1 - l))) & 7u)], 1);
+  const int64_t base = int64_t(blockIdx.x) * kCellThreads * rounds;
+  for (int r = 0; r < rounds; ++r) {
+    const int64_t i = base + int64_t(r) * kCellThreads + threadIdx.x;
+    if (i >= n) break;
+    const uint64_t key = keys[i];
+    const int64_t j = perm[i];
+    const double x = pos[3 * j], y = pos[3 * j + 1], z = pos[3 * j + 2];
+    for (int l = first_level(keys, i, key, h); l < h; ++l)
+      atomicAdd(&cnt[8 * l + int((key >> (3 * (h - 1 - l))) & 7u)], 1);
+    px[i] = x;
+    py[i] = y;
+    pz[i] = z;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < 8 * kMaxHeight; e += blockDim.x)
-    if (hist[e]) atomicAdd(&pcount[e], hist[e]);
+  for (int e = threadIdx.x; e < 8 * h; e += kCellThreads)
+    count[int64_t(e) * gridDim.x + blockIdx.x] = cnt[e];
 }
 
-struct LevelOut {
+// Workgroup c: exclusive scan of count[c * nb ...], the total to the head.
+__global__ __launch_bounds__(kScanThreads) void cells_scan_kernel(int* __restrict__ count,
+                                                                  int nb,
+                                                                  PlanHead* __restrict__ head) {
+  __shared__ int lds[kScanThreads / 64];
+  int* col = count + int64_t(blockIdx.x) * nb;
+  int carry = 0;
+  for (int b0 = 0; b0 < nb; b0 += kScanThreads) {
+    const int b = b0 + int(threadIdx.x);
+    const int v = b < nb ? col[b] : 0;
+    int total;
+    const int before = block_exclusive_scan<int>(v, lds, &total);
+    if (b < nb) col[b] = carry + before;
+    carry += total;
+  }
+  if (threadIdx.x == 0) head->cells[blockIdx.x] = carry;
+}
+
+struct CellsOut {
   uint64_t* keys[kMaxHeight];
   int* child_start[kMaxHeight];  // [ncell_l + 1] first child at level l+1
   int* parent[kMaxHeight];       // [ncell_l] cell of level l-1 containing it
+  int* table[kMaxHeight];        // dense key -> index, or null
+  int ncell[kMaxHeight];
+  int off[kMaxHeight];           // global id of the level's first cell
+  int tstart[8 * kMaxHeight];    // first target of (level, parity) in tgt
+  int* leaf_start;
+  int* tgt;                      // null below height 3
 };
 
-// After an exclusive scan S of the concatenated flags: ncell of every level,
-// count[l] = S[(l+1) nl] - S[l nl] (the last level up to the total).
-__global__ void level_counts_kernel(const int64_t* __restrict__ flags,
-                                    const int64_t* __restrict__ S, int64_t nl, int h,
-                                    int64_t* __restrict__ count) {
-  const int l = threadIdx.x;
-  if (l >= h - 1) return;
-  const int64_t end = l + 1 < h - 1 ? S[int64_t(l + 1) * nl]
-                                    : S[int64_t(h - 1) * nl - 1] + flags[int64_t(h - 1) * nl - 1];
-  count[l] = end - S[int64_t(l) * nl];
-}
-
-// Level l (grid y) and leaf i: the unique keys and child offsets of level l
-// and the parents of level l+1, all read off the flags and their scan.
-__global__ void level_emit_kernel(const uint64_t* __restrict__ lk, int64_t nl, int h,
-                                  const int64_t* __restrict__ flags,
-                                  const int64_t* __restrict__ S, LevelOut out) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int l = blockIdx.y;
-  if (i >= nl) return;
-  const int64_t at = int64_t(l) * nl + i;
-  const int64_t f = flags[at];
-  const int64_t pos = S[at] - S[int64_t(l) * nl];
-  const bool leaf1 = l + 1 == h - 1;  // level l+1 is the leaf level
-  const bool f1 = leaf1 ? true : flags[at + nl] != 0;
-  const int64_t c1 = leaf1 ? i : S[at + nl] - S[int64_t(l + 1) * nl];
-  if (f) {
-    out.keys[l][pos] = lk[i] >> (3 * (h - 1 - l));
-    out.child_start[l][pos] = int(c1);  // a level-l boundary is one at l+1
+__global__ __launch_bounds__(kCellThreads) void cells_emit_kernel(
+    const uint64_t* __restrict__ keys, int64_t n, int h, int rounds,
+    const int* __restrict__ count, CellsOut out) {
+  // cells of (level, parity), and of the level, that start before the
+  // wavefront's next round
+  __shared__ int pbase[kCellWaves][8 * kMaxHeight];
+  __shared__ int lbase[kCellWaves][kMaxHeight];
+  const int lane = threadIdx.x & 63, wave = wuni(int(threadIdx.x >> 6));
+  for (int e = threadIdx.x; e < kCellWaves * 8 * kMaxHeight; e += kCellThreads)
+    pbase[e / (8 * kMaxHeight)][e % (8 * kMaxHeight)] = 0;
+  __syncthreads();
+  const int64_t base = (int64_t(blockIdx.x) * kCellWaves + wave) * 64 * rounds;
+  for (int r = 0; r < rounds; ++r) {
+    const int64_t i = base + 64 * r + lane;
+    if (i >= n) break;
+    const uint64_t key = keys[i];
+    for (int l = first_level(keys, i, key, h); l < h; ++l)
+      atomicAdd(&pbase[wave][8 * l + int((key >> (3 * (h - 1 - l))) & 7u)], 1);
   }
-  if (f1) out.parent[l + 1][c1] = int(pos + f - 1);
-}
-
-// child_start[l][ncell_l] = ncell_{l+1} for every level l < h-1
-__global__ void level_ends_kernel(LevelOut out, const int64_t* __restrict__ count, int h,
-                                  int64_t nl) {
-  const int l = threadIdx.x;
-  if (l >= h - 1) return;
-  out.child_start[l][count[l]] = int(l + 1 < h - 1 ? count[l + 1] : nl);
-}
-
-// ------------------------------------------------------------ gathers
-__global__ void gather_pos_kernel(const double* __restrict__ pos,
-                                  const int* __restrict__ perm, int64_t n,
-                                  double* __restrict__ px, double* __restrict__ py,
-                                  double* __restrict__ pz) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int64_t j = perm[i];
-  px[i] = pos[3 * j];
-  py[i] = pos[3 * j + 1];
-  pz[i] = pos[3 * j + 2];
-}
-
-// Leaf-local FP32 coordinates for the FP32 near field: x - c_leaf.
-__global__ void rel_coords_kernel(const double* __restrict__ px,
-                                  const double* __restrict__ py,
-                                  const double* __restrict__ pz,
-                                  const int* __restrict__ leaf_start,
-                                  const uint64_t* __restrict__ leaf_keys,
-                                  int64_t nleaf, int bits, double lo0,
-                                  double lo1, double lo2, double w,
-                                  float4* __restrict__ prel) {
-  const int64_t a = blockIdx.x;
-  if (a >= nleaf) return;
-  int c[3];
-  demorton3(leaf_keys[a], bits, c);
-  const double cx = lo0 + (c[0] + 0.5) * w, cy = lo1 + (c[1] + 0.5) * w,
-               cz = lo2 + (c[2] + 0.5) * w;
-  for (int i = leaf_start[a] + threadIdx.x; i < leaf_start[a + 1]; i += blockDim.x)
-    prel[i] = make_float4(float(px[i] - cx), float(py[i] - cy), float(pz[i] - cz), 0.f);
-}
-
-// ---------------------------------------------------------- lookup tables
-struct TableSet {
-  const uint64_t* keys[kMaxHeight];
-  int* table[kMaxHeight];
-  int64_t cum[kMaxHeight + 1];  // prefix sums of the cell counts of the levels
-  int nlev;
-};
-
-// table[l][key] = index, for the levels of the set (thread = one cell)
-__global__ void table_scatter_kernel(TableSet t) {
-  const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (g >= t.cum[t.nlev]) return;
-  int l = 0;
-  while (g >= t.cum[l + 1]) ++l;
-  const int64_t i = g - t.cum[l];
-  t.table[l][t.keys[l][i]] = int(i);
+  __syncthreads();
+  for (int e = threadIdx.x; e < 8 * h; e += kCellThreads) {
+    int run = count[int64_t(e) * gridDim.x + blockIdx.x];
+    for (int w = 0; w < kCellWaves; ++w) {
+      const int c = pbase[w][e];
+      pbase[w][e] = run;
+      run += c;
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < kCellWaves * h; e += kCellThreads) {
+    int v = 0;
+    for (int c = 0; c < 8; ++c) v += pbase[e / h][8 * (e % h) + c];
+    lbase[e / h][e % h] = v;
+  }
+  __syncthreads();
+  const uint64_t lt = (uint64_t(1) << lane) - 1;
+  for (int r = 0; r < rounds; ++r) {
+    if (base + 64 * r >= n) break;  // the same for the whole wavefront
+    const int64_t i = base + 64 * r + lane;
+    const uint64_t key = i < n ? keys[i] : 0;
+    const int first = i < n ? first_level(keys, i, key, h) : h;
+    uint64_t above = 0;      // lanes that start a cell of the level above
+    int above_base = 0;      // its lbase before this round
+    int above_cell = 0;      // the cell of the level above this lane starts
+    for (int l = 0; l < h; ++l) {
+      const int lb = lbase[wave][l];
+      const uint64_t mask = __ballot(first <= l);
+      if (mask) {
+        const uint64_t ck = key >> (3 * (h - 1 - l));
+        const int par = int(ck & 7u);
+        uint64_t peers = mask;
+        for (int b = 0; b < 3; ++b) {
+          const uint64_t m = __ballot((par >> b) & 1);
+          peers &= (par >> b) & 1 ? m : ~m;
+        }
+        const int c = lb + __popcll(mask & lt);
+        if (first <= l) {
+          const int pb = pbase[wave][8 * l + par];
+          out.keys[l][c] = ck;
+          if (out.table[l]) out.table[l][ck] = c;
+          if (l > 0) out.parent[l][c] = above_base + __popcll(above & (lt | (lt + 1))) - 1;
+          if (first < l) out.child_start[l - 1][above_cell] = c;
+          if (l == h - 1) out.leaf_start[c] = int(i);
+          if (l >= 2 && out.tgt)
+            out.tgt[out.tstart[8 * l + par] + pb + __popcll(peers & lt)] = out.off[l] + c;
+          above_cell = c;
+          if ((peers & lt) == 0) pbase[wave][8 * l + par] = pb + __popcll(peers);
+        }
+        if (lane == 0) lbase[wave][l] = lb + __popcll(mask);
+        wave_lds_sync();
+      }
+      above = mask;
+      above_base = lb;
+    }
+  }
+  if (blockIdx.x == 0)
+    for (int l = threadIdx.x; l < h; l += kCellThreads) {
+      if (l < h - 1) out.child_start[l][out.ncell[l]] = out.ncell[l + 1];
+      else out.leaf_start[out.ncell[l]] = int(n);
+    }
 }
 
 // ------------------------------------------------------------ near lists
 // near[a][s], s = (dx+1)*9 + (dy+1)*3 + (dz+1): the leaf at offset (dx,dy,dz)
-// or -1.  Also counts directed particle pairs n_a * sum_b n_b.
-__global__ void near_kernel(LevelDev leaves, const int* __restrict__ leaf_start,
-                            int* __restrict__ near,
-                            unsigned long long* __restrict__ pairs) {
-  const int a = blockIdx.x * blockDim.x + threadIdx.x;
+// or -1.  Also counts directed particle pairs n_a * sum_b n_b.  A workgroup
+// takes 64 leaves, its threads their 27 slots side by side (one thread per
+// leaf ran 27 lookups in a row: 1,000 particles 14 -> 5.4 us).
+constexpr int kNearLeaves = 64;
+
+__global__ __launch_bounds__(256) void near_kernel(LevelDev leaves,
+                                                   const int* __restrict__ leaf_start,
+                                                   int* __restrict__ near,
+                                                   unsigned long long* __restrict__ pairs) {
+  __shared__ int cell[kNearLeaves][4];  // coordinates, particles
+  __shared__ unsigned long long sum[4];
+  const int a0 = blockIdx.x * kNearLeaves, t = threadIdx.x;
+  if (t < kNearLeaves && a0 + t < leaves.ncell) {
+    const int a = a0 + t;
+    demorton3(leaves.keys[a], leaves.bits, cell[t]);
+    cell[t][3] = leaf_start[a + 1] - leaf_start[a];
+  }
+  __syncthreads();
   unsigned long long cnt = 0;
-  if (a < leaves.ncell) {
-    int c[3];
-    demorton3(leaves.keys[a], leaves.bits, c);
-    long long src = 0;
-    for (int s = 0; s < 27; ++s) {
-      const int b = level_find_xyz(leaves, c[0] + s / 9 - 1, c[1] + (s / 3) % 3 - 1,
-                                   c[2] + s % 3 - 1);
-      near[27 * a + s] = b;
-      if (b >= 0) src += leaf_start[b + 1] - leaf_start[b];
-    }
-    cnt = (unsigned long long)(leaf_start[a + 1] - leaf_start[a]) * (unsigned long long)src;
+  const int na = min(kNearLeaves, leaves.ncell - a0);
+  for (int e = t; e < 27 * na; e += 256) {
+    const int k = e / 27, s = e % 27;
+    const int b = level_find_xyz(leaves, cell[k][0] + s / 9 - 1, cell[k][1] + (s / 3) % 3 - 1,
+                                 cell[k][2] + s % 3 - 1);
+    near[27 * int64_t(a0) + e] = b;
+    if (b >= 0)
+      cnt += (unsigned long long)cell[k][3] * (unsigned long long)(leaf_start[b + 1] - leaf_start[b]);
   }
   for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-  if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(pairs, cnt);
+  if ((t & 63) == 0) sum[t >> 6] = cnt;
+  __syncthreads();
+  if (t == 0) atomicAdd(pairs, sum[0] + sum[1] + sum[2] + sum[3]);
 }
 
 // ------------------------------------------------------------ M2L tiles
-struct CellLevels {
-  const uint64_t* keys[kMaxHeight];
-  int64_t off[kMaxHeight + 1];  // global id of each level's first cell
-};
-
-// Cells of levels >= 2 (global ids g from off[2]): sort key (level - 2, child
-// parity) for the M2L target order, the gid as value.
-__global__ __launch_bounds__(256) void parity_keys_kernel(CellLevels c, int h,
-                                                          uint64_t* __restrict__ key,
-                                                          int* __restrict__ val) {
-  const int64_t m = c.off[h] - c.off[2];
-  const int64_t j = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j < m) {
-    const int64_t g = c.off[2] + j;
-    int l = 2;
-    while (g >= c.off[l + 1]) ++l;
-    const int par = int(c.keys[l][g - c.off[l]] & 7u);
-    key[j] = uint64_t((l - 2) << 3 | par);
-    val[j] = int(g);
-  }
-}
-
 // One workgroup of eight wavefronts per tile.  Lane j of every wavefront owns
 // target j; wavefront w looks up the source cells of the slots w, w+8, ...
 // (zero row if absent) and marks the slots with at least one source; then
@@ -600,7 +679,7 @@ void build_plan(fmm_plan_s* p, const double* pos, hipStream_t s) {
     std::vector<void*>& v;
     hipStream_t s;
     ~TmpGuard() {
-      (void)hipStreamSynchronize(s);
+      (void)hipStreamSynchronize(s);  // returns at once where s has drained
       for (void* q : v) dev_free(q);
     }
   } guard{tmp, s};
@@ -614,199 +693,124 @@ void build_plan(fmm_plan_s* p, const double* pos, hipStream_t s) {
   const int h = p->height;
   const int bits = h - 1;
 
-  // --- root box (the only input-dependent host decision) ---
+  // --- root box and keys (non-finite positions give clamped keys, and the
+  // plan is rejected at the read-back) ---
   const int nb = int(std::min<int64_t>(kBoxBlocks, (n + 255) / 256));
-  double* part = static_cast<double*>(talloc(sizeof(double) * 6 * nb + 64));
-  double* box = static_cast<double*>(talloc(sizeof(double) * 8));
-  int* bad = static_cast<int*>(talloc(sizeof(int)));
-  FMM_HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), s));
+  double* part = static_cast<double*>(talloc(sizeof(double) * 6 * nb));
+  int* bad = static_cast<int*>(talloc(sizeof(int) * nb));
+  PlanHead* head = static_cast<PlanHead*>(talloc(sizeof(PlanHead)));
+  unsigned long long* stats =
+      static_cast<unsigned long long*>(talloc(sizeof(unsigned long long) * kStats));
   bbox_partial_kernel<<<nb, 256, 0, s>>>(pos, n, part, bad);
   FMM_HIP_CHECK(hipGetLastError());
-  bbox_final_kernel<<<1, 256, 0, s>>>(part, nb, box);
-  FMM_HIP_CHECK(hipGetLastError());
-  // the box stays on the device until the leaf count comes back: keys are
-  // formed from it there (non-finite positions give clamped keys, and the
-  // plan is rejected at that first read-back)
-  // pinned staging: [0] box (6 doubles), [6] bad flag and leaf count
-  char* stage = static_cast<char*>(pinned_staging(4096));
-  double* hb = reinterpret_cast<double*>(stage);
-  int* hcount = reinterpret_cast<int*>(stage + 64);
 
-  // --- keys and the stable sort ---
-  uint64_t* k1 = static_cast<uint64_t*>(talloc(sizeof(uint64_t) * n));
-  uint64_t* k2 = static_cast<uint64_t*>(talloc(sizeof(uint64_t) * n));
-  int* v1 = static_cast<int*>(talloc(sizeof(int) * n));
-  int* v2 = static_cast<int*>(talloc(sizeof(int) * n));
-  keys_kernel<<<grid_for(n, 256), 256, 0, s>>>(pos, n, box, bits, k1, v1);
-  FMM_HIP_CHECK(hipGetLastError());
-  radix_sort(k1, v1, k2, v2, n, 3 * bits, s, tmp);
-
+  // --- the stable sort, which ends in the plan's own buffers ---
   p->keys = static_cast<uint64_t*>(p->alloc(sizeof(uint64_t) * n));
   p->perm = static_cast<int*>(p->alloc(sizeof(int) * n));
-  FMM_HIP_CHECK(hipMemcpyAsync(p->keys, k1, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, s));
-  FMM_HIP_CHECK(hipMemcpyAsync(p->perm, v1, sizeof(int) * n, hipMemcpyDeviceToDevice, s));
+  uint64_t* kt = static_cast<uint64_t*>(talloc(sizeof(uint64_t) * n));
+  int* vt = static_cast<int*>(talloc(sizeof(int) * n));
+  const bool odd = radix_passes(n, 3 * bits) % 2 != 0;
+  uint64_t *k1 = odd ? kt : p->keys, *k2 = odd ? p->keys : kt;
+  int *v1 = odd ? vt : p->perm, *v2 = odd ? p->perm : vt;
+  keys_kernel<<<grid_for(n, kKeyItems), 256, 0, s>>>(pos, n, part, bad, nb, bits, k1, v1, head,
+                                                     stats);
+  FMM_HIP_CHECK(hipGetLastError());
+  if (n <= kRsSmall) radix_sort<4>(k1, v1, k2, v2, n, 3 * bits, s, tmp);
+  else radix_sort<16>(k1, v1, k2, v2, n, 3 * bits, s, tmp);
+
+  // --- sorted positions, cell counts of every level and child parity ---
   p->px = static_cast<double*>(p->alloc(sizeof(double) * n));
   p->py = static_cast<double*>(p->alloc(sizeof(double) * n));
   p->pz = static_cast<double*>(p->alloc(sizeof(double) * n));
-  gather_pos_kernel<<<grid_for(n, 256), 256, 0, s>>>(pos, p->perm, n, p->px, p->py, p->pz);
+  const int rounds = cell_rounds(n);
+  const int cb = int(grid_for(n, kCellThreads * rounds));
+  int* count = static_cast<int*>(talloc(sizeof(int) * 8 * size_t(h) * cb));
+  cells_count_kernel<<<cb, kCellThreads, 0, s>>>(p->keys, p->perm, pos, n, h, rounds, p->px,
+                                                 p->py, p->pz, count);
   FMM_HIP_CHECK(hipGetLastError());
-
-  // --- leaves: the unique keys of the sorted particles ---
-  int* flags = static_cast<int*>(talloc(sizeof(int) * n));
-  int* scn = static_cast<int*>(talloc(sizeof(int) * n));
-  int* cnt_d = static_cast<int*>(talloc(sizeof(int) * 4));
-  uint64_t* lk = static_cast<uint64_t*>(talloc(sizeof(uint64_t) * n));
-  int* ls = static_cast<int*>(talloc(sizeof(int) * (n + 1)));
-  seg_flags_kernel<<<grid_for(n, 256), 256, 0, s>>>(p->keys, n, 0, flags);
+  cells_scan_kernel<<<8 * h, kScanThreads, 0, s>>>(count, cb, head);
   FMM_HIP_CHECK(hipGetLastError());
-  exclusive_scan<int>(flags, scn, n, s, tmp);
-  seg_emit_kernel<<<grid_for(n, 256), 256, 0, s>>>(p->keys, n, 0, flags, scn, lk, ls, nullptr);
-  FMM_HIP_CHECK(hipGetLastError());
-  seg_count_kernel<<<1, 64, 0, s>>>(flags, scn, n, cnt_d);
-  FMM_HIP_CHECK(hipGetLastError());
-  // first read-back: the root box, the non-finite flag and the leaf count
-  FMM_HIP_CHECK(hipMemcpyAsync(hb, box, sizeof(double) * 6, hipMemcpyDeviceToHost, s));
-  FMM_HIP_CHECK(hipMemcpyAsync(hcount, bad, sizeof(int), hipMemcpyDeviceToHost, s));
-  FMM_HIP_CHECK(hipMemcpyAsync(hcount + 1, cnt_d, sizeof(int), hipMemcpyDeviceToHost, s));
-  FMM_HIP_CHECK(hipStreamSynchronize(s));
-  if (hcount[0]) throw FmmError{FMM_ERR_ARG, "positions contain NaN or Inf"};
-  for (int d = 0; d < 3; ++d) p->lo[d] = hb[d];
-  const double L = root_side(hb);
-  p->L = L;
-  p->nleaf = hcount[1];
-  const int64_t nl = p->nleaf;
-  set_int_kernel<<<1, 64, 0, s>>>(ls + nl, int(n));
-  FMM_HIP_CHECK(hipGetLastError());
-  p->leaf_start = static_cast<int*>(p->alloc(sizeof(int) * (nl + 1)));
-  FMM_HIP_CHECK(hipMemcpyAsync(p->leaf_start, ls, sizeof(int) * (nl + 1),
-                               hipMemcpyDeviceToDevice, s));
-  LevelView* lev = p->lev;
-  lev[h - 1].ncell = nl;
-  lev[h - 1].keys = static_cast<uint64_t*>(p->alloc(sizeof(uint64_t) * nl));
-  FMM_HIP_CHECK(hipMemcpyAsync(lev[h - 1].keys, lk, sizeof(uint64_t) * nl,
-                               hipMemcpyDeviceToDevice, s));
-  if (h >= 2) {
-    // every coarser level from the leaf keys: flags, one scan, one count
-    // read-back, then keys, child offsets and parents in one pass
-    const int64_t tot = int64_t(h - 1) * nl;
-    int64_t* fl = static_cast<int64_t*>(talloc(sizeof(int64_t) * tot));
-    int64_t* S = static_cast<int64_t*>(talloc(sizeof(int64_t) * tot));
-    int64_t* cnt = static_cast<int64_t*>(talloc(sizeof(int64_t) * kMaxHeight));
-    int* pc = static_cast<int*>(talloc(sizeof(int) * 8 * kMaxHeight));
-    FMM_HIP_CHECK(hipMemsetAsync(pc, 0, sizeof(int) * 8 * kMaxHeight, s));
-    level_flags_kernel<<<grid_for(nl, 256), 256, 0, s>>>(lk, nl, h, fl, pc);
-    FMM_HIP_CHECK(hipGetLastError());
-    exclusive_scan<int64_t>(fl, S, tot, s, tmp);
-    level_counts_kernel<<<1, 64, 0, s>>>(fl, S, nl, h, cnt);
-    FMM_HIP_CHECK(hipGetLastError());
-    int64_t* hcnt = reinterpret_cast<int64_t*>(stage + 128);  // pinned
-    FMM_HIP_CHECK(hipMemcpyAsync(hcnt, cnt, sizeof(int64_t) * (h - 1), hipMemcpyDeviceToHost, s));
-    // per-(level, parity) cell counts for the M2L tiles, in the same read-back
-    FMM_HIP_CHECK(hipMemcpyAsync(stage + 512, pc, sizeof(int) * 8 * kMaxHeight,
-                                 hipMemcpyDeviceToHost, s));
-    FMM_HIP_CHECK(hipStreamSynchronize(s));
-    LevelOut out{};
-    // every count first: level l's loop iteration sizes level l+1's parents.
-    // A tree has one root and at most 8x (and at least as many) cells per
-    // level down to the leaves; anything else would make the kernels below
-    // write out of bounds.
-    for (int l = 0; l < h - 1; ++l) {
-      const int64_t below = l + 1 < h - 1 ? hcnt[l + 1] : nl;
-      if (hcnt[l] < 1 || hcnt[l] > below || (l == 0 && hcnt[l] != 1))
-        throw FmmError{FMM_ERR_HIP, "inconsistent octree level counts"};
-      lev[l].ncell = hcnt[l];
-    }
-    for (int l = 0; l < h - 1; ++l) {
-      lev[l].keys = static_cast<uint64_t*>(p->alloc(sizeof(uint64_t) * hcnt[l]));
-      lev[l].child_start = static_cast<int*>(p->alloc(sizeof(int) * (hcnt[l] + 1)));
-      lev[l + 1].parent = static_cast<int*>(p->alloc(sizeof(int) * lev[l + 1].ncell));
-      out.keys[l] = lev[l].keys;
-      out.child_start[l] = lev[l].child_start;
-      out.parent[l + 1] = lev[l + 1].parent;
-    }
-    level_emit_kernel<<<dim3(grid_for(nl, 256), unsigned(h - 1)), 256, 0, s>>>(lk, nl, h, fl, S,
-                                                                               out);
-    FMM_HIP_CHECK(hipGetLastError());
-    level_ends_kernel<<<1, 64, 0, s>>>(out, cnt, h, nl);
-    FMM_HIP_CHECK(hipGetLastError());
-  }
-  int64_t off = 0;
-  for (int l = 0; l < h; ++l) {
-    lev[l].off = off;
-    off += lev[l].ncell;
-  }
-  p->ncell_total = off;
-  if (off >= (int64_t(1) << 31) - 1) throw FmmError{FMM_ERR_ARG, "too many cells"};
-
   // dense lookup tables for levels with at most 2^24 key slots, one block
-  LevelDev ldev[kMaxHeight];
-  TableSet ts{};
   int64_t tslots = 0;
-  for (int l = 0; l < h; ++l) {
-    ldev[l] = {lev[l].keys, nullptr, int(lev[l].ncell), l};
-    if (3 * l <= 24) tslots += int64_t(1) << (3 * l);
-  }
+  for (int l = 0; l < h && 3 * l <= 24; ++l) tslots += int64_t(1) << (3 * l);
   int* tables = static_cast<int*>(p->alloc(sizeof(int) * tslots));
   FMM_HIP_CHECK(hipMemsetAsync(tables, 0xff, sizeof(int) * tslots, s));  // all -1
+
+  // --- the read-back that sizes the plan ---
+  // pinned staging of the calling thread: the head, later the statistics
+  static_assert(sizeof(PlanHead) <= 4096 && sizeof(unsigned long long) * kStats <= 4096, "staging");
+  char* stage = static_cast<char*>(pinned_staging(4096));
+  const PlanHead* hd = reinterpret_cast<const PlanHead*>(stage);
+  FMM_HIP_CHECK(hipMemcpyAsync(stage, head, sizeof(PlanHead), hipMemcpyDeviceToHost, s));
+  FMM_HIP_CHECK(hipStreamSynchronize(s));
+  if (hd->bad) throw FmmError{FMM_ERR_ARG, "positions contain NaN or Inf"};
+  for (int d = 0; d < 3; ++d) p->lo[d] = hd->box[d];
+  p->L = root_side(hd->box);
+  LevelView* lev = p->lev;
+  CellsOut out{};
+  int64_t off = 0;
   tslots = 0;
-  for (int l = 0; l < h && 3 * l <= 24; ++l) {
-    lev[l].lookup = tables + tslots;
-    ldev[l].table = lev[l].lookup;
-    ts.keys[ts.nlev] = lev[l].keys;
-    ts.table[ts.nlev] = lev[l].lookup;
-    ts.cum[ts.nlev + 1] = ts.cum[ts.nlev] + lev[l].ncell;
-    ++ts.nlev;
-    tslots += int64_t(1) << (3 * l);
+  // A tree has one root and at least as many cells per level down to the
+  // leaves, at most n; anything else would make the kernels below write out
+  // of bounds.
+  for (int l = 0; l < h; ++l) {
+    int64_t c = 0;
+    for (int q = 0; q < 8; ++q) c += hd->cells[8 * l + q];
+    if (c < 1 || c > n || (l == 0 ? c != 1 : c < lev[l - 1].ncell))
+      throw FmmError{FMM_ERR_HIP, "inconsistent octree level counts"};
+    lev[l].ncell = c;
+    lev[l].off = off;
+    off += c;
   }
-  if (ts.cum[ts.nlev] > 0) {
-    table_scatter_kernel<<<grid_for(ts.cum[ts.nlev], 256), 256, 0, s>>>(ts);
-    FMM_HIP_CHECK(hipGetLastError());
+  p->ncell_total = off;
+  p->nleaf = lev[h - 1].ncell;
+  const int64_t nl = p->nleaf;
+  if (off >= (int64_t(1) << 31) - 1) throw FmmError{FMM_ERR_ARG, "too many cells"};
+
+  // --- cells of every level, lookup tables, M2L targets ---
+  LevelDev ldev[kMaxHeight];
+  for (int l = 0; l < h; ++l) {
+    lev[l].keys = static_cast<uint64_t*>(p->alloc(sizeof(uint64_t) * lev[l].ncell));
+    if (l < h - 1)
+      lev[l].child_start = static_cast<int*>(p->alloc(sizeof(int) * (lev[l].ncell + 1)));
+    if (l > 0) lev[l].parent = static_cast<int*>(p->alloc(sizeof(int) * lev[l].ncell));
+    if (3 * l <= 24) {
+      lev[l].lookup = tables + tslots;
+      tslots += int64_t(1) << (3 * l);
+    }
+    ldev[l] = {lev[l].keys, lev[l].lookup, int(lev[l].ncell), l};
+    out.keys[l] = lev[l].keys;
+    out.child_start[l] = lev[l].child_start;
+    out.parent[l] = lev[l].parent;
+    out.table[l] = lev[l].lookup;
+    out.ncell[l] = int(lev[l].ncell);
+    out.off[l] = int(lev[l].off);
   }
+  p->leaf_start = static_cast<int*>(p->alloc(sizeof(int) * (nl + 1)));
+  out.leaf_start = p->leaf_start;
+  if (h >= 3) {
+    // targets grouped by (level, child parity), in Morton order within
+    p->tgt = static_cast<int*>(p->alloc(sizeof(int) * (p->ncell_total - lev[2].off)));
+    out.tgt = p->tgt;
+    int at = 0;
+    for (int l = 2; l < h; ++l)
+      for (int q = 0; q < 8; ++q) {
+        out.tstart[8 * l + q] = at;
+        at += hd->cells[8 * l + q];
+      }
+  }
+  cells_emit_kernel<<<cb, kCellThreads, 0, s>>>(p->keys, n, h, rounds, count, out);
+  FMM_HIP_CHECK(hipGetLastError());
 
   // --- near lists ---
-  // counters: far pairs per level, near pairs, active M2L slots, then far
-  // pairs per operator
-  const size_t ncount = kMaxHeight + 2 + kOffsets + 2;
-  unsigned long long* counters =
-      static_cast<unsigned long long*>(talloc(sizeof(unsigned long long) * ncount));
-  FMM_HIP_CHECK(hipMemsetAsync(counters, 0, sizeof(unsigned long long) * ncount, s));
   p->near = static_cast<int*>(p->alloc(sizeof(int) * 27 * nl));
-  near_kernel<<<grid_for(nl, 256), 256, 0, s>>>(ldev[h - 1], p->leaf_start, p->near,
-                                                counters + kMaxHeight);
+  near_kernel<<<grid_for(nl, kNearLeaves), 256, 0, s>>>(ldev[h - 1], p->leaf_start, p->near,
+                                                        stats + kMaxHeight);
   FMM_HIP_CHECK(hipGetLastError());
-
-  // --- leaf-local FP32 coordinates ---
-  p->prel = static_cast<float4*>(p->alloc(sizeof(float4) * n));
-  rel_coords_kernel<<<unsigned(nl), 64, 0, s>>>(p->px, p->py, p->pz, p->leaf_start,
-                                               lev[h - 1].keys, nl, bits, p->lo[0],
-                                               p->lo[1], p->lo[2],
-                                               L / double(int64_t(1) << bits), p->prel);
-  FMM_HIP_CHECK(hipGetLastError());
+  p->q32 = static_cast<float*>(p->alloc(sizeof(float) * n));
 
   // --- M2L tiles: targets of each level >= 2 grouped by child parity ---
   if (h >= 3) {
-    const int64_t ntgt = p->ncell_total - lev[2].off;
-    p->tgt = static_cast<int*>(p->alloc(sizeof(int) * ntgt));
-    // one stable radix pass by (level - 2, parity): within a group the
-    // cells stay in Morton order
-    CellLevels cl{};
-    for (int l = 0; l < h; ++l) {
-      cl.keys[l] = lev[l].keys;
-      cl.off[l] = lev[l].off;
-    }
-    cl.off[h] = p->ncell_total;
-    uint64_t* pk1 = static_cast<uint64_t*>(talloc(sizeof(uint64_t) * ntgt));
-    uint64_t* pk2 = static_cast<uint64_t*>(talloc(sizeof(uint64_t) * ntgt));
-    int* pv1 = static_cast<int*>(talloc(sizeof(int) * ntgt));
-    int* pv2 = static_cast<int*>(talloc(sizeof(int) * ntgt));
-    parity_keys_kernel<<<grid_for(ntgt, 256), 256, 0, s>>>(cl, h, pk1, pv1);
-    FMM_HIP_CHECK(hipGetLastError());
-    int kbits = 3;
-    while ((1 << (kbits - 3)) < h - 2) ++kbits;
-    radix_sort(pk1, pv1, pk2, pv2, ntgt, kbits, s, tmp);
-    FMM_HIP_CHECK(hipMemcpyAsync(p->tgt, pv1, sizeof(int) * ntgt, hipMemcpyDeviceToDevice, s));
-    // counts read back with the level counts (level_flags_kernel)
-    const int* hpc = reinterpret_cast<const int*>(stage + 512);
     // finest level first: the largest tiles' work is scheduled before the
     // coarse levels fill in the tail.  Within a level the parities take
     // turns: the k-th tile of every parity covers about the same region of
@@ -815,69 +819,64 @@ void build_plan(fmm_plan_s* p, const double* pos, hipStream_t s) {
     // whole level after another.
     std::vector<M2LTile> tiles;
     for (int l = h - 1; l >= 2; --l) {
-      int64_t start[8];
       int kmax = 0;
-      start[0] = lev[l].off - lev[2].off;
-      for (int par = 0; par < 8; ++par) {
-        if (par > 0) start[par] = start[par - 1] + hpc[8 * l + par - 1];
-        kmax = std::max(kmax, hpc[8 * l + par]);
-      }
+      for (int q = 0; q < 8; ++q) kmax = std::max(kmax, hd->cells[8 * l + q]);
       for (int k = 0; k < kmax; k += kTileN)
-        for (int par = 0; par < 8; ++par) {
-          const int c = hpc[8 * l + par];
-          if (k < c) tiles.push_back({l, par, int(start[par] + k), std::min(kTileN, c - k)});
+        for (int q = 0; q < 8; ++q) {
+          const int c = hd->cells[8 * l + q];
+          if (k < c) tiles.push_back({l, q, out.tstart[8 * l + q] + k, std::min(kTileN, c - k)});
         }
     }
     p->ntiles = int64_t(tiles.size());
     p->tiles_host = tiles;
     if (p->ntiles > 0) {
-      // every earlier transfer through the staging buffer has completed (the
-      // level-count read-back waited for them), so it may grow here; layout
-      // from 4 KiB on:
-      // level tables, level offsets, then the tiles
-      const size_t tbytes = sizeof(M2LTile) * tiles.size();
-      stage = static_cast<char*>(pinned_staging(4096 + 2048 + tbytes));
-      LevelDev* hld = reinterpret_cast<LevelDev*>(stage + 4096);
-      int64_t* hoff = reinterpret_cast<int64_t*>(stage + 4096 + 1024);
-      M2LTile* htiles = reinterpret_cast<M2LTile*>(stage + 4096 + 2048);
-      static_assert(sizeof(LevelDev) * kMaxHeight <= 1024 && sizeof(int64_t) * kMaxHeight <= 1024,
+      // one transfer: the level tables, the level offsets, then the tiles
+      // (the head has been read: the staging may grow)
+      constexpr size_t kOffAt = 1024, kTilesAt = 2048;
+      static_assert(sizeof(LevelDev) * kMaxHeight <= kOffAt &&
+                        sizeof(int64_t) * kMaxHeight <= kTilesAt - kOffAt,
                     "staging layout");
-      std::memcpy(htiles, tiles.data(), tbytes);
-      p->tiles = static_cast<M2LTile*>(p->alloc(tbytes));
-      FMM_HIP_CHECK(hipMemcpyAsync(p->tiles, htiles, tbytes, hipMemcpyHostToDevice, s));
+      const size_t bytes = kTilesAt + sizeof(M2LTile) * tiles.size();
+      stage = static_cast<char*>(pinned_staging(4096 + bytes));
+      char* hs = stage + 4096;
+      std::memset(hs, 0, kTilesAt);
+      std::memcpy(hs, ldev, sizeof(LevelDev) * h);
+      for (int l = 0; l < h; ++l) reinterpret_cast<int64_t*>(hs + kOffAt)[l] = lev[l].off;
+      std::memcpy(hs + kTilesAt, tiles.data(), sizeof(M2LTile) * tiles.size());
+      char* dev = static_cast<char*>(p->alloc(bytes));
+      FMM_HIP_CHECK(hipMemcpyAsync(dev, hs, bytes, hipMemcpyHostToDevice, s));
+      p->tiles = reinterpret_cast<M2LTile*>(dev + kTilesAt);
       p->tile_src = static_cast<int*>(p->alloc(sizeof(int) * size_t(p->ntiles) * kSlots * kTileN));
       p->tile_act = static_cast<unsigned char*>(p->alloc(size_t(p->ntiles) * kSlots));
       p->tile_gmask = static_cast<unsigned char*>(p->alloc(size_t(p->ntiles) * kSlots));
       p->tile_nact = static_cast<int*>(p->alloc(sizeof(int) * p->ntiles));
-      LevelDev* ld_d = static_cast<LevelDev*>(talloc(sizeof(LevelDev) * kMaxHeight));
-      int64_t* off_d = static_cast<int64_t*>(talloc(sizeof(int64_t) * kMaxHeight));
-      for (int l = 0; l < kMaxHeight; ++l) {
-        hoff[l] = l < h ? lev[l].off : 0;
-        hld[l] = ldev[l];
-      }
-      FMM_HIP_CHECK(hipMemcpyAsync(ld_d, hld, sizeof(LevelDev) * kMaxHeight,
-                                   hipMemcpyHostToDevice, s));
-      FMM_HIP_CHECK(hipMemcpyAsync(off_d, hoff, sizeof(int64_t) * kMaxHeight,
-                                   hipMemcpyHostToDevice, s));
       tile_src_kernel<<<unsigned(p->ntiles), kTileThreads, 0, s>>>(
-          p->tiles, p->tgt, ld_d, off_d, p->ops->slot_t,
-          int(p->ncell_total), p->tile_src, p->tile_act, p->tile_gmask, p->tile_nact, counters,
-          p->ops->slot_kid, counters + kMaxHeight + 2, counters + kMaxHeight + 1,
-          counters + kMaxHeight + 2 + kOffsets);
+          p->tiles, p->tgt, reinterpret_cast<const LevelDev*>(dev),
+          reinterpret_cast<const int64_t*>(dev + kOffAt), p->ops->slot_t, int(p->ncell_total),
+          p->tile_src, p->tile_act, p->tile_gmask, p->tile_nact, stats, p->ops->slot_kid,
+          stats + kMaxHeight + 2, stats + kMaxHeight + 1, stats + kMaxHeight + 2 + kOffsets);
       FMM_HIP_CHECK(hipGetLastError());
     }
   }
 
   // --- statistics ---
-  // statistics in the staging buffer's first 4 KiB (the box and counts
-  // there are no longer needed)
-  static_assert(sizeof(unsigned long long) * (kMaxHeight + 4 + kOffsets) <= 4096, "staging");
-  unsigned long long* hc = reinterpret_cast<unsigned long long*>(stage);
-  FMM_HIP_CHECK(hipMemcpyAsync(hc, counters, sizeof(unsigned long long) * (kMaxHeight + 4 + kOffsets),
+  FMM_HIP_CHECK(hipMemcpyAsync(stage, stats, sizeof(unsigned long long) * kStats,
                                hipMemcpyDeviceToHost, s));
-  // read by plan_stats after the caller's next synchronisation of s (no
-  // wait here: nothing the plan builds next needs them)
-  p->stats_stage = hc;
+  FMM_HIP_CHECK(hipStreamSynchronize(s));
+  const unsigned long long* hc = reinterpret_cast<const unsigned long long*>(stage);
+  for (int k = 0; k < kOffsets; ++k) p->pairs_by_kid[k] = int64_t(hc[kMaxHeight + 2 + k]);
+  p->near_pairs = int64_t(hc[kMaxHeight]);
+  p->far_pairs = 0;
+  for (int l = 0; l < kMaxHeight; ++l) {
+    p->far_pairs_level[l] = int64_t(hc[l]);
+    p->far_pairs += int64_t(hc[l]);
+  }
+  p->active_slots = int64_t(hc[kMaxHeight + 1]);
+  p->m2l_groups = int64_t(hc[kMaxHeight + 2 + kOffsets]);
+  p->m2l_groups_empty = int64_t(hc[kMaxHeight + 3 + kOffsets]);
+  // plans whose tiles leave many 16-target groups without a source at an
+  // offset (points on surfaces) take the compressed M2L that skips them
+  p->m2l_gskip = p->m2l_groups > 0 && 10 * p->m2l_groups_empty >= p->m2l_groups;
 }
 
 // ------------------------------------------------------ mutual pair lists
@@ -966,25 +965,6 @@ void build_mutual_lists(fmm_plan_s* p, hipStream_t s) {
   FMM_HIP_CHECK(hipGetLastError());
   p->mutual_list = list;
   for (int k = 0; k <= 2 * kMutualSlots; ++k) p->mutual_off[k] = off[k];
-}
-
-void plan_stats(fmm_plan_s* p) {
-  const unsigned long long* hc = p->stats_stage;
-  if (!hc) return;
-  for (int k = 0; k < kOffsets; ++k) p->pairs_by_kid[k] = int64_t(hc[kMaxHeight + 2 + k]);
-  p->near_pairs = int64_t(hc[kMaxHeight]);
-  p->far_pairs = 0;
-  for (int l = 0; l < kMaxHeight; ++l) {
-    p->far_pairs_level[l] = int64_t(hc[l]);
-    p->far_pairs += int64_t(hc[l]);
-  }
-  p->active_slots = int64_t(hc[kMaxHeight + 1]);
-  p->m2l_groups = int64_t(hc[kMaxHeight + 2 + kOffsets]);
-  p->m2l_groups_empty = int64_t(hc[kMaxHeight + 3 + kOffsets]);
-  // plans whose tiles leave many 16-target groups without a source at an
-  // offset (points on surfaces) take the compressed M2L that skips them
-  p->m2l_gskip = p->m2l_groups > 0 && 10 * p->m2l_groups_empty >= p->m2l_groups;
-  p->stats_stage = nullptr;
 }
 
 }  // namespace fmm
