@@ -119,7 +119,7 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
   J.fold_every = p->m2l_fold > 0 ? p->m2l_fold : kSlots;
   J.svd = p->svd ? 1 : 0;
   if (p->svd) J.xs = m2l_svd_xs(p->svd->rmax_pad, fp32);
-  J.nmb = p->svd ? m2l_svd_nmb(op->mt, fp32, J.xs) : m2l_nmb(op->mt);
+  J.nmb = m2l_nmb(op->mt);
   if (p->svd) {
     J.svd_rpad = p->svd->rpad;
     J.svd_rank = p->svd->rk;
@@ -139,13 +139,16 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
   int parts = 1;
   const int64_t lrows = h >= 3 ? int64_t(p->ncell_total) - int64_t(p->lev[2].off) : 0;
   const size_t part_bytes = sizeof(double) * size_t(lrows) * op->ld;
-  if (p->svd && h >= 3 && m2l_svd_splits(fp32)) {
+  int cus = 0;
+  FMM_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
+  if (p->svd && h >= 3) {
+    int items = 1, slots = 1;
+    m2l_svd_ranges(p->order, fp32, J.xs, cus, &items, &slots);
     parts = p->m2l_split > 0 ? p->m2l_split
-                             : auto_parts(int64_t(p->ntiles) * J.nmb,
-                                          m2l_svd_slots(p->order, fp32, J.xs), part_bytes);
+                             : auto_parts(int64_t(p->ntiles) * items, slots, part_bytes);
+    J.svd_nt = m2l_svd_nt(p->order, fp32, int64_t(p->ntiles) * parts, cus);
+    J.nmb = m2l_svd_nmb(op->mt, fp32, J.svd_nt);
   } else if (!p->svd && h >= 3 && p->W) {
-    int cus = 0;
-    FMM_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
     parts = dense_parts(int64_t(p->ntiles) * J.nmb, op->mt, fp32, part_bytes, cus);
     if (p->dense_parts_max > 0) parts = std::min(parts, p->dense_parts_max);
   }
@@ -399,7 +402,7 @@ static bool ensure_w(fmm_plan_s* p, hipStream_t s) {
     if (p->W) p->free_block(p->W);
     p->W = nullptr;  // a failed allocation below leaves no stale pointer
     p->w64_rows = 0;
-    p->W = static_cast<double*>(p->alloc(sizeof(double) * size_t(want64) * ld));
+    p->W = static_cast<double*>(p->alloc(sizeof(double) * (size_t(want64) * ld + fmm::kSvdPadChunks * 16)));
     if (!mixed)
       FMM_HIP_CHECK(hipMemsetAsync(p->W + (rows - 1) * ld, 0, sizeof(double) * ld, s));
     p->w64_rows = want64;
@@ -407,7 +410,7 @@ static bool ensure_w(fmm_plan_s* p, hipStream_t s) {
   }
   if (mixed && !p->W32) {
     p->w32_leaf = false;
-    p->W32 = static_cast<float*>(p->alloc(sizeof(float) * size_t(rows) * ld));
+    p->W32 = static_cast<float*>(p->alloc(sizeof(float) * (size_t(rows) * ld + fmm::kSvdPadChunks * 16)));
     FMM_HIP_CHECK(hipMemsetAsync(p->W32 + (rows - 1) * ld, 0, sizeof(float) * ld, s));
     changed = true;
   } else if (!mixed && p->W32) {

@@ -162,19 +162,18 @@ enum {
 
 int m2l_nmb(int mt);      // M-blocks per M2L tile for mt 16-row tiles (dense)
 double m2l_item_flops(int mt);  // ... and the flops of one item at one far offset
-// Compressed M2L for mt 16-row tiles and a slab stride of xs values (the
-// kernel's shape depends on both): work items per tile, and 16-column
-// N-tiles per item (launches of one order and precision that batch several
-// plans group them by the latter)
-int m2l_svd_nmb(int mt, bool fp32, int xs);
-int m2l_svd_nt(int order, bool fp32, int xs);
-int m2l_svd_slots(int order, bool fp32, int xs);  // compressed M2L workgroups resident at once
-bool m2l_svd_splits(bool fp32);          // whether the compressed kernel takes m2l_parts
-// LDS bytes of one compressed-M2L workgroup of nt N-tiles, and of the shape
-// the kernel takes at this order
-size_t m2l_svd_lds_bytes(int xs, bool fp32, int nt);
+// Compressed M2L (m2l_svd.hip): 16-column N-tiles per item, work items per tile
+// for mt 16-row tiles, the slab stride for a padded rank, the LDS a rank may
+// need, and the (items per tile, workgroup slots) the split into offset
+// ranges is computed from
+// (its reads run up to kSvdPadChunks 16-row chunks past the end of the
+// multipoles and of the S V^T factors, so those are allocated that much longer)
+constexpr int kSvdPadChunks = 48;
+int m2l_svd_nt(int order, bool fp32, int64_t tile_parts, int cus);
+int m2l_svd_nmb(int mt, bool fp32, int nt);
+int m2l_svd_xs(int rmax_pad, bool fp32);
 size_t m2l_svd_lds_need(int order, bool fp32, int xs);
-int m2l_svd_xs(int rmax_pad, bool fp32);  // the slab stride for a padded rank
+void m2l_svd_ranges(int order, bool fp32, int xs, int cus, int* items, int* slots);
 
 }  // namespace fmm
 

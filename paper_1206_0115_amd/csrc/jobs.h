@@ -75,6 +75,7 @@ struct JobDev {
   // compressed M2L (svd != 0): per packed operator kid, the padded rank, the
   // kept rank and the element offset of its two factors in the packs below
   int svd, xs;
+  int svd_nt;  // 16-column N-tiles of an item
   const int* svd_rpad;
   const int* svd_rank;
   const int64_t* svd_off;
@@ -134,13 +135,15 @@ __device__ inline int step_find(const StepTab& t, int item) {
 // item (the total must then be given); a positive grid makes every block loop
 // over items with that stride (persistent launch).
 // kStepM2LSvd is the compressed M2L; `xs` is then the LDS row stride (the
-// largest padded rank of the launch's jobs + 4).
+// largest padded rank of the launch's jobs + 4) and `nt` their N-tiles per
+// item.
 enum StepKind { kStepGather, kStepP2M, kStepM2M, kStepCast, kStepM2L, kStepL2L, kStepL2P,
                 kStepP2P, kStepCombine, kStepM2LSvd, kStepLocSum, kStepL2PSparse,
                 kStepP2PSelf };
 // gskip: the compressed M2L skips the 16-target groups without a source at
 // an offset (plans whose tiles have many, fmm_info.m2l_group_skip).
 void launch_step(StepKind kind, int order, bool fp32, const JobDev* jobs, const StepTab* tab,
-                 const CallDev* calls, int grid, hipStream_t s, int xs = 0, bool gskip = false);
+                 const CallDev* calls, int grid, hipStream_t s, int xs = 0, int nt = 0,
+                 bool gskip = false);
 
 }  // namespace fmm

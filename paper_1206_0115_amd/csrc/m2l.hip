@@ -47,6 +47,7 @@
 #include "device_util.h"
 #include "fmm_internal.h"
 #include "jobs.h"
+#include "m2l_dev.h"
 
 namespace fmm {
 
@@ -363,27 +364,6 @@ const OpSet* get_opset(int l, int kernel, hipStream_t s) {
 }
 
 // ------------------------------------------------------------- M2L kernel
-typedef double d4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-struct Vec4;
-template <>
-struct Vec4<double> {
-  typedef d4 type;
-};
-template <>
-struct Vec4<float> {
-  typedef f4 type;
-};
-
-__device__ inline d4 mfma16x16x4(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ inline f4 mfma16x16x4(float a, float b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 // One workgroup = 4 wavefronts = one (tile, M-block) item.  Wavefront w owns
 // the M-tiles [mt0, mt0 + MTW) of the output rows and all 64 target columns
 // (four 16-column N-tiles).  K-chunks of 16 coefficients = 4 MFMA k-steps;
@@ -404,20 +384,6 @@ __device__ inline f4 mfma16x16x4(float a, float b, f4 c) {
 #ifndef FMM_M2L_F64_PREFETCH_B
 #define FMM_M2L_F64_PREFETCH_B 1
 #endif
-
-// Block b of n, dealt round-robin to the 8 XCDs, to an item such that each
-// XCD's items are consecutive.
-__device__ inline int xcd_run(int b, int n) {
-  const int n8 = n / 8 * 8;
-  return b < n8 ? (b % 8) * (n8 / 8) + b / 8 : b;
-}
-
-// The FP64 row that target cell t of offset range `part` accumulates into: the
-// cell's local expansion for part 0, else the part's own row of LocX.
-__device__ inline double* m2l_out_row(const JobDev& J, int part, int64_t t) {
-  if (part == 0) return J.Loc + t * J.ld;
-  return J.LocX + (int64_t(part - 1) * J.locx_rows + (t - J.locx_first)) * J.ld;
-}
 
 template <typename T, int MTW, bool FOLD>
 __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
@@ -801,9 +767,10 @@ const SvdOps* get_svd_ops(int l, double eps, int kernel, hipStream_t s) {
     sv->rk = static_cast<int*>(dev_alloc(sizeof(int) * kOffsets));
     FMM_HIP_CHECK(hipMemcpyAsync(sv->rk, rk_h.data(), sizeof(int) * kOffsets,
                                  hipMemcpyHostToDevice, s));
-    sv->p1_64 = static_cast<double*>(dev_alloc(sizeof(double) * tot));
+    const int64_t pad = int64_t(kSvdPadChunks) * 256;
+    sv->p1_64 = static_cast<double*>(dev_alloc(sizeof(double) * (tot + pad)));
     sv->p2_64 = static_cast<double*>(dev_alloc(sizeof(double) * tot));
-    sv->p1_32 = static_cast<float*>(dev_alloc(sizeof(float) * tot));
+    sv->p1_32 = static_cast<float*>(dev_alloc(sizeof(float) * (tot + pad)));
     sv->p2_32 = static_cast<float*>(dev_alloc(sizeof(float) * tot));
     // Uc[a][k] = Vt[a * l3 + k]: its rows as Chebyshev coefficients, for FP32
     double* VtM = static_cast<double*>(talloc(sizeof(double) * 16 * nn));
@@ -826,1071 +793,6 @@ const SvdOps* get_svd_ops(int l, double eps, int kernel, hipStream_t s) {
   const SvdOps* r = sv.get();
   g_svd[key] = std::move(sv);
   return r;
-}
-
-// Target columns per workgroup of the compressed kernel, 16 * NT, for FP32
-// and FP64.  Fewer columns than the tile's 64 cost operator re-reads (from
-// L2) but free registers for two wavefronts per SIMD.  Measured on gfx950
-// at order 7 with the 4-wavefront kernel: FP32 best at 32 columns in 8
-// wavefronts (3 M-tiles each, no spills); FP64 at 16 columns in 4
-// wavefronts (within 1% of 32 columns in 8, and half the LDS, so order 9 at
-// 1e-9 still fits).  These are the base shapes; the warp-specialised kernel
-// takes wider items where they fit (FMM_M2L_SVD_FULL_*).
-#ifndef FMM_M2L_SVD_NT_F32
-#define FMM_M2L_SVD_NT_F32 2
-#endif
-#ifndef FMM_M2L_SVD_NT_F64
-#define FMM_M2L_SVD_NT_F64 1
-#endif
-constexpr int svd_nt(bool fp32) { return fp32 ? FMM_M2L_SVD_NT_F32 : FMM_M2L_SVD_NT_F64; }
-static_assert(svd_nt(true) == 1 || svd_nt(true) == 2 || svd_nt(true) == 4, "NT");
-static_assert(svd_nt(false) == 1 || svd_nt(false) == 2 || svd_nt(false) == 4, "NT");
-// Whether phase 2 loads its U fragments one rank chunk ahead (FP32, FP64).
-#ifndef FMM_M2L_SVD_P2_PREFETCH_F32
-#define FMM_M2L_SVD_P2_PREFETCH_F32 0
-#endif
-#ifndef FMM_M2L_SVD_P2_PREFETCH_F64
-#define FMM_M2L_SVD_P2_PREFETCH_F64 0
-#endif
-// Rank tiles per pass of phase 1 over the l^3 contraction (each pass reads
-// its share of the gathered multipoles once), FP32 and FP64.
-#ifndef FMM_M2L_SVD_RPASS_F32
-#define FMM_M2L_SVD_RPASS_F32 2
-#endif
-#ifndef FMM_M2L_SVD_RPASS_F64
-#define FMM_M2L_SVD_RPASS_F64 2
-#endif
-// FP32 mode: where the FP32 accumulators are folded into FP64 sums, every
-// J.fold_every far offsets (the plan's fold interval):
-//   0  nowhere (FP32 across all far offsets)
-//   1  FP64 registers (acc64)
-//   2  the item's own FP64 rows of the local expansions in global memory
-// Measured at order 7 (fold every 8): mode 2 runs in 5.5 ms where mode 1
-// runs in 8.0 ms, because without the FP64 registers two 4-wavefront
-// workgroups fit per CU without spills.
-#ifndef FMM_M2L_SVD_F32_FOLD_MODE
-#define FMM_M2L_SVD_F32_FOLD_MODE 2
-#endif
-// Wavefronts per SIMD the register allocation must allow, FP32 and FP64.
-#ifndef FMM_M2L_SVD_WAVES_F32
-#define FMM_M2L_SVD_WAVES_F32 2
-#endif
-#ifndef FMM_M2L_SVD_WAVES_F64
-#define FMM_M2L_SVD_WAVES_F64 2
-#endif
-// Wavefronts per workgroup (4 or 8), FP32 and FP64.  With 8, two wavefronts
-// share each K-group of phase 1 (one per N-tile half) and every wavefront
-// owns half as many output rows, which halves its accumulator registers.
-#ifndef FMM_M2L_SVD_NWV_F32
-#define FMM_M2L_SVD_NWV_F32 4
-#endif
-#ifndef FMM_M2L_SVD_NWV_F64
-#define FMM_M2L_SVD_NWV_F64 4
-#endif
-constexpr int svd_nwv(bool fp32) { return fp32 ? FMM_M2L_SVD_NWV_F32 : FMM_M2L_SVD_NWV_F64; }
-static_assert((svd_nwv(true) == 4 || svd_nwv(true) == 8) &&
-                  (svd_nwv(false) == 4 || svd_nwv(false) == 8),
-              "4 or 8 wavefronts per workgroup");
-static_assert(4 * svd_nt(true) % svd_nwv(true) == 0 && 4 * svd_nt(false) % svd_nwv(false) == 0,
-              "8 wavefronts need at least 2 N-tiles");
-
-// One workgroup = NWV wavefronts = one (tile, M-block, N-group) item, the
-// N-group being NC = 16 NT of the tile's 64 target columns.  Per far offset:
-//   phase 1  X(rp x NC) = (S V^T)_g W.  K-group kg = w % 4 takes the
-//            K-chunks kg, kg+4, ... of the l^3 contraction for every rank
-//            tile (two per pass); its NWV/4 wavefronts split the N-tiles.
-//            Partial sums go to the K-group's LDS slab P[kg];
-//   phase 2  Y(l^3 x NC) += U_g X, X read as P[0]+P[1]+P[2]+P[3] (always
-//            in that order, so every wavefront sees the same X and the
-//            result does not depend on timing).  Wavefront w owns MTW
-//            16-row M-tiles of the output.
-// The slabs are double-buffered, the buffer alternating with every offset
-// the workgroup processes (also across items), so one barrier per offset
-// suffices: a wavefront writes buffer b again only after the barrier of the
-// next offset, which every wavefront reaches after its reads of buffer b.
-template <typename T, int MTW, int NT, int NWV, int FM>
-__global__ __launch_bounds__(64 * NWV, sizeof(T) == 4 ? FMM_M2L_SVD_WAVES_F32
-                                                      : FMM_M2L_SVD_WAVES_F64) void m2l_svd_kernel(const JobDev* __restrict__ jobs,
-                                                         const StepTab* __restrict__ tab) {
-  typedef typename Vec4<T>::type T4;
-  constexpr bool FOLD = FM == 1;  // FP64 register sums
-  constexpr int NC = 16 * NT, NG = 4 / NT;
-  constexpr int NTW = NT * 4 / NWV;  // N-tiles per wavefront in phase 1
-  constexpr int kRP = sizeof(T) == 4 ? FMM_M2L_SVD_RPASS_F32 : FMM_M2L_SVD_RPASS_F64;
-  extern __shared__ __align__(16) unsigned char lds_raw[];
-  T* const lds = reinterpret_cast<T*>(lds_raw);
-  int buf = 0;
-  const int total = step_total(*tab);
-  const int wave = wuni(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int g = lane >> 4, c16 = lane & 15;
-  const bool f64 = sizeof(T) == 8;
-  for (int it = blockIdx.x; it < total; it += gridDim.x) {
-    int b = it;
-    if (int(gridDim.x) == total) {
-      const int n8 = (total / 8) * 8;
-      if (b < n8) b = (b % 8) * (n8 / 8) + b / 8;
-    }
-    const int k = step_find(*tab, b);
-    const JobDev& J = jobs[tab->job[k]];
-    const int local = b - tab->start[k] + tab->first[k];
-    const int tile = local / J.nmb, rem = local % J.nmb;
-    const int mb = rem / NG, col0 = NC * (rem % NG);
-    const M2LTile tl = J.tiles[tile];
-    if (col0 >= tl.count) continue;  // the same for the whole workgroup
-    const int MT = J.mt, KC = J.kc, ld = J.ld, XS = J.xs;
-    const int mt0 = (mb * NWV + wave) * MTW;
-    const int nmt = mt0 < MT ? min(MTW, MT - mt0) : 0;
-    const int kg = wave & 3, jn0 = (wave >> 2) * NTW;
-    constexpr bool F32 = sizeof(T) == 4;
-    const T* __restrict__ Wp = F32 ? reinterpret_cast<const T*>(J.W32)
-                                   : reinterpret_cast<const T*>(J.W);
-    const T* __restrict__ P1 = F32 ? reinterpret_cast<const T*>(J.p1_32)
-                                   : reinterpret_cast<const T*>(J.p1_64);
-    const T* __restrict__ P2 = F32 ? reinterpret_cast<const T*>(J.p2_32)
-                                   : reinterpret_cast<const T*>(J.p2_64);
-    T4 acc[MTW][NT];
-    d4 acc64[FOLD ? MTW : 1][NT];
-#pragma unroll
-    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        acc[i][j] = T4{0, 0, 0, 0};
-        if (FOLD) acc64[FOLD ? i : 0][j] = d4{0, 0, 0, 0};
-      }
-    const int nact = wuni(gld(J.tile_nact + tile));
-    bool folded = false;  // FM == 2: Loc rows written once already
-    const unsigned char* act = J.tile_act + int64_t(tile) * kSlots;
-    const int* srcb = J.tile_src + int64_t(tile) * kSlots * kTileN + col0;
-    const int* kidp = J.slot_kid + tl.parity * kSlots;
-
-    for (int ia = 0; ia < nact; ++ia) {
-      const int s = wuni(int(gld(act + ia)));
-      const int kid = wuni(gld(kidp + s));
-      const int rp = wuni(gld(J.svd_rpad + kid)), nr = rp >> 4;
-      const int nst = (wuni(gld(J.svd_rank + kid)) - 16 * (nr - 1) + 3) >> 2;  // K-steps, last chunk
-      const int64_t off = wuni(gld(J.svd_off + kid));
-      T* const P = lds + buf * 4 * NC * XS;
-      T* const Pw = P + kg * NC * XS;
-      buf ^= 1;
-      // ---- phase 1: this wavefront's share of X, into its K-group's slab ----
-      const T* bp[NTW];
-#pragma unroll
-      for (int j = 0; j < NTW; ++j)
-        bp[j] = Wp + int64_t(gld(srcb + s * kTileN + 16 * (jn0 + j) + c16)) * ld + 4 * g;
-      for (int i0 = 0; i0 < nr; i0 += kRP) {
-        const int np = min(kRP, nr - i0);
-        const T* a0 = P1 + off + (int64_t(i0) * KC) * 256 + lane * 4;
-        T4 x[kRP][NTW];
-#pragma unroll
-        for (int i = 0; i < kRP; ++i)
-#pragma unroll
-          for (int j = 0; j < NTW; ++j) x[i][j] = T4{0, 0, 0, 0};
-        T4 bv[NTW], av[kRP];
-        if (kg < KC) {
-#pragma unroll
-          for (int j = 0; j < NTW; ++j) bv[j] = gld(reinterpret_cast<const T4*>(bp[j] + 16 * kg));
-#pragma unroll
-          for (int i = 0; i < kRP; ++i)
-            av[i] = i < np ? gld(reinterpret_cast<const T4*>(a0 + (int64_t(i) * KC + kg) * 256))
-                           : T4{0, 0, 0, 0};
-        }
-        for (int c = kg; c < KC; c += 4) {
-          T4 bn[NTW], an[kRP];
-          const bool more = c + 4 < KC;
-          if (more) {
-#pragma unroll
-            for (int j = 0; j < NTW; ++j)
-              bn[j] = gld(reinterpret_cast<const T4*>(bp[j] + 16 * (c + 4)));
-#pragma unroll
-            for (int i = 0; i < kRP; ++i)
-              an[i] = i < np ? gld(reinterpret_cast<const T4*>(a0 + (int64_t(i) * KC + c + 4) * 256))
-                             : T4{0, 0, 0, 0};
-          }
-#pragma unroll
-          for (int st = 0; st < 4; ++st)
-#pragma unroll
-            for (int i = 0; i < kRP; ++i)
-#pragma unroll
-              for (int j = 0; j < NTW; ++j)
-                if (i < np) x[i][j] = mfma16x16x4(av[i][st], bv[j][st], x[i][j]);
-          if (more) {
-#pragma unroll
-            for (int j = 0; j < NTW; ++j) bv[j] = bn[j];
-#pragma unroll
-            for (int i = 0; i < kRP; ++i) av[i] = an[i];
-          }
-        }
-        // D rows: FP32 item r -> row 4g + r, FP64 item r -> row 4r + g
-#pragma unroll
-        for (int i = 0; i < kRP; ++i)
-#pragma unroll
-          for (int j = 0; j < NTW; ++j) {
-            if (i >= np) continue;
-            T* xrow = Pw + (16 * (jn0 + j) + c16) * XS + 16 * (i0 + i);
-            if (f64) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) xrow[4 * r + g] = x[i][j][r];
-            } else {
-              *reinterpret_cast<T4*>(xrow + 4 * g) = x[i][j];
-            }
-          }
-      }
-      __syncthreads();
-      // ---- phase 2: Loc rows of this wavefront's M-tiles ----
-      if (nmt > 0) {
-        const T* a2 = P2 + off + int64_t(mt0) * nr * 256 + lane * 4;
-        constexpr bool kPre = sizeof(T) == 4 ? FMM_M2L_SVD_P2_PREFETCH_F32
-                                             : FMM_M2L_SVD_P2_PREFETCH_F64;
-        T4 av[MTW];
-        if (kPre) {
-#pragma unroll
-          for (int i = 0; i < MTW; ++i)
-            av[i] = i < nmt ? gld(reinterpret_cast<const T4*>(a2 + int64_t(i) * nr * 256))
-                            : T4{0, 0, 0, 0};
-        }
-        for (int c = 0; c < nr; ++c) {
-          T4 bv[NT], an[kPre ? MTW : 1];
-          if (!kPre) {
-#pragma unroll
-            for (int i = 0; i < MTW; ++i)
-              av[i] = i < nmt ? gld(reinterpret_cast<const T4*>(a2 + (int64_t(i) * nr + c) * 256))
-                              : T4{0, 0, 0, 0};
-          } else if (c + 1 < nr) {
-#pragma unroll
-            for (int i = 0; i < MTW; ++i)
-              an[kPre ? i : 0] =
-                  i < nmt ? gld(reinterpret_cast<const T4*>(a2 + (int64_t(i) * nr + c + 1) * 256))
-                          : T4{0, 0, 0, 0};
-          }
-#pragma unroll
-          for (int j = 0; j < NT; ++j) {
-            const int o = (16 * j + c16) * XS + 16 * c + 4 * g;
-            T4 v = *reinterpret_cast<const T4*>(P + o);
-#pragma unroll
-            for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const T4*>(P + w * NC * XS + o);
-            bv[j] = v;
-          }
-          // K-steps past the kept rank hold zeros in both operands
-          const int ns = c + 1 < nr ? 4 : nst;
-#pragma unroll
-          for (int st = 0; st < 4; ++st) {
-            if (st >= ns) continue;
-#pragma unroll
-            for (int i = 0; i < MTW; ++i) {
-              if (i >= nmt) continue;
-#pragma unroll
-              for (int j = 0; j < NT; ++j)
-                acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
-            }
-          }
-          if (kPre && c + 1 < nr) {
-#pragma unroll
-            for (int i = 0; i < MTW; ++i) av[i] = an[kPre ? i : 0];
-          }
-        }
-        const bool fold_now = (ia + 1) % J.fold_every == 0 || ia == nact - 1;
-        if (FOLD && fold_now) {
-#pragma unroll
-          for (int i = 0; i < MTW; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) acc64[FOLD ? i : 0][j][r] += double(acc[i][j][r]);
-              acc[i][j] = T4{0, 0, 0, 0};
-            }
-        }
-        if (FM == 2 && fold_now) {
-          // fold into this item's rows of Loc (scaled; the first fold
-          // stores, later ones add): no other workgroup touches these rows
-          const double sc = J.scale[tl.level];
-#pragma unroll
-          for (int j = 0; j < NT; ++j) {
-            const int col = col0 + 16 * j + c16;
-            if (col < tl.count) {
-              double* out = J.Loc + int64_t(gld(J.tgt + tl.first + col)) * ld;
-#pragma unroll
-              for (int i = 0; i < MTW; ++i) {
-                if (i >= nmt) continue;
-                d4* o = reinterpret_cast<d4*>(out + 16 * (mt0 + i) + 4 * g);  // rows 4g..4g+3
-                d4 v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = sc * double(acc[i][j][r]);
-                if (folded) v += gld(o);
-                gst(o, v);
-              }
-            }
-#pragma unroll
-            for (int i = 0; i < MTW; ++i) acc[i][j] = T4{0, 0, 0, 0};
-          }
-          folded = true;
-        }
-      }
-    }
-
-    if (FM == 2 && folded) continue;  // the folds wrote the rows
-    const double sc = J.scale[tl.level];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const int col = col0 + 16 * j + c16;
-      if (col >= tl.count) continue;
-      double* out = J.Loc + int64_t(gld(J.tgt + tl.first + col)) * ld;
-#pragma unroll
-      for (int i = 0; i < MTW; ++i) {
-        if (i >= nmt) continue;
-        const int base = 16 * (mt0 + i);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = f64 ? 4 * r + g : 4 * g + r;
-          gst(out + base + row, sc * (FOLD ? acc64[FOLD ? i : 0][j][r] : double(acc[i][j][r])));
-        }
-      }
-    }
-  }
-}
-
-// Warp-specialised form of the same computation, 8 wavefronts: 0-3 are the
-// four K-groups of phase 1 (producers), 4-7 own the M-tiles of phase 2
-// (consumers, MTW each, as the 4-wavefront kernel).  Iteration ia of an
-// item: the producers write X of offset ia into slab buffer ia % 2 while the
-// consumers apply X of offset ia - 1 from the other buffer; one barrier ends
-// the iteration, so phase 1 of one offset runs beside phase 2 of the
-// previous one, and a buffer is written again only after the barrier that
-// follows its last read.  Both roles walk the same items and pass nact + 1
-// barriers per item; the role is taken on a wavefront-uniform branch, and
-// each role keeps only its own registers live.  The arithmetic, including
-// its order, is that of m2l_svd_kernel with 4 wavefronts: FP32 folds into
-// the item's FP64 Loc rows every J.fold_every offsets; FP64 accumulates in
-// registers and writes once.
-#ifndef FMM_M2L_SVD_WS_WAVES
-#define FMM_M2L_SVD_WS_WAVES 4
-#endif
-// ...and for workgroups of 8 consumers (12 wavefronts): one of them fills a
-// CU at 3 wavefronts per SIMD, and a second would need 6 per SIMD (85
-// VGPRs), so they take the 168 VGPRs of 3 per SIMD at no loss of occupancy
-// (the 32-column shapes of orders 8 to 10 spilled at 128).
-#ifndef FMM_M2L_SVD_WS_WAVES_BIG
-#define FMM_M2L_SVD_WS_WAVES_BIG 3
-#endif
-constexpr int svd_ws_waves(int ncw, int nt) {
-  return ncw >= 8 ? FMM_M2L_SVD_WS_WAVES_BIG : FMM_M2L_SVD_WS_WAVES;
-}
-// Producer stage depth D, FP32 and FP64: where every K-group has at most D
-// chunks of the l^3 contraction (ceil(KC / 4) <= D), the kernel built for D
-// loads each K-group's chunks all at once; otherwise (or D = 0) they stream
-// one chunk ahead.
-#ifndef FMM_M2L_SVD_WS_STAGE_F32
-#define FMM_M2L_SVD_WS_STAGE_F32 0
-#endif
-#ifndef FMM_M2L_SVD_WS_STAGE_F64
-#define FMM_M2L_SVD_WS_STAGE_F64 0
-#endif
-// Whether a producer loads the first chunk of its next offset before the
-// barrier that ends the current one (streamed path), FP32 and FP64 (the FP64
-// registers would spill).
-#ifndef FMM_M2L_SVD_WS_XPRE_F32
-#define FMM_M2L_SVD_WS_XPRE_F32 1
-#endif
-#ifndef FMM_M2L_SVD_WS_XPRE_F64
-#define FMM_M2L_SVD_WS_XPRE_F64 0
-#endif
-// Chunks a producer keeps in flight ahead of the one it computes (1 or 2),
-// FP32 and FP64.
-#ifndef FMM_M2L_SVD_WS_LOOK_F32
-#define FMM_M2L_SVD_WS_LOOK_F32 1
-#endif
-#ifndef FMM_M2L_SVD_WS_LOOK_F64
-#define FMM_M2L_SVD_WS_LOOK_F64 1
-#endif
-// U fragments (M-tiles of rank chunk 0) a consumer loads for its next offset
-// before the barrier, FP32 and FP64 (measured at order 7: 0 to 6 within
-// noise, so off).
-#ifndef FMM_M2L_SVD_WS_CPRE_F32
-#define FMM_M2L_SVD_WS_CPRE_F32 0
-#endif
-#ifndef FMM_M2L_SVD_WS_CPRE_F64
-#define FMM_M2L_SVD_WS_CPRE_F64 0
-#endif
-#ifndef FMM_M2L_SVD_WS_APRE_F32
-#define FMM_M2L_SVD_WS_APRE_F32 0
-#endif
-#ifndef FMM_M2L_SVD_WS_APRE_F64
-#define FMM_M2L_SVD_WS_APRE_F64 0
-#endif
-
-struct SvdItem {
-  const JobDev* J;
-  M2LTile tl;
-  int tile, mb, col0;
-  int part;  // offset range [ia0, ia1) of the tile's active offsets
-};
-
-__device__ inline void svd_part_range(const SvdItem& I, int nact, int& ia0, int& ia1) {
-  const int K = I.J->m2l_parts;
-  ia0 = int(int64_t(I.part) * nact / K);
-  ia1 = int(int64_t(I.part + 1) * nact / K);
-}
-
-// Per active offset of an item, what both roles look up: the factor offset,
-// the slot (for the source columns), the rank chunks and the K-steps of the
-// last one.  Filled once per item into LDS, after the slabs, by all threads.
-struct SvdMeta {
-  int64_t off;
-  int s;
-  int nr_nst;  // nr | nst << 16 | gmask << 24 (the slot's 16-target groups with a source)
-};
-constexpr size_t kSvdMetaBytes = sizeof(SvdMeta) * kSlots;
-
-template <bool GS = false>
-__device__ inline void svd_meta_fill(const SvdItem& I, int nact, SvdMeta* meta) {
-  const JobDev& J = *I.J;
-  int ia0, ia1;
-  svd_part_range(I, nact, ia0, ia1);
-  const unsigned char* act = J.tile_act + int64_t(I.tile) * kSlots;
-  const int* kidp = J.slot_kid + I.tl.parity * kSlots;
-  for (int t = threadIdx.x; t < ia1 - ia0; t += blockDim.x) {
-    const int sl = gld(act + ia0 + t);
-    const int kid = gld(kidp + sl);
-    const int nr = gld(J.svd_rpad + kid) >> 4;
-    const int nst = (gld(J.svd_rank + kid) - 16 * (nr - 1) + 3) >> 2;
-    const int gm = GS ? gld(J.tile_gmask + int64_t(I.tile) * kSlots + ia0 + t) : 0xf;
-    meta[t] = SvdMeta{gld(J.svd_off + kid), sl, nr | (nst << 16) | (gm << 24)};
-  }
-  __syncthreads();
-}
-
-// The FP64 row that target column col of the item accumulates into.
-__device__ inline double* svd_out_row(const SvdItem& I, int col) {
-  return m2l_out_row(*I.J, I.part, gld(I.J->tgt + I.tl.first + col));
-}
-
-// Item `it` of the launch; false when its N-group holds no target column
-// (the same for the whole workgroup).
-template <int NT>
-__device__ inline bool svd_item(const JobDev* __restrict__ jobs, const StepTab* __restrict__ tab,
-                                int it, int total, SvdItem& I) {
-  constexpr int NC = 16 * NT, NG = 4 / NT;
-  int b = it;
-  if (int(gridDim.x) == total) {
-    const int n8 = (total / 8) * 8;
-    if (b < n8) b = (b % 8) * (n8 / 8) + b / 8;
-  }
-  const int k = step_find(*tab, b);
-  const JobDev& J = jobs[tab->job[k]];
-  const int local = b - tab->start[k] + tab->first[k];
-  I.J = &J;
-  const int per_tile = J.nmb * J.m2l_parts;
-  I.tile = local / per_tile;
-  const int rem0 = local % per_tile;
-  I.part = rem0 / J.nmb;
-  const int rem = rem0 % J.nmb;
-  I.mb = rem / NG;
-  I.col0 = NC * (rem % NG);
-  I.tl = J.tiles[I.tile];
-  return I.col0 < I.tl.count;
-}
-
-// The 32-column items of 8 consumers (FP32 at orders 10 to 12, where whole
-// tiles would spill) have registers to spare at 3 wavefronts per SIMD: their
-// producers take 3 rank tiles per pass, so that the offsets padded to rank
-// 48 gather their multipoles once, and keep two chunks in flight (30M-
-// particle order-10 cube, M2L 5126 -> 4771 ms; 167 VGPRs, no spills).  The
-// other shapes spill with either.
-#ifndef FMM_M2L_SVD_RPASS_WIDE_F32
-#define FMM_M2L_SVD_RPASS_WIDE_F32 3
-#endif
-#ifndef FMM_M2L_SVD_WS_LOOK_WIDE_F32
-#define FMM_M2L_SVD_WS_LOOK_WIDE_F32 2
-#endif
-
-// GS: the N-tiles whose 16 target columns have no source at an offset
-// (their multipole columns are the zero row, so their products are zero)
-// are skipped, by both roles; a wavefront-uniform test per N-tile, which
-// costs the dense cubes 9-11%, so only plans with many empty groups take it
-template <typename T, int NT, int D, int NCW, bool GS>
-__device__ inline void svd_ws_produce(const JobDev* __restrict__ jobs,
-                                      const StepTab* __restrict__ tab, T* const lds,
-                                      SvdMeta* const meta, int kg) {
-  typedef typename Vec4<T>::type T4;
-  constexpr bool F32 = sizeof(T) == 4;
-  constexpr int NC = 16 * NT;
-  constexpr bool kWide = F32 && NT == 2 && NCW == 8;
-  constexpr int kRP = kWide ? FMM_M2L_SVD_RPASS_WIDE_F32
-                            : F32 ? FMM_M2L_SVD_RPASS_F32 : FMM_M2L_SVD_RPASS_F64;
-  // staged path: the next rank tile's factor fragments load while this one
-  // computes (1) or after it (0)
-  constexpr bool kAPre = F32 ? FMM_M2L_SVD_WS_APRE_F32 : FMM_M2L_SVD_WS_APRE_F64;
-  constexpr bool kXPre = F32 ? FMM_M2L_SVD_WS_XPRE_F32 : FMM_M2L_SVD_WS_XPRE_F64;
-  constexpr int kLook = kWide ? FMM_M2L_SVD_WS_LOOK_WIDE_F32
-                              : F32 ? FMM_M2L_SVD_WS_LOOK_F32 : FMM_M2L_SVD_WS_LOOK_F64;
-  // the chunk pipeline below holds the current chunk and at most two more
-  static_assert(kLook == 1 || kLook == 2, "one or two chunks in flight");
-  const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
-  const int total = step_total(*tab);
-  int buf = 0;
-  for (int it = blockIdx.x; it < total; it += gridDim.x) {
-    SvdItem I;
-    if (!svd_item<NT>(jobs, tab, it, total, I)) continue;
-    const JobDev& J = *I.J;
-    const int KC = J.kc, ld = J.ld, XS = J.xs;
-    const int nck = KC > kg ? (KC - kg + 3) / 4 : 0;  // chunks kg, kg + 4, ...
-    const T* __restrict__ Wp = F32 ? reinterpret_cast<const T*>(J.W32)
-                                   : reinterpret_cast<const T*>(J.W);
-    const T* __restrict__ P1 = F32 ? reinterpret_cast<const T*>(J.p1_32)
-                                   : reinterpret_cast<const T*>(J.p1_64);
-    const int nact = wuni(gld(J.tile_nact + I.tile));
-    const unsigned char* act = J.tile_act + int64_t(I.tile) * kSlots;
-    const int* srcb = J.tile_src + int64_t(I.tile) * kSlots * kTileN + I.col0;
-    const int* kidp = J.slot_kid + I.tl.parity * kSlots;
-    int ia0, ia1;
-    svd_part_range(I, nact, ia0, ia1);
-    svd_meta_fill<GS>(I, nact, meta);
-    // each lane's source cells, one offset ahead
-    int src_next[NT];
-    if (ia0 < ia1) {
-      const int s0 = wuni(meta[0].s);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) src_next[j] = gld(srcb + s0 * kTileN + 16 * j + c16);
-    }
-    // the first chunk of the next offset, loaded before the barrier
-    T4 pre_bv[NT], pre_av[kRP];
-    bool have_pre = false;
-    for (int ia = ia0; ia <= ia1; ++ia) {
-      if (ia < ia1) {
-        // phase 1 of offset ia: this K-group's partial X into its slab
-        const SvdMeta md = meta[ia - ia0];
-        const int nrs = wuni(md.nr_nst);
-        const int nr = nrs & 0xffff;
-        bool on[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) on[j] = !GS || ((nrs >> (24 + I.col0 / 16 + j)) & 1);
-        const int64_t off = wuni(md.off);
-        int src[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) src[j] = src_next[j];
-        if (ia + 1 < ia1) {
-          const int sn = wuni(meta[ia + 1 - ia0].s);
-#pragma unroll
-          for (int j = 0; j < NT; ++j) src_next[j] = gld(srcb + sn * kTileN + 16 * j + c16);
-        }
-        T* const Pw = lds + buf * 4 * NC * XS + kg * NC * XS;
-        const T* bp[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          bp[j] = Wp + int64_t(src[j]) * ld + 4 * g;
-        if (D > 0) {  // the host launches D > 0 only where nck <= D
-          // the K-group's whole share of the gathered multipoles in
-          // registers at once (one memory latency per offset, not per
-          // chunk), then one rank tile after the other with the next
-          // tile's factor fragments in flight
-          T4 wv[D > 0 ? D : 1][NT], an[D > 0 ? D : 1];
-          const T* a0 = P1 + off + lane * 4;
-#pragma unroll
-          for (int u = 0; u < D; ++u) {
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-              wv[u][j] = u < nck ? gld(reinterpret_cast<const T4*>(bp[j] + 16 * (kg + 4 * u)))
-                                 : T4{0, 0, 0, 0};
-            an[u] = u < nck ? gld(reinterpret_cast<const T4*>(a0 + int64_t(kg + 4 * u) * 256))
-                            : T4{0, 0, 0, 0};
-          }
-          for (int i = 0; i < nr; ++i) {
-            T4 av[D > 0 ? D : 1];
-#pragma unroll
-            for (int u = 0; u < D; ++u) av[u] = an[u];
-            if (kAPre && i + 1 < nr) {
-              const T* an0 = a0 + int64_t(i + 1) * KC * 256;
-#pragma unroll
-              for (int u = 0; u < D; ++u)
-                an[u] = u < nck ? gld(reinterpret_cast<const T4*>(an0 + int64_t(kg + 4 * u) * 256))
-                                : T4{0, 0, 0, 0};
-            }
-            T4 x[NT];
-#pragma unroll
-            for (int j = 0; j < NT; ++j) x[j] = T4{0, 0, 0, 0};
-#pragma unroll
-            for (int u = 0; u < D; ++u) {
-              if (u >= nck) continue;
-#pragma unroll
-              for (int st = 0; st < 4; ++st)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                  if (on[j]) x[j] = mfma16x16x4(av[u][st], wv[u][j][st], x[j]);
-            }
-            if (!kAPre && i + 1 < nr) {
-              const T* an0 = a0 + int64_t(i + 1) * KC * 256;
-#pragma unroll
-              for (int u = 0; u < D; ++u)
-                an[u] = u < nck ? gld(reinterpret_cast<const T4*>(an0 + int64_t(kg + 4 * u) * 256))
-                                : T4{0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-              T* xrow = Pw + (16 * j + c16) * XS + 16 * i;
-              if (!F32) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) xrow[4 * r + g] = x[j][r];
-              } else {
-                *reinterpret_cast<T4*>(xrow + 4 * g) = x[j];
-              }
-            }
-          }
-        } else {
-        for (int i0 = 0; i0 < nr; i0 += kRP) {
-          const int np = min(kRP, nr - i0);
-          const T* a0 = P1 + off + (int64_t(i0) * KC) * 256 + lane * 4;
-          T4 x[kRP][NT];
-#pragma unroll
-          for (int i = 0; i < kRP; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) x[i][j] = T4{0, 0, 0, 0};
-          T4 bv[NT], av[kRP];
-          if (kXPre && i0 == 0 && have_pre) {
-#pragma unroll
-            for (int j = 0; j < NT; ++j) bv[j] = pre_bv[j];
-#pragma unroll
-            for (int i = 0; i < kRP; ++i) av[i] = pre_av[i];
-          } else if (kg < KC) {
-#pragma unroll
-            for (int j = 0; j < NT; ++j) bv[j] = gld(reinterpret_cast<const T4*>(bp[j] + 16 * kg));
-#pragma unroll
-            for (int i = 0; i < kRP; ++i)
-              av[i] = i < np ? gld(reinterpret_cast<const T4*>(a0 + (int64_t(i) * KC + kg) * 256))
-                             : T4{0, 0, 0, 0};
-          }
-          // chunks in flight: c + 4 (kLook = 1) or also c + 8 (kLook = 2)
-          T4 b1[kLook > 1 ? NT : 1], a1[kLook > 1 ? kRP : 1];
-          if (kLook > 1 && kg + 4 < KC) {
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-              b1[kLook > 1 ? j : 0] = gld(reinterpret_cast<const T4*>(bp[j] + 16 * (kg + 4)));
-#pragma unroll
-            for (int i = 0; i < kRP; ++i)
-              a1[kLook > 1 ? i : 0] =
-                  i < np ? gld(reinterpret_cast<const T4*>(a0 + (int64_t(i) * KC + kg + 4) * 256))
-                         : T4{0, 0, 0, 0};
-          }
-          for (int c = kg; c < KC; c += 4) {
-            T4 bn[NT], an[kRP];
-            const int cn = c + 4 * kLook;
-            const bool more = cn < KC;
-            if (more) {
-#pragma unroll
-              for (int j = 0; j < NT; ++j)
-                bn[j] = gld(reinterpret_cast<const T4*>(bp[j] + 16 * cn));
-#pragma unroll
-              for (int i = 0; i < kRP; ++i)
-                an[i] = i < np
-                            ? gld(reinterpret_cast<const T4*>(a0 + (int64_t(i) * KC + cn) * 256))
-                            : T4{0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int st = 0; st < 4; ++st)
-#pragma unroll
-              for (int i = 0; i < kRP; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                  if (i < np && on[j]) x[i][j] = mfma16x16x4(av[i][st], bv[j][st], x[i][j]);
-            if (kLook > 1) {
-#pragma unroll
-              for (int j = 0; j < NT; ++j) {
-                bv[j] = b1[kLook > 1 ? j : 0];
-                if (more) b1[kLook > 1 ? j : 0] = bn[j];
-              }
-#pragma unroll
-              for (int i = 0; i < kRP; ++i) {
-                av[i] = a1[kLook > 1 ? i : 0];
-                if (more) a1[kLook > 1 ? i : 0] = an[i];
-              }
-            } else if (more) {
-#pragma unroll
-              for (int j = 0; j < NT; ++j) bv[j] = bn[j];
-#pragma unroll
-              for (int i = 0; i < kRP; ++i) av[i] = an[i];
-            }
-          }
-          // D rows: FP32 item r -> row 4g + r, FP64 item r -> row 4r + g
-#pragma unroll
-          for (int i = 0; i < kRP; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-              if (i >= np) continue;
-              T* xrow = Pw + (16 * j + c16) * XS + 16 * (i0 + i);
-              if (!F32) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) xrow[4 * r + g] = x[i][j][r];
-              } else {
-                *reinterpret_cast<T4*>(xrow + 4 * g) = x[i][j];
-              }
-            }
-        }
-        have_pre = false;
-        if (kXPre && ia + 1 < ia1 && kg < KC) {
-          const SvdMeta mn = meta[ia + 1 - ia0];
-          const int npn = min(kRP, wuni(mn.nr_nst) & 0xffff);
-          const T* an0 = P1 + wuni(mn.off) + lane * 4;
-#pragma unroll
-          for (int j = 0; j < NT; ++j)
-            pre_bv[j] = gld(reinterpret_cast<const T4*>(Wp + int64_t(src_next[j]) * ld + 4 * g +
-                                                        16 * kg));
-#pragma unroll
-          for (int i = 0; i < kRP; ++i)
-            pre_av[i] = i < npn ? gld(reinterpret_cast<const T4*>(an0 + (int64_t(i) * KC + kg) * 256))
-                                : T4{0, 0, 0, 0};
-          have_pre = true;
-        }
-        }
-      }
-      buf ^= 1;
-      __syncthreads();
-    }
-  }
-}
-
-template <typename T, int MTW, int NT, int NCW, bool GS>
-__device__ inline void svd_ws_consume(const JobDev* __restrict__ jobs,
-                                      const StepTab* __restrict__ tab, const T* const lds,
-                                      SvdMeta* const meta, int wg) {
-  typedef typename Vec4<T>::type T4;
-  constexpr bool F32 = sizeof(T) == 4;
-  constexpr int NC = 16 * NT;
-  const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
-  const int total = step_total(*tab);
-  int buf = 0;
-  for (int it = blockIdx.x; it < total; it += gridDim.x) {
-    SvdItem I;
-    if (!svd_item<NT>(jobs, tab, it, total, I)) continue;
-    const JobDev& J = *I.J;
-    const M2LTile tl = I.tl;
-    const int MT = J.mt, ld = J.ld, XS = J.xs;
-    const int mt0 = (I.mb * NCW + wg) * MTW;
-    const int nmt = mt0 < MT ? min(MTW, MT - mt0) : 0;
-    const T* __restrict__ P2 = F32 ? reinterpret_cast<const T*>(J.p2_32)
-                                   : reinterpret_cast<const T*>(J.p2_64);
-    T4 acc[MTW][NT];
-#pragma unroll
-    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) acc[i][j] = T4{0, 0, 0, 0};
-    const int nact = wuni(gld(J.tile_nact + I.tile));
-    bool folded = false;
-    const unsigned char* act = J.tile_act + int64_t(I.tile) * kSlots;
-    const int* kidp = J.slot_kid + tl.parity * kSlots;
-    int ia0, ia1;
-    svd_part_range(I, nact, ia0, ia1);
-    svd_meta_fill<GS>(I, nact, meta);
-    // the first U fragments (rank chunk 0) of the offset consumed next,
-    // loaded before the barrier that precedes it
-    constexpr int kCP = F32 ? FMM_M2L_SVD_WS_CPRE_F32 : FMM_M2L_SVD_WS_CPRE_F64;
-    T4 cpre[kCP > 0 ? kCP : 1];
-    for (int ia = ia0; ia <= ia1; ++ia) {
-      if (ia > ia0 && nmt > 0) {
-        // phase 2 of offset ia - 1 from the buffer the producers filled
-        const int ic = ia - 1;
-        const SvdMeta md = meta[ic - ia0];
-        const int nrs = wuni(md.nr_nst);
-        const int nr = nrs & 0xffff, nst = (nrs >> 16) & 0xff;  // rank chunks; K-steps of the last
-        bool on[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) on[j] = !GS || ((nrs >> (24 + I.col0 / 16 + j)) & 1);
-        const int64_t off = wuni(md.off);
-        const T* const P = lds + (buf ^ 1) * 4 * NC * XS;
-        const T* a2 = P2 + off + int64_t(mt0) * nr * 256 + lane * 4;
-        for (int c = 0; c < nr; ++c) {
-          T4 bv[NT];
-#pragma unroll
-          for (int j = 0; j < NT; ++j) {
-            bv[j] = T4{0, 0, 0, 0};
-            if (!on[j]) continue;
-            const int o = (16 * j + c16) * XS + 16 * c + 4 * g;
-            T4 v = *reinterpret_cast<const T4*>(P + o);
-#pragma unroll
-            for (int w = 1; w < 4; ++w) v += *reinterpret_cast<const T4*>(P + w * NC * XS + o);
-            bv[j] = v;
-          }
-          // one U fragment live at a time; each accumulator still takes the
-          // K-steps in order, and the steps past the kept rank (zeros in
-          // both operands) are skipped
-          const int ns = c + 1 < nr ? 4 : nst;
-#pragma unroll
-          for (int i = 0; i < MTW; ++i) {
-            if (i >= nmt) continue;
-            const T4 av = i < kCP && c == 0
-                              ? cpre[i < kCP ? i : 0]
-                              : gld(reinterpret_cast<const T4*>(a2 + (int64_t(i) * nr + c) * 256));
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-              if (st >= ns) continue;
-#pragma unroll
-              for (int j = 0; j < NT; ++j)
-                if (on[j]) acc[i][j] = mfma16x16x4(av[st], bv[j][st], acc[i][j]);
-            }
-          }
-        }
-        if (F32 && ((ic - ia0 + 1) % J.fold_every == 0 || ic == ia1 - 1)) {
-          // fold into this item's rows of Loc (scaled; the first fold
-          // stores, later ones add): no other workgroup touches these rows
-          const double sc = J.scale[tl.level];
-#pragma unroll
-          for (int j = 0; j < NT; ++j) {
-            const int col = I.col0 + 16 * j + c16;
-            if (col < tl.count) {
-              double* out = svd_out_row(I, col);
-#pragma unroll
-              for (int i = 0; i < MTW; ++i) {
-                if (i >= nmt) continue;
-                d4* o = reinterpret_cast<d4*>(out + 16 * (mt0 + i) + 4 * g);  // rows 4g..4g+3
-                d4 v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = sc * double(acc[i][j][r]);
-                if (folded) v += gld(o);
-                gst(o, v);
-              }
-            }
-#pragma unroll
-            for (int i = 0; i < MTW; ++i) acc[i][j] = T4{0, 0, 0, 0};
-          }
-          folded = true;
-        }
-      }
-      if (kCP > 0 && ia < ia1 && nmt > 0) {
-        const SvdMeta mn = meta[ia - ia0];
-        const int nrn = wuni(mn.nr_nst) & 0xffff;
-        const T* a2n = P2 + wuni(mn.off) + int64_t(mt0) * nrn * 256 + lane * 4;
-#pragma unroll
-        for (int i = 0; i < kCP; ++i)
-          cpre[i] = i < nmt ? gld(reinterpret_cast<const T4*>(a2n + int64_t(i) * nrn * 256))
-                            : T4{0, 0, 0, 0};
-      }
-      buf ^= 1;
-      __syncthreads();
-    }
-    if (nmt == 0 || (F32 && folded)) continue;
-    const double sc = J.scale[tl.level];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const int col = I.col0 + 16 * j + c16;
-      if (col >= tl.count) continue;
-      double* out = svd_out_row(I, col);
-#pragma unroll
-      for (int i = 0; i < MTW; ++i) {
-        if (i >= nmt) continue;
-        const int base = 16 * (mt0 + i);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = F32 ? 4 * g + r : 4 * r + g;
-          gst(out + base + row, sc * double(acc[i][j][r]));
-        }
-      }
-    }
-  }
-}
-
-template <typename T, int MTW, int NT, int D, int NCW, bool GS = false>
-__global__ __launch_bounds__(64 * (4 + NCW), svd_ws_waves(NCW, NT * int(sizeof(T) / 4))) void m2l_svd_ws_kernel(
-    const JobDev* __restrict__ jobs, const StepTab* __restrict__ tab) {
-  extern __shared__ __align__(16) unsigned char lds_raw[];
-  // the per-offset table first (a fixed size, so jobs of different slab
-  // widths share one launch), then the two sets of slabs
-  static_assert(kSvdMetaBytes % 16 == 0, "slabs stay 16-byte aligned");
-  SvdMeta* const meta = reinterpret_cast<SvdMeta*>(lds_raw);
-  T* const lds = reinterpret_cast<T*>(lds_raw + kSvdMetaBytes);
-  // the role is uniform per wavefront: a scalar branch, no lane masking
-  const int wave = wuni(int(threadIdx.x >> 6));
-  if (wave < 4) {
-    // producers issue ahead of the consumers on their SIMD, so that their
-    // gathers are in flight while the consumers' MFMAs run (30M-particle
-    // order-10 cube: M2L 4255 -> 4223 ms; the same at levels 1 to 3, while
-    // raising the consumers instead costs 1.6%)
-    __builtin_amdgcn_s_setprio(1);
-    svd_ws_produce<T, NT, D, NCW, GS>(jobs, tab, lds, meta, wave);
-  } else {
-    svd_ws_consume<T, MTW, NT, NCW, GS>(jobs, tab, lds, meta, wave - 4);
-  }
-}
-
-// M-tiles per wavefront for the compressed kernel: the whole output in one
-// M-block when it fits NWV x 6 tiles (phase 1 then runs once per N-group).
-// Whether the warp-specialised kernel runs (FP32, FP64).
-#ifndef FMM_M2L_SVD_WS_F32
-#define FMM_M2L_SVD_WS_F32 1
-#endif
-#ifndef FMM_M2L_SVD_WS_F64
-#define FMM_M2L_SVD_WS_F64 1
-#endif
-// Warp-specialised kernel: when NWV consumers of up to 6 M-tiles cannot
-// hold all l^3 rows (l >= 8), 8 consumers of up to 8 M-tiles take them in
-// one M-block instead of several, each of which would repeat phase 1.
-#ifndef FMM_M2L_SVD_WIDE
-#define FMM_M2L_SVD_WIDE 1
-#endif
-constexpr int kSvdWideMtw = 8;
-// FP32, warp-specialised: where the slabs of all 64 columns of a tile fit
-// the LDS, one item takes the whole tile (NT = 4) with 8 consumers of up to
-// 6 M-tiles, so that each operator chunk is read once per tile rather than
-// once per 32-column half (M2L time on gfx950: order 7 -2.2%, order 8
-// -6.8%).  Beyond 6 M-tiles NT = 4 spills, and the shapes above take over;
-// at 16 M-tiles or fewer (l <= 6) the 32-column items are as fast (l = 6)
-// or faster (l = 5: by 9%).
-#ifndef FMM_M2L_SVD_FULL_F32
-#define FMM_M2L_SVD_FULL_F32 1
-#endif
-// FP64 likewise with 32-column items (NT = 2) where they fit: fp64_svd M2L
-// order 7 9.0 -> 8.3 ms, order 8 16.0 -> 13.6 ms (order 9 at 1e-9 needs
-// 168 KiB and keeps 16 columns).
-#ifndef FMM_M2L_SVD_FULL_F64
-#define FMM_M2L_SVD_FULL_F64 1
-#endif
-constexpr int kSvdFullNt = 4, kSvdFullNt64 = 2, kSvdFullMtw = 6;
-constexpr int svd_full_nt(bool fp32) { return fp32 ? kSvdFullNt : kSvdFullNt64; }
-constexpr size_t kSvdLdsMax = 160 * 1024;  // LDS per workgroup on gfx950
-
-struct SvdShape {
-  int ncw, mtw, nt;  // consumer wavefronts (compressed kernel: wavefronts), M-tiles each,
-                     // 16-column N-tiles per item
-};
-
-size_t m2l_svd_lds_bytes(int xs, bool fp32, int nt) {
-  return size_t(2) * 4 * 16 * nt * xs * (fp32 ? sizeof(float) : sizeof(double)) + kSvdMetaBytes;
-}
-
-static SvdShape m2l_svd_shape(int mt, bool fp32, int xs) {
-  const int nw = svd_nwv(fp32), nt = svd_nt(fp32);
-  const bool ws = fp32 ? FMM_M2L_SVD_WS_F32 : FMM_M2L_SVD_WS_F64;
-  const int fnt = svd_full_nt(fp32);
-  const bool full = fp32 ? FMM_M2L_SVD_FULL_F32 : FMM_M2L_SVD_FULL_F64;
-  if (ws && full && nt < fnt && mt > 16 && 8 * kSvdFullMtw >= mt &&
-      m2l_svd_lds_bytes(xs, fp32, fnt) <= kSvdLdsMax)
-    for (int w = 1; w <= kSvdFullMtw; ++w)
-      if (8 * w >= mt) return {8, w, fnt};
-  for (int w = 1; w <= 6; ++w)
-    if (nw * w >= mt) return {nw, w, nt};
-  if (ws && FMM_M2L_SVD_WIDE && nw < 8)
-    for (int w = 4; w <= kSvdWideMtw; ++w)
-      if (8 * w >= mt) return {8, w, nt};
-  return ws && FMM_M2L_SVD_WIDE && nw < 8 ? SvdShape{8, kSvdWideMtw, nt} : SvdShape{nw, 6, nt};
-}
-
-static int svd_kc(int order) { return (order * order * order + 15) / 16; }
-
-int m2l_svd_nt(int order, bool fp32, int xs) { return m2l_svd_shape(svd_kc(order), fp32, xs).nt; }
-
-int m2l_svd_nmb(int mt, bool fp32, int xs) {
-  const SvdShape sh = m2l_svd_shape(mt, fp32, xs);
-  return (mt + sh.ncw * sh.mtw - 1) / (sh.ncw * sh.mtw) * (4 / sh.nt);
-}
-
-// Slab row stride: the padded rank plus 16 bytes, so that consecutive target
-// columns start 16 bytes apart modulo the LDS banks.
-int m2l_svd_xs(int rmax_pad, bool fp32) { return rmax_pad + (fp32 ? 4 : 2); }
-
-size_t m2l_svd_lds_need(int order, bool fp32, int xs) {
-  return m2l_svd_lds_bytes(xs, fp32, m2l_svd_shape(svd_kc(order), fp32, xs).nt);
-}
-
-// With the warp-specialised kernel, NWV counts the consumer wavefronts (the
-// workgroup has 4 more).
-
-template <typename T, int MTW, int NT, int NCW>
-static const void* svd_ws_ptr(bool gs = false) {
-  return gs ? reinterpret_cast<const void*>(&m2l_svd_ws_kernel<T, MTW, NT, 0, NCW, true>)
-            : reinterpret_cast<const void*>(&m2l_svd_ws_kernel<T, MTW, NT, 0, NCW>);
-}
-
-// The warp-specialised kernel of a shape; staged selects the stage depth
-// FMM_M2L_SVD_WS_STAGE_* of the NWV-consumer shape, gs the form that skips
-// empty 16-target groups (whole-tile and 8-consumer shapes).
-template <typename T>
-static const void* svd_ws_fn(SvdShape sh, bool staged, bool gs) {
-  constexpr int NT = svd_nt(sizeof(T) == 4), NW = svd_nwv(sizeof(T) == 4);
-  constexpr int D = sizeof(T) == 4 ? FMM_M2L_SVD_WS_STAGE_F32 : FMM_M2L_SVD_WS_STAGE_F64;
-  const int mtw = sh.mtw;
-  constexpr int FNT = svd_full_nt(sizeof(T) == 4);
-  constexpr bool FULL = sizeof(T) == 4 ? FMM_M2L_SVD_FULL_F32 : FMM_M2L_SVD_FULL_F64;
-  if constexpr (FULL && NT < FNT) {
-    if (sh.nt == FNT) {
-      switch (mtw) {
-        case 1: return svd_ws_ptr<T, 1, FNT, 8>(gs);
-        case 2: return svd_ws_ptr<T, 2, FNT, 8>(gs);
-        case 3: return svd_ws_ptr<T, 3, FNT, 8>(gs);
-        case 4: return svd_ws_ptr<T, 4, FNT, 8>(gs);
-        case 5: return svd_ws_ptr<T, 5, FNT, 8>(gs);
-        default: return svd_ws_ptr<T, kSvdFullMtw, FNT, 8>(gs);
-      }
-    }
-  }
-  if (sh.ncw == 8 && NW != 8) {
-    switch (mtw) {
-      case 4: return svd_ws_ptr<T, 4, NT, 8>(gs);
-      case 5: return svd_ws_ptr<T, 5, NT, 8>(gs);
-      case 6: return svd_ws_ptr<T, 6, NT, 8>(gs);
-      case 7: return svd_ws_ptr<T, 7, NT, 8>(gs);
-      default: return svd_ws_ptr<T, kSvdWideMtw, NT, 8>(gs);
-    }
-  }
-#define FMM_WS_FN(M)                                                                     \
-  return staged ? reinterpret_cast<const void*>(&m2l_svd_ws_kernel<T, M, NT, D, NW>)    \
-                : svd_ws_ptr<T, M, NT, NW>()
-  switch (mtw) {
-    case 1: FMM_WS_FN(1);
-    case 2: FMM_WS_FN(2);
-    case 3: FMM_WS_FN(3);
-    case 4: FMM_WS_FN(4);
-    case 5: FMM_WS_FN(5);
-    default: FMM_WS_FN(6);
-  }
-#undef FMM_WS_FN
-}
-
-template <typename T, int FOLD>
-static void launch_svd_mtw(SvdShape sh, int kc, const JobDev* jobs, const StepTab* tab, int grid,
-                           size_t lds, hipStream_t s, bool gs) {
-  constexpr int NT = svd_nt(sizeof(T) == 4), NW = svd_nwv(sizeof(T) == 4), B = 64 * NW;
-  constexpr bool WS = sizeof(T) == 4 ? FMM_M2L_SVD_WS_F32 : FMM_M2L_SVD_WS_F64;
-  if (WS) {
-    constexpr int D = sizeof(T) == 4 ? FMM_M2L_SVD_WS_STAGE_F32 : FMM_M2L_SVD_WS_STAGE_F64;
-    const bool staged = D > 0 && (kc + 3) / 4 <= D && sh.ncw == NW && sh.nt == NT;
-    const void* f = svd_ws_fn<T>(sh, staged, gs);
-    void* args[] = {&jobs, &tab};
-    FMM_HIP_CHECK(hipLaunchKernel(f, dim3(grid), dim3(64 * (4 + sh.ncw)), args, lds, s));
-    return;
-  }
-  switch (sh.mtw) {
-    case 1: m2l_svd_kernel<T, 1, NT, NW, FOLD><<<grid, B, lds, s>>>(jobs, tab); break;
-    case 2: m2l_svd_kernel<T, 2, NT, NW, FOLD><<<grid, B, lds, s>>>(jobs, tab); break;
-    case 3: m2l_svd_kernel<T, 3, NT, NW, FOLD><<<grid, B, lds, s>>>(jobs, tab); break;
-    case 4: m2l_svd_kernel<T, 4, NT, NW, FOLD><<<grid, B, lds, s>>>(jobs, tab); break;
-    case 5: m2l_svd_kernel<T, 5, NT, NW, FOLD><<<grid, B, lds, s>>>(jobs, tab); break;
-    default: m2l_svd_kernel<T, 6, NT, NW, FOLD><<<grid, B, lds, s>>>(jobs, tab); break;
-  }
-}
-
-bool m2l_svd_splits(bool fp32) { return fp32 ? FMM_M2L_SVD_WS_F32 : FMM_M2L_SVD_WS_F64; }
-
-int m2l_svd_slots(int order, bool fp32, int xs) {
-  const int kc = svd_kc(order);
-  const SvdShape sh = m2l_svd_shape(kc, fp32, xs);
-  const int D = fp32 ? FMM_M2L_SVD_WS_STAGE_F32 : FMM_M2L_SVD_WS_STAGE_F64;
-  const bool staged =
-      D > 0 && (kc + 3) / 4 <= D && sh.ncw == svd_nwv(fp32) && sh.nt == svd_nt(fp32);
-  const void* f = fp32 ? svd_ws_fn<float>(sh, staged, false) : svd_ws_fn<double>(sh, staged, false);
-  int per_cu = 0, dev = 0, cus = 0;
-  FMM_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, f, 64 * (4 + sh.ncw), m2l_svd_lds_bytes(xs, fp32, sh.nt)));
-  FMM_HIP_CHECK(hipGetDevice(&dev));
-  FMM_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  return std::max(1, per_cu) * std::max(1, cus);
-}
-
-void launch_m2l_svd_step(int order, bool fp32, const JobDev* jobs, const StepTab* tab, int grid,
-                         int xs, hipStream_t s, bool gskip) {
-  const int kc = svd_kc(order);
-  const SvdShape sh = m2l_svd_shape(kc, fp32, xs);
-  const size_t lds = m2l_svd_lds_bytes(xs, fp32, sh.nt);
-  if (fp32)
-    launch_svd_mtw<float, FMM_M2L_SVD_F32_FOLD_MODE>(sh, kc, jobs, tab, grid, lds, s, gskip);
-  else
-    launch_svd_mtw<double, 0>(sh, kc, jobs, tab, grid, lds, s, gskip);
-  FMM_HIP_CHECK(hipGetLastError());
 }
 
 }  // namespace fmm

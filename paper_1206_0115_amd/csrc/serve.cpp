@@ -95,6 +95,7 @@ struct Launch {
   int order;
   bool fp32;
   int xs;  // LDS row stride of the compressed M2L
+  int nt;  // ... and its N-tiles per item
   bool gskip;  // compressed M2L: skip the 16-target groups without a source
 };
 
@@ -336,7 +337,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
                  bool gskip = false) {
     StepTab& t = tabs[seq.size()];
     std::memset(&t, 0, sizeof(t));
-    int tot = 0, xs = 0;
+    int tot = 0, xs = 0, nt = 0;
     for (int j = 0; j < nj; ++j) {
       if (!want(reqs[j])) continue;
       const int it = items(reqs[j]);
@@ -346,15 +347,16 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
       t.start[t.njobs] = tot;
       tot += it;
       xs = std::max(xs, reqs[j]->plan->job_h.xs);
+      nt = reqs[j]->plan->job_h.svd_nt;  // the same for every job of a launch
       ++t.njobs;
     }
     t.start[t.njobs] = tot;
     if (t.njobs == 0) return;
     if (seq.size() + 1 >= size_t(kMaxSteps)) throw FmmError{FMM_ERR_HIP, "batch step table full"};
-    if (kind != kStepM2LSvd) xs = 0;
-    seq.push_back({kind, order, fp32, xs, gskip});
+    if (kind != kStepM2LSvd) xs = nt = 0;
+    seq.push_back({kind, order, fp32, xs, nt, gskip});
     key += std::to_string(int(kind)) + ":" + std::to_string(order) + (fp32 ? "f" : "d") + ":" +
-           std::to_string(xs) + (gskip ? "g" : "") + ";";
+           std::to_string(xs) + ":" + std::to_string(nt) + (gskip ? "g" : "") + ";";
   };
   auto all_ = [](Request*) { return true; };
   auto lvl0 = [](Request*) { return 0; };
@@ -389,7 +391,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
   // dense, then compressed by the kernel's N-tiles per item (1, 2, 4): one
   // launch decodes every plan's items alike; the compressed plans that skip
   // empty 16-target groups (points on surfaces) in launches of their own
-  auto svd_nt = [&](Request* r) { return m2l_svd_nt(r->order, mixed(r), r->plan->job_h.xs); };
+  auto svd_nt = [&](Request* r) { return r->plan->job_h.svd_nt; };
   for (int L : orders)
     for (int f32 = 0; f32 < 2; ++f32)
       for (int cmp = 0; cmp < 4; ++cmp)
@@ -437,7 +439,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
     FMM_HIP_CHECK(hipMemcpyAsync(B.dev, B.pinned, kTableBytes, hipMemcpyHostToDevice, exec_stream));
     for (size_t i = 0; i < seq.size(); ++i)
       launch_step(seq[i].kind, seq[i].order, seq[i].fp32, jobs_d, tabs_d + i, calls_d,
-                  persistent_grid(seq[i].kind), exec_stream, seq[i].xs, seq[i].gskip);
+                  persistent_grid(seq[i].kind), exec_stream, seq[i].xs, seq[i].nt, seq[i].gskip);
     FMM_HIP_CHECK(hipStreamEndCapture(exec_stream, &g));
     hipGraphExec_t ge = nullptr;
     FMM_HIP_CHECK(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
