@@ -333,26 +333,29 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
     SvdItem I;
     if (!svd_item<NT>(jobs, tab, it, total, I)) continue;
     const JobDev& J = *I.J;
-    const int MT = J.mt, XS = J.xs, na = I.ia1 - I.ia0;
+    const int MT = wuni(J.mt), XS = wuni(J.xs), na = I.ia1 - I.ia0;
     const int64_t ld = J.ld;
     const int mt0 = (I.mb * NCW + wg) * MTW;
     const int nmt = mt0 < MT ? min(MTW, MT - mt0) : 0;
     const T* __restrict__ P2 = (F32 ? reinterpret_cast<const T*>(J.p2_32)
                                     : reinterpret_cast<const T*>(J.p2_64));
     T4 acc[MTW][NT];
-#pragma unroll
-    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) acc[i][j] = T4{0, 0, 0, 0};
+    auto clear = [&]() FMM_INLINE {
+      static_for<MTW>([&](auto i) FMM_INLINE {
+        static_for<NT>([&](auto j) FMM_INLINE { acc[i][j] = T4{0, 0, 0, 0}; });
+      });
+    };
+    clear();
     bool folded = false;
     svd_fill<NT, GS>(I, meta, srct);
+    const int fold_every = wuni(J.fold_every);
     T4 ring[RD];
     if (nmt > 0 && na > 0) {
       const int nr = wuni(meta[0].nr_nst) & 0xffff;
       const T* const a2 = P2 + wuni(meta[0].off) + int64_t(mt0) * nr * 256;
-#pragma unroll
-      for (int i = 0; i < RD; ++i)
-        ring[i] = frag(a2 + int64_t(min(i, nmt - 1)) * nr * 256, lo);
+      static_for<RD>([&](auto i) FMM_INLINE {
+        ring[i] = frag(a2 + int64_t(min(int(i), nmt - 1)) * nr * 256, lo);
+      });
     }
     for (int ia = 0; ia <= na; ++ia) {
       if (ia > 0 && nmt > 0) {
@@ -360,25 +363,22 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
         const int ic = ia - 1, inx = min(ia, na - 1);
         const int nrs = wuni(meta[ic].nr_nst);
         const int nr = nrs & 0xffff, nst = (nrs >> 16) & 0xff;  // rank chunks; K-steps of the last
-        bool on[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) on[j] = !GS || ((nrs >> (24 + I.col0 / 16 + j)) & 1);
+        const int gon = nrs >> (24 + I.col0 / 16);
         const T* const X = slabs + ((buf ^ 1) * NS * NC + c16) * XS + 4 * g;
         const T* const a2 = P2 + wuni(meta[ic].off) + int64_t(mt0) * nr * 256;
         const int nrn = wuni(meta[inx].nr_nst) & 0xffff;
         const T* const a2n = P2 + wuni(meta[inx].off) + int64_t(mt0) * nrn * 256;
         for (int c = 0; c < nr; ++c) {
           T4 bv[NT];
-#pragma unroll
-          for (int j = 0; j < NT; ++j) {
+          static_for<NT>([&](auto j) FMM_INLINE {
             bv[j] = T4{0, 0, 0, 0};
-            if (!on[j]) continue;
+            if (GS && !((gon >> j) & 1)) return;
             T4 v = *reinterpret_cast<const T4*>(X + 16 * j * XS + 16 * c);
-#pragma unroll
-            for (int k = 1; k < NS; ++k)
-              v += *reinterpret_cast<const T4*>(X + (k * NC + 16 * j) * XS + 16 * c);
+            static_for<NS - 1>([&](auto k) FMM_INLINE {
+              v += *reinterpret_cast<const T4*>(X + ((k + 1) * NC + 16 * j) * XS + 16 * c);
+            });
             bv[j] = v;
-          }
+          });
           const bool more = c + 1 < nr;
           // where the ring reads on past this chunk's last M-tile
           const T* const an = more ? a2 + int64_t(c + 1) * 256 : a2n;
@@ -395,7 +395,7 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
                 if (st >= ns) continue;
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
-                  if (on[j]) acc[i][j] = mfma16x16x4(av[st], bv[j][st], acc[i][j]);
+                  if (!GS || ((gon >> j) & 1)) acc[i][j] = mfma16x16x4(av[st], bv[j][st], acc[i][j]);
               }
             }
             __builtin_amdgcn_sched_barrier(0);  // a stage is free once used
@@ -404,29 +404,26 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
                              : an + min(i + RD - MTW, nmt - 1) * sn, lo);
           }
         }
-        if (F32 && ((ic + 1) % J.fold_every == 0 || ic == na - 1)) {
+        if (F32 && ((ic + 1) % fold_every == 0 || ic == na - 1)) {
           // fold into this item's rows of Loc (scaled; the first fold
           // stores, later ones add): no other workgroup touches these rows
           const double sc = J.scale[I.tl.level];
-#pragma unroll
-          for (int j = 0; j < NT; ++j) {
+          static_for<NT>([&](auto j) FMM_INLINE {
             const int col = I.col0 + 16 * j + c16;
             if (col < I.tl.count) {
               double* out = m2l_out_row(J, I.part, gld(J.tgt + I.tl.first + col));
-#pragma unroll
-              for (int i = 0; i < MTW; ++i) {
-                if (i >= nmt) continue;
+              static_for<MTW>([&](auto i) FMM_INLINE {
+                if (i >= nmt) return;
                 d4* o = reinterpret_cast<d4*>(out + 16 * (mt0 + i) + 4 * g);  // rows 4g..4g+3
                 d4 v;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = sc * double(acc[i][j][r]);
                 if (folded) v += gld(o);
                 gst(o, v);
-              }
+              });
             }
-#pragma unroll
-            for (int i = 0; i < MTW; ++i) acc[i][j] = T4{0, 0, 0, 0};
-          }
+          });
+          clear();
           folded = true;
         }
       }
@@ -435,27 +432,22 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
     }
     if (nmt == 0 || (F32 && folded)) continue;
     const double sc = J.scale[I.tl.level];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
+    static_for<NT>([&](auto j) FMM_INLINE {
       const int col = I.col0 + 16 * j + c16;
-      if (col >= I.tl.count) continue;
+      if (col >= I.tl.count) return;
       double* out = m2l_out_row(J, I.part, gld(J.tgt + I.tl.first + col));
-#pragma unroll
-      for (int i = 0; i < MTW; ++i) {
-        if (i >= nmt) continue;
-        const int base = 16 * (mt0 + i);
+      static_for<MTW>([&](auto i) FMM_INLINE {
+        if (i >= nmt) return;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          gst(out + base + (F32 ? 4 * g + r : 4 * r + g), sc * double(acc[i][j][r]));
-      }
-    }
+          gst(out + 16 * (mt0 + i) + (F32 ? 4 * g + r : 4 * r + g), sc * double(acc[i][j][r]));
+      });
+    });
   }
 }
 
-// GS: the N-tiles whose 16 target columns have no source at an offset (their
-// multipole columns are the zero row, so their products are zero) are
-// skipped, by both roles: a wavefront-uniform test per N-tile in the
-// consumers, which only plans with many empty groups take.
+// GS (plans with many empty 16-target groups): the N-tiles whose columns have
+// no source at an offset, all products zero, are skipped by both roles.
 template <typename T, int MTW, int NCW, typename PC, bool GS>
 __global__ __launch_bounds__(64 * (PC::NPW + NCW), NCW == 4 && MTW < 6 ? 4 : (PC::NPW + NCW) / 4) void m2l_svd_kernel(
     const JobDev* __restrict__ jobs, const StepTab* __restrict__ tab, int staged) {
@@ -516,6 +508,9 @@ SvdShape svd_shape(int mt, bool fp32, int xs, int nt) {
   // whether four partial slabs of 64 FP32 or 32 FP64 columns fit the LDS
   const bool four = size_t(2048) * xs + kSvdMetaBytes <= kSvdLdsMax;
   if (fp32) {
+    if (mt <= 4)
+      return nt == 2 ? svd_make<float, 1, 4, Producers<4, 2, 1, 2, 2, 1>>()
+                     : svd_make<float, 1, 4, Producers<4, 1, 1, 1, 1, 1>>();
     if (mt <= 8)
       return nt == 2 ? svd_make<float, 2, 4, Producers<4, 2, 1, 2, 2, 2>>()
                      : svd_make<float, 2, 4, Producers<4, 1, 1, 1, 2, 2>>();
@@ -540,6 +535,9 @@ SvdShape svd_shape(int mt, bool fp32, int xs, int nt) {
     if (w == 7) return svd_make<float, 7, 8, Producers<4, 1, 1, 1, 4, 2>>();
     return svd_make<float, 8, 8, Producers<4, 1, 1, 1, 4, 2>>();
   }
+  if (mt <= 4)
+    return nt == 2 ? svd_make<double, 1, 4, Producers<4, 2, 1, 2, 2, 1>>()
+                   : svd_make<double, 1, 4, Producers<4, 1, 1, 1, 1, 1>>();
   if (nt == 2) {
     if (mt <= 8) return svd_make<double, 2, 4, Producers<4, 2, 1, 2, 2, 2>>();
     if (mt <= 16)
@@ -576,8 +574,10 @@ static int svd_widest(int mt, bool fp32) {
 
 // N-tiles per item: the widest shape reads each operator fragment for the most
 // columns, but a plan of few tiles then leaves CUs idle or ends on a partly
-// empty round.  Half the columns take 0.62 of an item's time (order 7 to 10),
-// so the fewest rounds in those units win (20,000 particles, height 4, order
+// empty round.  Half the columns take 0.62 of an item's time (order 7 to 10;
+// 0.8 below, where an item's fixed work weighs more: points on spheres, order
+// 3, 30,000 at height 6 117 -> 107 us, 100,000 at height 7 317 -> 220), so the
+// fewest rounds in those units win (20,000 particles, height 4, order
 // 7: 64, 32, 16 columns 379, 238, 157 us; 60,000, height 5: 515, 608, 743).
 // Every column's sums are the same in each shape.
 int m2l_svd_nt(int order, bool fp32, int64_t tile_parts, int cus) {
@@ -586,7 +586,7 @@ int m2l_svd_nt(int order, bool fp32, int64_t tile_parts, int cus) {
   const int64_t slots = int64_t(mt <= (fp32 ? 16 : 8) ? 2 : 1) * std::max(1, cus);
   int best = widest;
   double best_cost = 0.0, item = 1.0;
-  for (int nt = widest; nt >= 1; nt /= 2, item *= 0.62) {
+  for (int nt = widest; nt >= 1; nt /= 2, item *= mt <= 16 ? 0.8 : 0.62) {
     const int64_t items = tile_parts * m2l_svd_nmb(mt, fp32, nt);
     const double cost = double((items + slots - 1) / slots) * item;
     if (nt == widest || cost < 0.95 * best_cost) {

@@ -347,7 +347,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
       t.start[t.njobs] = tot;
       tot += it;
       xs = std::max(xs, reqs[j]->plan->job_h.xs);
-      nt = reqs[j]->plan->job_h.svd_nt;  // the same for every job of a launch
+      nt = jobs[j].svd_nt;  // the same for every job of a compressed M2L launch
       ++t.njobs;
     }
     t.start[t.njobs] = tot;
@@ -388,25 +388,38 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
           [&](Request* r) { return r->h - 2 - s; });
   add(kStepCast, 0, true, [&](Request* r) { return far(r) && mixed(r); },
       [](Request* r) { return int(r->plan->tab_h[kTabCast].start[1]); }, lvl0);
-  // dense, then compressed by the kernel's N-tiles per item (1, 2, 4): one
-  // launch decodes every plan's items alike; the compressed plans that skip
-  // empty 16-target groups (points on surfaces) in launches of their own
-  auto svd_nt = [&](Request* r) { return r->plan->job_h.svd_nt; };
+  // dense, then compressed; the compressed plans that skip empty 16-target
+  // groups (points on surfaces) in launches of their own.  The jobs of a
+  // compressed launch take the item width that suits their tiles together
+  // (every width gives a plan the same results)
+  int cus = 0;
+  FMM_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
   for (int L : orders)
     for (int f32 = 0; f32 < 2; ++f32)
-      for (int cmp = 0; cmp < 4; ++cmp)
-        for (int gs = 0; gs < (cmp ? 2 : 1); ++gs)
-          add(cmp ? kStepM2LSvd : kStepM2L, L, f32 != 0,
+      for (int cmp = 0; cmp < 2; ++cmp)
+        for (int gs = 0; gs < (cmp ? 2 : 1); ++gs) {
+          auto want = [&](Request* r) {
+            return far(r) && r->order == L && mixed(r) == (f32 != 0) && svd(r) == (cmp != 0) &&
+                   (cmp == 0 || r->plan->m2l_gskip == (gs != 0));
+          };
+          if (cmp) {
+            int64_t tile_parts = 0;
+            for (int j = 0; j < nj; ++j)
+              if (want(reqs[j])) tile_parts += int64_t(jobs[j].ntiles) * jobs[j].m2l_parts;
+            const int nt = m2l_svd_nt(L, f32 != 0, tile_parts, cus);
+            for (int j = 0; j < nj; ++j)
+              if (want(reqs[j])) {
+                jobs[j].svd_nt = nt;
+                jobs[j].nmb = m2l_svd_nmb(jobs[j].mt, f32 != 0, nt);
+              }
+          }
+          add(cmp ? kStepM2LSvd : kStepM2L, L, f32 != 0, want,
               [&](Request* r) {
-                return far(r) && r->order == L && mixed(r) == (f32 != 0) &&
-                       svd(r) == (cmp != 0) &&
-                       (cmp == 0 || (svd_nt(r) == 1 << (cmp - 1) &&
-                                     r->plan->m2l_gskip == (gs != 0)));
-              },
-              [](Request* r) {
-                return int(r->plan->ntiles) * r->plan->job_h.nmb * r->plan->job_h.m2l_parts;
+                const JobDev& J = jobs[std::find(reqs.begin(), reqs.end(), r) - reqs.begin()];
+                return J.ntiles * J.nmb * J.m2l_parts;
               },
               lvl0, gs != 0);
+        }
   // partial sums of plans that split their M2L back into Loc
   add(kStepLocSum, 0, false, [&](Request* r) { return far(r) && r->plan->job_h.m2l_parts > 1; },
       [](Request* r) { return loc_sum_items(r->plan->job_h); }, lvl0);
