@@ -532,40 +532,65 @@ __global__ __launch_bounds__(64) void l2p_sparse_kernel(const JobDev* __restrict
 }
 
 // ------------------------------------------------------------------- P2P
-// Item = target leaf, one wavefront.  Source leaves of the near list are
-// staged through LDS in tiles of 64 particles.  When the leaf holds P <= 32
-// targets, the 64 lanes split into 64/P groups that take interleaved
-// sources, and the partial sums are combined with wavefront butterflies.
-__device__ inline int p2p_groups(int nt) {
-  int P = 1;
-  while (P < nt && P < 64) P <<= 1;
-  return P;
-}
+// Item = target leaf, one workgroup of W = 1, 4 or 16 wavefronts (p2p_waves),
+// so that a plan of few leaves still fills the GPU and a leaf of many
+// particles is not the launch's tail.  The vector units bound large plans:
+// 18 instructions (FP64) or 17 (FP32) a pair and the reciprocal (square) root.
+// Near field, one wavefront a leaf with a lane per target before, and now:
+// FP64 20,000 particles, height 4 114 -> 53 us, 300,000, height 5 976 -> 532,
+// 1M, height 6 1009 -> 722; FP32 200,000 on a sphere, height 6 215 -> 134, 10M,
+// height 8 11.6 -> 10.5 ms.
+constexpr int kSelfSlot = 13;  // the near-list slot of the target leaf itself
+constexpr double kFarAway = 1e30;
+typedef double src4 __attribute__((ext_vector_type(4)));  // x, y, z, q of one source
 
-// One near-field pair for the kernel |x - y|^-KP: adds the potential term
-// q r^-KP to ph and the force factor KP q r^-(KP+2) times d to (fx, fy, fz);
-// the target charge multiplies the force at the end.  Zero distance adds 0.
-// CHECK: whether the pair may be at zero distance.  Particles at one position
-// share a leaf, so only the target leaf's own particles need the test; the
-// padding of a source tile (q = 0, 1e30 away) contributes exact zeros.
-template <int KP, bool CHECK = true>
-__device__ __forceinline__ void pair_f64(double dx, double dy, double dz, double q, double& ph,
-                                         double& fx, double& fy, double& fz) {
+struct Near4 {
+  double ph, fx, fy, fz;
+};
+
+// One FP64 near-field pair for the kernel |x - y|^-KP: adds the potential
+// term q r^-KP to ph and the force factor KP q r^-(KP+2) times d to (fx, fy,
+// fz); the target charge multiplies the force at the end.  Zero distance adds
+// 0.  CHECK: whether the pair may be at zero distance.  Particles at one
+// position share a leaf, so only the target leaf's own particles need the
+// test; the padding of a source tile (q = 0, 1e30 away) contributes exact
+// zeros.  The hardware's approximation (good to about 2^-24) and one
+// third-order step leave an error below 2^-70 before rounding; where r^2
+// overflows or underflows they give NaN, and SAFE takes the library's root
+// and divide instead.
+template <int KP, bool CHECK, bool SAFE>
+__device__ __forceinline__ void pair_f64(double dx, double dy, double dz, double q, Near4& a) {
   const double r2 = dx * dx + dy * dy + dz * dz;
   double t, s;
   if (KP == 2) {
-    const double ir2 = !CHECK || r2 > 0.0 ? 1.0 / r2 : 0.0;
+    double ir2;
+    if (SAFE) {
+      ir2 = 1.0 / r2;
+    } else {
+      const double y = __builtin_amdgcn_rcp(r2);
+      const double e = fma(-r2, y, 1.0);
+      ir2 = fma(y, fma(e, e, e), y);
+    }
+    if (CHECK) ir2 = r2 > 0.0 ? ir2 : 0.0;
     t = q * ir2;
     s = 2.0 * t * ir2;
   } else {
-    const double ir = !CHECK || r2 > 0.0 ? rsqrt(r2) : 0.0;
+    double ir;
+    if (SAFE) {
+      ir = rsqrt(r2);
+    } else {
+      const double y = __builtin_amdgcn_rsq(r2);
+      const double e = fma(-(r2 * y), y, 1.0);
+      ir = fma(y * e, fma(e, 0.375, 0.5), y);
+    }
+    if (CHECK) ir = r2 > 0.0 ? ir : 0.0;
     t = q * ir;
     s = t * ir * ir;
   }
-  ph += t;
-  fx += s * dx;
-  fy += s * dy;
-  fz += s * dz;
+  a.ph += t;
+  a.fx += s * dx;
+  a.fy += s * dy;
+  a.fz += s * dz;
 }
 
 // The same in FP32 (v_rsq_f32 for 1/r, v_rcp_f32 for 1/r^2).
@@ -589,11 +614,200 @@ __device__ __forceinline__ void pair_f32(float dx, float dy, float dz, float q, 
   fz += s * dz;
 }
 
-// Next chunk (up to 64 consecutive particles of one source leaf) of the near
-// list, in slot order: advances (sl, jb, j1) and returns false past the last
-// one.  Lane s < 27 holds the particle range [nj0, nj1) of near slot s (empty
-// for an absent neighbour).  Start from sl = -1, jb = j1 = 0.  No memory
-// access: the loads of the chunk in flight are not waited for.
+// A target's sums to the near field's outputs.
+__device__ __forceinline__ void p2p_store(const JobDev& J, int i, const Near4& a) {
+  const double qi = gld(J.qs + i);
+  gst(J.phi_n + i, a.ph);
+  const int64_t i3 = 3 * int64_t(i);
+  gst(J.f_n + i3, qi * a.fx);
+  gst(J.f_n + i3 + 1, qi * a.fy);
+  gst(J.f_n + i3 + 2, qi * a.fz);
+}
+
+// --- FP64.  Thread = (two targets, split): a batch of nb pairs of targets gives
+// T / nb splits of the sources, so that most lanes work whatever the leaf's
+// size (a lane per target of 64 left a third of them idle); two targets share
+// an LDS read.  The near list's particles, the leaf's own first, pass through
+// LDS T at a time as one run; the next T are read while the current ones are
+// computed.  The splits' sums are added pairwise in a fixed order.
+template <int W>
+struct P2PLds {
+  static constexpr int T = 64 * W;
+  union {
+    src4 src[2 * T];  // the second half stays padding
+    double red[4][T];
+  };
+  int pre[28], base[27];  // the run's slots: first position, first particle
+};
+
+struct P2PTargets {
+  double x[2], y[2], z[2];
+};
+
+template <int KP, bool SAFE, int W>
+__device__ __forceinline__ void p2p_run(const JobDev& J, P2PLds<W>& L, int total, int nself, int K,
+                                        int k, const P2PTargets& t, Near4* acc) {
+  constexpr int T = 64 * W;
+  const int tid = threadIdx.x;
+  acc[0] = acc[1] = Near4{0.0, 0.0, 0.0, 0.0};
+  int sl = 0;
+  src4 next;
+  auto load = [&](int pos) {
+    next = src4{kFarAway, kFarAway, kFarAway, 0.0};
+    if (pos < total) {
+      while (pos >= L.pre[sl + 1]) ++sl;
+      const int j = L.base[sl] + pos - L.pre[sl];
+      next = src4{gld(J.px + j), gld(J.py + j), gld(J.pz + j), gld(J.qs + j)};
+    }
+  };
+  // the first particle's slot by bisection, the later ones' from there on
+#pragma unroll
+  for (int step = 16; step >= 1; step /= 2)
+    if (sl + step < 27 && L.pre[sl + step] <= tid) sl += step;
+  load(tid);
+  for (int p0 = 0; p0 < total; p0 += T) {
+    __syncthreads();  // the previous tile's reads are done
+    L.src[tid] = next;
+    __syncthreads();
+    load(p0 + T + tid);
+    const int npass = (min(T, total - p0) + K - 1) / K;
+    const int ncheck = min(npass, (max(nself - p0, 0) + K - 1) / K);
+    const src4* u = L.src + k;
+    int i = 0;
+    for (; i < ncheck; ++i, u += K)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        pair_f64<KP, true, SAFE>(t.x[r] - u->x, t.y[r] - u->y, t.z[r] - u->z, u->w, acc[r]);
+    for (; i < npass; ++i, u += K)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        pair_f64<KP, false, SAFE>(t.x[r] - u->x, t.y[r] - u->y, t.z[r] - u->z, u->w, acc[r]);
+  }
+}
+
+template <int KP, bool SELF, int W>
+__device__ __forceinline__ void p2p_leaf_f64(const JobDev& J, int a, P2PLds<W>& L) {
+  constexpr int T = 64 * W;
+  const int tid = threadIdx.x;
+  const int t0 = wuni(gld(J.leaf_start + a)), nt = wuni(gld(J.leaf_start + a + 1)) - t0;
+  if (tid < 64) {
+    // slot 0 of the run is the leaf itself, then the other near slots
+    int cnt = 0, first = 0;
+    if (tid < (SELF ? 1 : 27)) {
+      const int slot = tid == 0 ? kSelfSlot : tid <= kSelfSlot ? tid - 1 : tid;
+      const int b = gld(J.near + 27 * a + slot);
+      if (b >= 0) {
+        first = gld(J.leaf_start + b);
+        cnt = gld(J.leaf_start + b + 1) - first;
+      }
+    }
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (tid >= o) incl += v;
+    }
+    if (tid < 27) {
+      L.pre[tid + 1] = incl;
+      L.base[tid] = first;
+    }
+    if (tid == 0) L.pre[0] = 0;
+  }
+  __syncthreads();
+  const int total = wuni(L.pre[27]), nself = wuni(L.pre[1]);
+  // batches of target pairs: the fewest passes, batches / splits, of one to
+  // four (more where a batch would exceed the threads)
+  const int pairs = (nt + 1) / 2, b0 = (pairs + T - 1) / T;
+  int nb = 0, K = 0;
+  float best = 0.f;
+  for (int B = b0; B < b0 + 4; ++B) {
+    const int n = (pairs + B - 1) / B, k = T / n;
+    const float cost = float(B) / float(k);
+    if (K == 0 || cost < 0.99f * best) {
+      nb = n;
+      K = k;
+      best = cost;
+    }
+  }
+  const int k = tid / nb, t = tid - k * nb;
+  for (int tb = 0; tb < pairs; tb += nb) {
+    // targets of the pair: tb + t and, half the leaf on, pairs + tb + t
+    const int p = tb + t;
+    const bool on = k < K && p < pairs, two = on && pairs + p < nt;
+    const int it[2] = {t0 + (on ? p : 0), t0 + (two ? pairs + p : 0)};
+    P2PTargets tg;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      tg.x[r] = gld(J.px + it[r]);
+      tg.y[r] = gld(J.py + it[r]);
+      tg.z[r] = gld(J.pz + it[r]);
+    }
+    Near4 acc[2];
+    p2p_run<KP, false, W>(J, L, total, nself, K, on ? k : 0, tg, acc);
+    double all = 0.0;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      all += (fabs(acc[r].ph) + fabs(acc[r].fx)) + (fabs(acc[r].fy) + fabs(acc[r].fz));
+    if (__syncthreads_or(on && !(all < INFINITY)))
+      p2p_run<KP, true, W>(J, L, total, nself, K, on ? k : 0, tg, acc);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      __syncthreads();  // the sources, or the first targets' sums, are read
+      L.red[0][tid] = acc[r].ph;
+      L.red[1][tid] = acc[r].fx;
+      L.red[2][tid] = acc[r].fy;
+      L.red[3][tid] = acc[r].fz;
+      for (int n = K; n > 1;) {
+        const int half = (n + 1) / 2;
+        __syncthreads();
+        if (k + half < n)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) L.red[c][tid] += L.red[c][tid + half * nb];
+        n = half;
+      }
+      if (k == 0 && (r == 0 ? on : two))
+        p2p_store(J, it[r], Near4{L.red[0][tid], L.red[1][tid], L.red[2][tid], L.red[3][tid]});
+    }
+    __syncthreads();
+  }
+}
+
+template <bool SELF, int W>
+__global__ __launch_bounds__(64 * W) void p2p_f64_kernel(const JobDev* __restrict__ jobs,
+                                                         const StepTab* __restrict__ tab) {
+  __shared__ P2PLds<W> L;
+  L.src[64 * W + threadIdx.x] = src4{kFarAway, kFarAway, kFarAway, 0.0};
+  FOR_ITEMS(tab) {
+    const int k = step_find(*tab, it_);
+    const JobDev& J = jobs[tab->job[k]];
+    const int a = it_ - tab->start[k];
+    if (J.kernel == 2)
+      p2p_leaf_f64<2, SELF, W>(J, a, L);
+    else
+      p2p_leaf_f64<1, SELF, W>(J, a, L);
+  }
+}
+
+// --- FP32.  The near list is taken in chunks of up to 64 consecutive
+// particles of one source leaf, the wavefronts in turn; each stages its chunk
+// in LDS, its next chunk's loads in flight meanwhile.  When the leaf holds P
+// <= 32 targets, the 64 lanes split into 64 / P groups that take interleaved
+// sources.  The pair difference is taken in FP64 and rounded once (a relative
+// error of 2^-24 of the distance itself, however close the pair), r^2, the
+// reciprocal (square) root and the products are FP32, and the partial sums
+// over one source chunk (so their rounding does not grow with the leaves'
+// occupancy) are kept in FP32 and folded into FP64 accumulators.
+__device__ inline int p2p_groups(int nt) {
+  int P = 1;
+  while (P < nt && P < 64) P <<= 1;
+  return P;
+}
+
+// Next chunk of the near list, in slot order: advances (sl, jb, j1) and
+// returns false past the last one.  Lane s < 27 holds the particle range
+// [nj0, nj1) of near slot s (empty for an absent neighbour).  Start from sl =
+// -1, jb = j1 = 0.  No memory access: the loads of the chunk in flight are
+// not waited for.
 __device__ __forceinline__ bool near_next(int nj0, int nj1, int& sl, int& jb, int& j1) {
   jb += 64;
   while (jb >= j1) {
@@ -604,18 +818,8 @@ __device__ __forceinline__ bool near_next(int nj0, int nj1, int& sl, int& jb, in
   return true;
 }
 
-// One target leaf.  The source chunks pass through LDS one at a time; the
-// next chunk's loads are in flight while the current one is computed.  FP32:
-// the pair difference is taken in FP64 and rounded once (a relative error of
-// 2^-24 of the distance itself, however close the pair), r^2, the reciprocal
-// (square) root and the products are FP32, and the partial sums over one
-// source chunk (at most 64 particles, so their rounding does not grow with
-// the leaves' occupancy) are kept in FP32 and folded into FP64 accumulators.
-// Pairs are taken in the same order as one leaf, one chunk at a time.
-typedef double src4 __attribute__((ext_vector_type(4)));  // x, y, z, q of one source
-
-// FP32 charges travel in the q slot as their own bits (low word), so the
-// pair loop reads them without a conversion.
+// The charge travels in the q slot as its own bits (low word), so the pair
+// loop reads it without a conversion.
 __device__ __forceinline__ double q_slot(float q) {
   return __longlong_as_double(static_cast<long long>(__float_as_uint(q)));
 }
@@ -623,53 +827,146 @@ __device__ __forceinline__ float q_of_slot(double d) {
   return __uint_as_float(static_cast<unsigned>(__double_as_longlong(d)));
 }
 
-// A source tile's passes for one lane group: sources k = split + S i,
+// A source chunk's passes for one lane group: sources k = split + S i,
 // i < npass (a wavefront-uniform count, so the loop needs no lane masks),
-// two per iteration, in increasing i.  Slots past the tile's sources hold
+// two per iteration, in increasing i.  Slots past the chunk's sources hold
 // the padding source, which adds zeros.
-constexpr int kSelfSlot = 13;   // the near-list slot of the target leaf itself
-constexpr int kSrcSlots = 128;  // 64 staged sources, then padding for the last passes
-constexpr double kFarAway = 1e30;
-
-template <int KP, bool CHECK>
-__device__ __forceinline__ void p2p_passes_f32(const src4* src, int split, int S, int npass,
-                                               double xi, double yi, double zi, float& p32,
-                                               float& x32, float& y32, float& z32) {
+template <int KP, bool CHECK, int R>
+__device__ __forceinline__ void p2p_passes_f32(const src4* src, int S, int npass,
+                                               const P2PTargets& t, float (&sum)[R][4]) {
+  auto pair = [&](const src4& u) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      pair_f32<KP, CHECK>(float(t.x[r] - u.x), float(t.y[r] - u.y), float(t.z[r] - u.z),
+                          q_of_slot(u.w), sum[r][0], sum[r][1], sum[r][2], sum[r][3]);
+  };
   int i = 0;
   for (; i + 1 < npass; i += 2) {
-    const src4 u = src[split + S * i], v = src[split + S * (i + 1)];
-    pair_f32<KP, CHECK>(float(xi - u.x), float(yi - u.y), float(zi - u.z), q_of_slot(u.w), p32,
-                        x32, y32, z32);
-    pair_f32<KP, CHECK>(float(xi - v.x), float(yi - v.y), float(zi - v.z), q_of_slot(v.w), p32,
-                        x32, y32, z32);
+    const src4 u = src[S * i], v = src[S * (i + 1)];
+    pair(u);
+    pair(v);
   }
-  if (i < npass) {
-    const src4 u = src[split + S * i];
-    pair_f32<KP, CHECK>(float(xi - u.x), float(yi - u.y), float(zi - u.z), q_of_slot(u.w), p32,
-                        x32, y32, z32);
-  }
+  if (i < npass) pair(src[S * i]);
 }
 
-template <int KP, bool CHECK>
-__device__ __forceinline__ void p2p_passes_f64(const src4* src, int split, int S, int npass,
-                                               double xi, double yi, double zi, double& ph,
-                                               double& fx, double& fy, double& fz) {
-  for (int i = 0; i < npass; ++i) {
-    const src4 u = src[split + S * i];
-    pair_f64<KP, CHECK>(xi - u.x, yi - u.y, zi - u.z, u.w, ph, fx, fy, fz);
+template <int W>
+struct P2PLds32 {
+  src4 src[W][64];
+  double red[W - 1][4][64];
+};
+template <>
+struct P2PLds32<1> {
+  src4 src[1][64];
+};
+
+// R batches of 64 targets (two share the staging and LDS reads), from tb on.
+template <int KP, int W, int R>
+__device__ __forceinline__ void p2p_batch_f32(const JobDev& J, P2PLds32<W>& L, int nj0, int nj1,
+                                              int t0, int nt, int tb, int P) {
+  const int lane = threadIdx.x & 63, wave = W > 1 ? wuni(int(threadIdx.x) / 64) : 0;
+  src4* const src = L.src[wave];
+  const double *px = J.px, *py = J.py, *pz = J.pz;
+  const int S = 64 / P, split = lane / P;
+  P2PTargets t;
+  bool valid[R];
+  int it[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int ti = tb + 64 * r + (lane % P);
+    valid[r] = ti < nt;
+    it[r] = t0 + (valid[r] ? ti : 0);
+    t.x[r] = gld(px + it[r]);
+    t.y[r] = gld(py + it[r]);
+    t.z[r] = gld(pz + it[r]);
+  }
+  Near4 acc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = Near4{0.0, 0.0, 0.0, 0.0};
+  int sl = -1, jb = 0, j1 = 0;
+  // the wavefront's next chunk: `skip` chunks of the other wavefronts on
+  auto advance = [&](int skip) {
+    bool more = near_next(nj0, nj1, sl, jb, j1);
+    for (int o = 0; o < skip && more; ++o) more = near_next(nj0, nj1, sl, jb, j1);
+    return more;
+  };
+  double rx, ry, rz;
+  float rq;
+  int cnt;
+  auto load = [&](bool have) {
+    cnt = have ? min(64, j1 - jb) : 0;
+    rx = ry = rz = kFarAway;
+    rq = 0.f;
+    if (lane < cnt) {
+      rx = gld(px + jb + lane);
+      ry = gld(py + jb + lane);
+      rz = gld(pz + jb + lane);
+      rq = gld(J.q32 + jb + lane);
+    }
+  };
+  bool have = advance(wave);
+  load(have);
+  while (have) {
+    const int ccnt = cnt, csl = sl;
+    wave_lds_sync();  // the previous chunk's reads are done
+    src[lane] = src4{rx, ry, rz, q_slot(rq)};
+    wave_lds_sync();
+    have = advance(W - 1);
+    load(have);
+    const int npass = (ccnt + S - 1) / S;
+    float sum[R][4];
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum[r][0] = sum[r][1] = sum[r][2] = sum[r][3] = 0.f;
+    if (csl == kSelfSlot)
+      p2p_passes_f32<KP, true, R>(src + split, S, npass, t, sum);
+    else
+      p2p_passes_f32<KP, false, R>(src + split, S, npass, t, sum);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      acc[r].ph += double(sum[r][0]);
+      acc[r].fx += double(sum[r][1]);
+      acc[r].fy += double(sum[r][2]);
+      acc[r].fz += double(sum[r][3]);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    for (int o = P; o < 64; o <<= 1) {
+      acc[r].ph += __shfl_xor(acc[r].ph, o, 64);
+      acc[r].fx += __shfl_xor(acc[r].fx, o, 64);
+      acc[r].fy += __shfl_xor(acc[r].fy, o, 64);
+      acc[r].fz += __shfl_xor(acc[r].fz, o, 64);
+    }
+    if constexpr (W > 1) {
+      __syncthreads();  // the previous batch's sums are read
+      if (wave > 0) {
+        L.red[wave - 1][0][lane] = acc[r].ph;
+        L.red[wave - 1][1][lane] = acc[r].fx;
+        L.red[wave - 1][2][lane] = acc[r].fy;
+        L.red[wave - 1][3][lane] = acc[r].fz;
+      }
+      __syncthreads();
+    }
+    if (wave == 0 && valid[r] && split == 0) {
+      if constexpr (W > 1)
+#pragma unroll
+        for (int w = 0; w < W - 1; ++w) {
+          acc[r].ph += L.red[w][0][lane];
+          acc[r].fx += L.red[w][1][lane];
+          acc[r].fy += L.red[w][2][lane];
+          acc[r].fz += L.red[w][3][lane];
+        }
+      p2p_store(J, it[r], acc[r]);
+    }
   }
 }
 
 // SELF: only the leaf's own particles (the within-leaf part of the mutual
 // near field, whose pairs of distinct leaves go through p2p_mutual.hip).
-template <int KP, bool F32, bool SELF>
-__device__ __forceinline__ void p2p_leaf(const JobDev& J, int a, src4* src) {
-  const int lane = threadIdx.x;
-  const double *px = J.px, *py = J.py, *pz = J.pz;
+template <int KP, bool SELF, int W>
+__device__ __forceinline__ void p2p_leaf_f32(const JobDev& J, int a, P2PLds32<W>& L) {
+  const int lane = threadIdx.x & 63;
   const int t0 = wuni(gld(J.leaf_start + a)), nt = wuni(gld(J.leaf_start + a + 1)) - t0;
   const int P = p2p_groups(nt);
-  const int S = 64 / P;
-  const int split = lane / P;
   int nj0 = 0, nj1 = 0;
   if (SELF ? lane == kSelfSlot : lane < 27) {
     const int b = gld(J.near + 27 * a + lane);
@@ -678,113 +975,54 @@ __device__ __forceinline__ void p2p_leaf(const JobDev& J, int a, src4* src) {
       nj1 = gld(J.leaf_start + b + 1);
     }
   }
-  // the source charge as stored (FP32 or FP64), widened when staged
-  typedef typename std::conditional<F32, float, double>::type QT;
-  const QT* qsrc = F32 ? reinterpret_cast<const QT*>(J.q32) : reinterpret_cast<const QT*>(J.qs);
-  for (int tb = 0; tb < nt; tb += 64) {
-    const int ti = tb + (lane % P);
-    const bool valid = ti < nt;
-    const int it = t0 + (valid ? ti : 0);
-    const double xi = gld(px + it), yi = gld(py + it), zi = gld(pz + it);
-    double ph = 0.0, fx = 0.0, fy = 0.0, fz = 0.0;
-    float p32 = 0.f, x32 = 0.f, y32 = 0.f, z32 = 0.f;
-    int sl = -1, jb = 0, j1 = 0;
-    bool have = near_next(nj0, nj1, sl, jb, j1);
-    int cnt = have ? min(64, j1 - jb) : 0;
-    double rx = kFarAway, ry = kFarAway, rz = kFarAway;
-    QT rq = 0;
-    if (lane < cnt) {
-      rx = gld(px + jb + lane);
-      ry = gld(py + jb + lane);
-      rz = gld(pz + jb + lane);
-      rq = gld(qsrc + jb + lane);
-    }
-    while (have) {
-      const int ccnt = cnt, csl = sl;
-      __syncthreads();  // the previous chunk's reads are done
-      src[lane] = src4{rx, ry, rz, F32 ? q_slot(float(rq)) : double(rq)};
-      __syncthreads();
-      have = near_next(nj0, nj1, sl, jb, j1);
-      cnt = have ? min(64, j1 - jb) : 0;
-      rx = ry = rz = kFarAway;
-      rq = 0;
-      if (lane < cnt) {
-        rx = gld(px + jb + lane);
-        ry = gld(py + jb + lane);
-        rz = gld(pz + jb + lane);
-        rq = gld(qsrc + jb + lane);
-      }
-      const int npass = (ccnt + S - 1) / S;
-      if (F32) {
-        if (csl == kSelfSlot)
-          p2p_passes_f32<KP, true>(src, split, S, npass, xi, yi, zi, p32, x32, y32, z32);
-        else
-          p2p_passes_f32<KP, false>(src, split, S, npass, xi, yi, zi, p32, x32, y32, z32);
-        ph += double(p32);
-        fx += double(x32);
-        fy += double(y32);
-        fz += double(z32);
-        p32 = x32 = y32 = z32 = 0.f;
-      } else if (csl == kSelfSlot) {
-        p2p_passes_f64<KP, true>(src, split, S, npass, xi, yi, zi, ph, fx, fy, fz);
-      } else {
-        p2p_passes_f64<KP, false>(src, split, S, npass, xi, yi, zi, ph, fx, fy, fz);
-      }
-    }
-    for (int o = P; o < 64; o <<= 1) {
-      ph += __shfl_xor(ph, o, 64);
-      fx += __shfl_xor(fx, o, 64);
-      fy += __shfl_xor(fy, o, 64);
-      fz += __shfl_xor(fz, o, 64);
-    }
-    if (valid && split == 0) {
-      const int i = t0 + ti;
-      const double qi = gld(J.qs + i);
-      gst(J.phi_n + i, ph);
-      const int64_t i3 = 3 * int64_t(i);
-      gst(J.f_n + i3, qi * fx);
-      gst(J.f_n + i3 + 1, qi * fy);
-      gst(J.f_n + i3 + 2, qi * fz);
-    }
-  }
+  int tb = 0;
+  if constexpr (W > 1)  // (plans of small leaves need the registers for occupancy)
+    for (; nt - tb > 64; tb += 128) p2p_batch_f32<KP, W, 2>(J, L, nj0, nj1, t0, nt, tb, P);
+  for (; tb < nt; tb += 64) p2p_batch_f32<KP, W, 1>(J, L, nj0, nj1, t0, nt, tb, P);
 }
 
-template <bool SELF>
-__global__ __launch_bounds__(64) void p2p_f64_kernel(const JobDev* __restrict__ jobs,
-                                                     const StepTab* __restrict__ tab) {
-  __shared__ src4 src[kSrcSlots];
-  // slots past the 64 staged sources: the padding source, set once (the
-  // first staging's barrier orders it before any read)
-  src[64 + threadIdx.x] = src4{kFarAway, kFarAway, kFarAway, 0.0};
+template <bool SELF, int W>
+__global__ __launch_bounds__(64 * W) void p2p_f32_kernel(const JobDev* __restrict__ jobs,
+                                                         const StepTab* __restrict__ tab) {
+  __shared__ P2PLds32<W> L;
   FOR_ITEMS(tab) {
     const int k = step_find(*tab, it_);
     const JobDev& J = jobs[tab->job[k]];
     const int a = it_ - tab->start[k];
     if (J.kernel == 2)
-      p2p_leaf<2, false, SELF>(J, a, src);
+      p2p_leaf_f32<2, SELF, W>(J, a, L);
     else
-      p2p_leaf<1, false, SELF>(J, a, src);
-    __syncthreads();
+      p2p_leaf_f32<1, SELF, W>(J, a, L);
   }
 }
 
+// Wavefronts a leaf.  Few leaves need many to fill the GPU and to hide each
+// other's latency, large ones share the staging among four; below 16
+// particles a leaf the wavefronts of a group would mostly wait.  Near field
+// with 1, 4, 16 wavefronts, us: FP64, 64 leaves of 16 25, 24, 14; 512 of 39
+// 101, 53, 64; 4,096 of 73 626, 532, 766; 32,768 of 30 722, 857, -; 218,039
+// of 2 420, 1590, -; FP32, 64 of 16 27, 13, 12; 512 of 39 89, 30, 32; 4,586 of
+// 44 202, 134, 266; 4,096 of 15 39, 46, -; 32,768 of 30 537, 572, 1304; 77,828
+// of 128 10715, 10345, 17246.
+int p2p_waves(int64_t n, int64_t nleaf) {
+  if (nleaf <= 256) return 16;
+  if (nleaf <= 1024) return 4;
+  if (n < 16 * nleaf) return 1;
+  return nleaf <= 16384 || n >= 48 * nleaf ? 4 : 1;
+}
+
 template <bool SELF>
-__global__ __launch_bounds__(64) void p2p_f32_kernel(const JobDev* __restrict__ jobs,
-                                                     const StepTab* __restrict__ tab) {
-  __shared__ src4 src[kSrcSlots];
-  // slots past the 64 staged sources: the padding source, set once (the
-  // first staging's barrier orders it before any read)
-  src[64 + threadIdx.x] = src4{kFarAway, kFarAway, kFarAway, 0.0};
-  FOR_ITEMS(tab) {
-    const int k = step_find(*tab, it_);
-    const JobDev& J = jobs[tab->job[k]];
-    const int a = it_ - tab->start[k];
-    if (J.kernel == 2)
-      p2p_leaf<2, true, SELF>(J, a, src);
-    else
-      p2p_leaf<1, true, SELF>(J, a, src);
-    __syncthreads();
+static void launch_p2p(bool fp32, int waves, const JobDev* jobs, const StepTab* tab, unsigned grid,
+                hipStream_t s) {
+#define P2P_CALL(W)                                                           \
+  if (fp32) p2p_f32_kernel<SELF, W><<<grid, 64 * W, 0, s>>>(jobs, tab);       \
+  else p2p_f64_kernel<SELF, W><<<grid, 64 * W, 0, s>>>(jobs, tab)
+  switch (waves) {
+    case 1: P2P_CALL(1); break;
+    case 4: P2P_CALL(4); break;
+    default: P2P_CALL(16); break;
   }
+#undef P2P_CALL
 }
 
 // ------------------------------------------------------------- M2L parts
@@ -974,12 +1212,10 @@ void launch_step(StepKind kind, int L, bool fp32, const JobDev* jobs, const Step
 #undef L2P_CALL
       break;
     case kStepP2P:
-      if (fp32) p2p_f32_kernel<false><<<g, 64, 0, s>>>(jobs, tab);
-      else p2p_f64_kernel<false><<<g, 64, 0, s>>>(jobs, tab);
+      launch_p2p<false>(fp32, nt, jobs, tab, g, s);
       break;
     case kStepP2PSelf:
-      if (fp32) p2p_f32_kernel<true><<<g, 64, 0, s>>>(jobs, tab);
-      else p2p_f64_kernel<true><<<g, 64, 0, s>>>(jobs, tab);
+      launch_p2p<true>(fp32, nt, jobs, tab, g, s);
       break;
     case kStepCombine:
       combine_kernel<<<g, kChunk, 0, s>>>(jobs, tab, calls);
@@ -1035,10 +1271,12 @@ void evaluate(fmm_plan_s* p, const double* q, double* phi, double* f, double* ph
   auto near_field = [&](hipStream_t st) {
     Timed t(FMM_TIME_P2P, st);
     if (p->near_mode == FMM_NEAR_MUTUAL) {
-      launch_step(kStepP2PSelf, L, mixed, J, p->tab_d + kTabLeaf, nullptr, int(p->nleaf), st);
+      launch_step(kStepP2PSelf, L, mixed, J, p->tab_d + kTabLeaf, nullptr, int(p->nleaf), st, 0,
+                  p2p_waves(p->n, p->nleaf));
       launch_p2p_mutual(p, mixed, st);
     } else {
-      launch_step(kStepP2P, L, mixed, J, p->tab_d + kTabLeaf, nullptr, int(p->nleaf), st);
+      launch_step(kStepP2P, L, mixed, J, p->tab_d + kTabLeaf, nullptr, int(p->nleaf), st, 0,
+                  p2p_waves(p->n, p->nleaf));
     }
   };
   auto fork_near = [&]() {

@@ -142,8 +142,14 @@ enum StepKind { kStepGather, kStepP2M, kStepM2M, kStepCast, kStepM2L, kStepL2L, 
                 kStepP2PSelf };
 // gskip: the compressed M2L skips the 16-target groups without a source at
 // an offset (plans whose tiles have many, fmm_info.m2l_group_skip).
+// xs, nt: the compressed M2L's LDS row stride and N-tiles per item; nt: the
+// near field's wavefronts per leaf (p2p_waves).
 void launch_step(StepKind kind, int order, bool fp32, const JobDev* jobs, const StepTab* tab,
                  const CallDev* calls, int grid, hipStream_t s, int xs = 0, int nt = 0,
                  bool gskip = false);
+
+// Wavefronts per target leaf of the near field, by the plan's particles and
+// leaves.
+int p2p_waves(int64_t n, int64_t nleaf);
 
 }  // namespace fmm

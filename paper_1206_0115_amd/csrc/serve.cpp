@@ -95,7 +95,7 @@ struct Launch {
   int order;
   bool fp32;
   int xs;  // LDS row stride of the compressed M2L
-  int nt;  // ... and its N-tiles per item
+  int nt;  // ... and its N-tiles per item; the near field's wavefronts per leaf
   bool gskip;  // compressed M2L: skip the 16-target groups without a source
 };
 
@@ -347,13 +347,15 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
       t.start[t.njobs] = tot;
       tot += it;
       xs = std::max(xs, reqs[j]->plan->job_h.xs);
-      nt = jobs[j].svd_nt;  // the same for every job of a compressed M2L launch
+      // the same for every job of a compressed M2L or near-field launch
+      nt = kind == kStepP2P ? p2p_waves(reqs[j]->plan->n, reqs[j]->plan->nleaf) : jobs[j].svd_nt;
       ++t.njobs;
     }
     t.start[t.njobs] = tot;
     if (t.njobs == 0) return;
     if (seq.size() + 1 >= size_t(kMaxSteps)) throw FmmError{FMM_ERR_HIP, "batch step table full"};
-    if (kind != kStepM2LSvd) xs = nt = 0;
+    if (kind != kStepM2LSvd) xs = 0;
+    if (kind != kStepM2LSvd && kind != kStepP2P) nt = 0;
     seq.push_back({kind, order, fp32, xs, nt, gskip});
     key += std::to_string(int(kind)) + ":" + std::to_string(order) + (fp32 ? "f" : "d") + ":" +
            std::to_string(xs) + ":" + std::to_string(nt) + (gskip ? "g" : "") + ";";
@@ -436,8 +438,12 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
           },
           [](Request* r) { return int(r->plan->nleaf); }, lvl0);
   for (int f32 = 0; f32 < 2; ++f32)
-    add(kStepP2P, 0, f32 != 0, [&](Request* r) { return mixed(r) == (f32 != 0); },
-        [](Request* r) { return int(r->plan->nleaf); }, lvl0);
+    for (int waves : {1, 4, 16})
+      add(kStepP2P, 0, f32 != 0,
+          [&](Request* r) {
+            return mixed(r) == (f32 != 0) && p2p_waves(r->plan->n, r->plan->nleaf) == waves;
+          },
+          [](Request* r) { return int(r->plan->nleaf); }, lvl0);
   add(kStepCombine, 0, false, all_, chunks, lvl0);
 
   // the graph for this launch sequence and buffer, captured on first use
