@@ -199,18 +199,24 @@ __device__ __host__ inline double root_side(const double* box) {
   return L == 0.0 ? 1.0 : L;
 }
 
-// kKeyItems particles a workgroup.  Every workgroup reduces the nb partial
-// boxes itself (at most 24 KiB, from L2), which saves a launch; the first
-// also writes the result to the head and clears the statistics.
-constexpr int kKeyItems = 2048;
-
+// ITEMS particles a workgroup.  Every workgroup reduces the nb partial boxes
+// itself (at most 24 KiB, from L2), which saves a launch; the first also
+// writes the result to the head and clears the statistics.  All of them set
+// the tslots entries of the lookup tables to -1.  HIST: a workgroup is a tile
+// of the sort and also counts its first digit.
+template <int ITEMS, bool HIST>
 __global__ __launch_bounds__(256) void keys_kernel(
     const double* __restrict__ pos, int64_t n, const double* __restrict__ part,
     const int* __restrict__ bad, int nb, int bits, uint64_t* __restrict__ keys,
     int* __restrict__ idx, PlanHead* __restrict__ head,
-    unsigned long long* __restrict__ stats) {
+    unsigned long long* __restrict__ stats, int* __restrict__ tables, int64_t tslots, int mask,
+    int* __restrict__ hist) {
   __shared__ double red[6][4];
+  __shared__ int digit[256];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  digit[t] = 0;
+  for (int64_t i = int64_t(blockIdx.x) * 256 + t; i < tslots; i += int64_t(gridDim.x) * 256)
+    tables[i] = -1;
   double v[6];
   for (int d = 0; d < 6; ++d) v[d] = d < 3 ? INFINITY : -INFINITY;
   int nonfinite = 0;
@@ -244,8 +250,8 @@ __global__ __launch_bounds__(256) void keys_kernel(
   const double side = double(int64_t(1) << bits);
   const int64_t kmax = (int64_t(1) << bits) - 1;
   const double L = root_side(box);
-  const int64_t base = int64_t(blockIdx.x) * kKeyItems;
-  for (int e = t; e < kKeyItems; e += 256) {
+  const int64_t base = int64_t(blockIdx.x) * ITEMS;
+  for (int e = t; e < ITEMS; e += 256) {
     const int64_t i = base + e;
     if (i >= n) break;
     uint32_t k3[3];
@@ -255,8 +261,14 @@ __global__ __launch_bounds__(256) void keys_kernel(
       k = k > kmax ? kmax : (k < 0 ? 0 : k);
       k3[d] = uint32_t(k);
     }
-    keys[i] = morton3(k3[0], k3[1], k3[2], bits);
+    const uint64_t key = morton3(k3[0], k3[1], k3[2], bits);
+    keys[i] = key;
     idx[i] = int(i);
+    if (HIST) atomicAdd(&digit[int(key) & mask], 1);
+  }
+  if (HIST) {
+    __syncthreads();
+    hist[int64_t(blockIdx.x) * 256 + t] = digit[t];
   }
 }
 
@@ -268,6 +280,11 @@ __global__ __launch_bounds__(256) void keys_kernel(
 // order with wavefront ballots.
 // A tile is 256 IT particles, IT = 4 up to kRsSmall of them (a tile is a
 // chain of IT ranked steps: 1,000 particles 11 -> 4.6 us a scatter) and 16 above.
+// Up to kRsSmall, where launches and latency are what a pass takes, the
+// histograms are tile-major, every scatter workgroup adds up the tiles'
+// counts itself (at most 256 KiB, from L2; 60,000 particles: 4 us, a scan by
+// one workgroup 16), and the first pass's counts come with the keys (steps of
+// 1,000, 20,000, 60,000 particles 245 -> 222, 380 -> 363, 1323 -> 1288 us).
 constexpr int kRsThreads = 256;
 constexpr int64_t kRsSmall = 262144;
 
@@ -284,7 +301,8 @@ __global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(
     if (i < n) atomicAdd(&h[int((keys[i] >> shift) & uint64_t(mask))], 1);
   }
   __syncthreads();
-  hist[int64_t(threadIdx.x) * ntiles + blockIdx.x] = h[threadIdx.x];
+  hist[IT == 4 ? int64_t(blockIdx.x) * 256 + threadIdx.x
+               : int64_t(threadIdx.x) * ntiles + blockIdx.x] = h[threadIdx.x];
 }
 
 template <int IT>
@@ -295,8 +313,29 @@ __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
   __shared__ int base_d[256];
   __shared__ int wcnt[kRsThreads / 64][256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  base_d[tid] = offs[int64_t(tid) * ntiles + blockIdx.x];
   const uint64_t lt = (uint64_t(1) << lane) - 1;
+  if (IT == 4) {
+    // smaller digits of all tiles, and this digit of the earlier ones
+    __shared__ int wave_sum[kRsThreads / 64];
+    int before = 0, incl = 0;
+#pragma unroll 16
+    for (int b = 0; b < ntiles; ++b) {
+      const int c = offs[b * 256 + tid];
+      incl += c;
+      before += b < int(blockIdx.x) ? c : 0;
+    }
+    before -= incl;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) incl += wave_sum[w];
+    base_d[tid] = before + incl;
+  } else {
+    base_d[tid] = offs[int64_t(tid) * ntiles + blockIdx.x];
+  }
   const int64_t tbase = int64_t(blockIdx.x) * (kRsThreads * IT);
   for (int it = 0; it < IT; ++it) {
     for (int k = lane; k < 256; k += 64) wcnt[wave][k] = 0;
@@ -339,19 +378,19 @@ static int radix_passes(int64_t n, int bits) { return n <= 1 ? 0 : (bits + 7) / 
 
 // Sorts n pairs by the low `bits` bits of the key, from (k, v) through
 // (k2, v2) and back: after an odd number of passes the result is in the
-// second pair of buffers.
+// second pair of buffers.  hist: 256 counts a tile (IT == 4: the first pass's).
 template <int IT>
 static void radix_sort(uint64_t* k, int* v, uint64_t* k2, int* v2, int64_t n, int bits,
-                       hipStream_t s, std::vector<void*>& tmp) {
+                       hipStream_t s, std::vector<void*>& tmp, int* hist) {
   const int ntiles = ceil_div(n, kRsThreads * IT);
-  int* hist = static_cast<int*>(dev_alloc(sizeof(int) * 256 * size_t(ntiles)));
-  tmp.push_back(hist);
   for (int p = 0; p < radix_passes(n, bits); ++p) {
     const int shift = 8 * p, db = std::min(8, bits - shift);
     const int mask = (1 << db) - 1;
-    radix_hist_kernel<IT><<<ntiles, kRsThreads, 0, s>>>(k, n, shift, mask, ntiles, hist);
-    FMM_HIP_CHECK(hipGetLastError());
-    exclusive_scan<int>(hist, hist, int64_t(256) * ntiles, s, tmp);
+    if (IT != 4 || p > 0) {
+      radix_hist_kernel<IT><<<ntiles, kRsThreads, 0, s>>>(k, n, shift, mask, ntiles, hist);
+      FMM_HIP_CHECK(hipGetLastError());
+    }
+    if (IT != 4) exclusive_scan<int>(hist, hist, int64_t(256) * ntiles, s, tmp);
     radix_scatter_kernel<IT><<<ntiles, kRsThreads, 0, s>>>(k, v, k2, v2, n, shift, mask,
                                                            ntiles, hist);
     FMM_HIP_CHECK(hipGetLastError());
@@ -564,14 +603,14 @@ __global__ __launch_bounds__(256) void near_kernel(LevelDev leaves,
 }
 
 // ------------------------------------------------------------ M2L tiles
-// One workgroup of eight wavefronts per tile.  Lane j of every wavefront owns
-// target j; wavefront w looks up the source cells of the slots w, w+8, ...
+// One workgroup of sixteen wavefronts per tile.  Lane j of every wavefront owns
+// target j; wavefront w looks up the source cells of the slots w, w+16, ...
 // (zero row if absent) and marks the slots with at least one source; then
 // the marked slots are listed in slot order, each with the mask of its
 // 16-target groups that have a source (bit g: targets 16g .. 16g+15), and
 // the tile's groups of targets without a source at an active slot are
 // counted.
-constexpr int kTileThreads = 512;
+constexpr int kTileThreads = 1024;
 
 __global__ __launch_bounds__(kTileThreads) void tile_src_kernel(
     const M2LTile* __restrict__ tiles, const int* __restrict__ tgt,
@@ -587,32 +626,39 @@ __global__ __launch_bounds__(kTileThreads) void tile_src_kernel(
   const int tile = blockIdx.x, j = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const M2LTile T = tiles[tile];
   const LevelDev L = levels[T.level];
+  const int first = int(lev_off[T.level]);
+  constexpr int kStride = kTileThreads / 64, kBatch = (kSlots + kStride - 1) / kStride;
+  // a wavefront's offsets are read beside its targets' keys, and all its
+  // lookups are issued before any is used: a chain of five reads in all, which
+  // bounds small plans (18 -> 12 us; eight wavefronts had three batches)
+  int off[kBatch][3];
+#pragma unroll
+  for (int u = 0; u < kBatch; ++u) {
+    const signed char* t = slot_t + (T.parity * kSlots + min(wave + u * kStride, kSlots - 1)) * 3;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) off[u][d] = t[d];
+  }
   int c[3] = {0, 0, 0};
   const bool have = j < T.count;
   if (have) {
-    const int local = tgt[T.first + j] - int(lev_off[T.level]);
+    const int local = tgt[T.first + j] - first;
     demorton3(L.keys[local], L.bits, c);
   }
   int* out = tile_src + int64_t(tile) * kSlots * kTileN;
-  // the lookups of 8 slots are issued before any is used (independent loads
-  // in flight instead of one table access at a time)
-  constexpr int kStride = kTileThreads / 64, kBatch = 8;
-  for (int s0 = wave; s0 < kSlots; s0 += kStride * kBatch) {
+  {
+    const int s0 = wave;
     int bs[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int s = s0 + u * kStride;
       bs[u] = -1;
-      if (have && s < kSlots) {
-        const signed char* t = slot_t + (T.parity * kSlots + s) * 3;
-        bs[u] = level_find_xyz(L, c[0] + t[0], c[1] + t[1], c[2] + t[2]);
-      }
+      if (have && s0 + u * kStride < kSlots)
+        bs[u] = level_find_xyz(L, c[0] + off[u][0], c[1] + off[u][1], c[2] + off[u][2]);
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int s = s0 + u * kStride;
       if (s >= kSlots) continue;  // the same for the whole wavefront
-      out[s * kTileN + j] = bs[u] >= 0 ? bs[u] + int(lev_off[T.level]) : zero_row;
+      out[s * kTileN + j] = bs[u] >= 0 ? bs[u] + first : zero_row;
       const uint64_t m = __ballot(bs[u] >= 0);
       if (j == 0) {
         npair[s] = __popcll(m);
@@ -712,11 +758,33 @@ void build_plan(fmm_plan_s* p, const double* pos, hipStream_t s) {
   const bool odd = radix_passes(n, 3 * bits) % 2 != 0;
   uint64_t *k1 = odd ? kt : p->keys, *k2 = odd ? p->keys : kt;
   int *v1 = odd ? vt : p->perm, *v2 = odd ? p->perm : vt;
-  keys_kernel<<<grid_for(n, kKeyItems), 256, 0, s>>>(pos, n, part, bad, nb, bits, k1, v1, head,
-                                                     stats);
-  FMM_HIP_CHECK(hipGetLastError());
-  if (n <= kRsSmall) radix_sort<4>(k1, v1, k2, v2, n, 3 * bits, s, tmp);
-  else radix_sort<16>(k1, v1, k2, v2, n, 3 * bits, s, tmp);
+  // dense lookup tables for levels with at most 2^24 key slots, one block,
+  // all -1
+  int64_t tslots = 0;
+  for (int l = 0; l < h && 3 * l <= 24; ++l) tslots += int64_t(1) << (3 * l);
+  int* tables = static_cast<int*>(p->alloc(sizeof(int) * tslots));
+  const bool small = n <= kRsSmall;
+  const int items = small ? 4 * kRsThreads : 2048;
+  const unsigned kb = grid_for(n, items);
+  int64_t fill = tslots;  // by the keys' workgroups where they are enough
+  if (tslots > int64_t(64) * 256 * kb) {
+    FMM_HIP_CHECK(hipMemsetAsync(tables, 0xff, sizeof(int) * tslots, s));
+    fill = 0;
+  }
+  int* hist = static_cast<int*>(
+      talloc(sizeof(int) * 256 * size_t(ceil_div(n, kRsThreads * (small ? 4 : 16)))));
+  if (small) {
+    keys_kernel<4 * kRsThreads, true><<<kb, 256, 0, s>>>(
+        pos, n, part, bad, nb, bits, k1, v1, head, stats, tables, fill,
+        (1 << std::min(8, 3 * bits)) - 1, hist);
+    FMM_HIP_CHECK(hipGetLastError());
+    radix_sort<4>(k1, v1, k2, v2, n, 3 * bits, s, tmp, hist);
+  } else {
+    keys_kernel<2048, false><<<kb, 256, 0, s>>>(pos, n, part, bad, nb, bits, k1, v1, head,
+                                                stats, tables, fill, 0, nullptr);
+    FMM_HIP_CHECK(hipGetLastError());
+    radix_sort<16>(k1, v1, k2, v2, n, 3 * bits, s, tmp, hist);
+  }
 
   // --- sorted positions, cell counts of every level and child parity ---
   p->px = static_cast<double*>(p->alloc(sizeof(double) * n));
@@ -730,11 +798,6 @@ void build_plan(fmm_plan_s* p, const double* pos, hipStream_t s) {
   FMM_HIP_CHECK(hipGetLastError());
   cells_scan_kernel<<<8 * h, kScanThreads, 0, s>>>(count, cb, head);
   FMM_HIP_CHECK(hipGetLastError());
-  // dense lookup tables for levels with at most 2^24 key slots, one block
-  int64_t tslots = 0;
-  for (int l = 0; l < h && 3 * l <= 24; ++l) tslots += int64_t(1) << (3 * l);
-  int* tables = static_cast<int*>(p->alloc(sizeof(int) * tslots));
-  FMM_HIP_CHECK(hipMemsetAsync(tables, 0xff, sizeof(int) * tslots, s));  // all -1
 
   // --- the read-back that sizes the plan ---
   // pinned staging of the calling thread: the head, later the statistics
