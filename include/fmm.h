@@ -186,10 +186,12 @@ int fmm_plan_set_precision(fmm_plan_t plan, int mode);
  *   FMM_SCHEDULE_FORKED  (default) P2P on a stream owned by the plan (a
  *                        non-blocking stream of default priority, reused
  *                        from plans released earlier on the device), forked
- *                        from the caller's stream after the M2L launch (so
- *                        it runs beside L2L and L2P, which leave the GPU
- *                        partly idle) and joined back before the final sum;
- *                        the far chain stays on the caller's stream
+ *                        from the caller's stream after the M2L (so it runs
+ *                        beside L2L and L2P, which leave the GPU partly
+ *                        idle), or before it where the M2L itself leaves the
+ *                        GPU partly idle (small plans), and joined back
+ *                        before the final sum; the far chain stays on the
+ *                        caller's stream
  *   FMM_SCHEDULE_PIPELINED  as FMM_SCHEDULE_FORKED, and the M2L of the leaf
  *                        level (which needs only the leaf multipoles) also
  *                        runs on the plan's stream, right after P2M and

@@ -152,6 +152,17 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
     parts = dense_parts(int64_t(p->ntiles) * J.nmb, op->mt, fp32, part_bytes, cus);
     if (p->dense_parts_max > 0) parts = std::min(parts, p->dense_parts_max);
   }
+  // The forked schedule's near field starts beside the M2L where that is one
+  // round of workgroups (dense: of unsplit tiles) and leaves CUs idle, after
+  // it elsewhere, where both would only take turns: evaluations, after and
+  // beside, 20,000 FP64 order 5 202 and 189 us, 200,003 on a sphere 1/r^2
+  // compressed mixed 481 and 382, 300,000 dense mixed order 7 3226 and 2923,
+  // compressed order 9 2234 and 2108; of more rounds, 300,007 compressed FP64
+  // order 8 2075 and 2399, 1M order 5 2380 and 2500, mixed order 7 4425 and
+  // 4490.
+  p->near_early =
+      p->svd ? int64_t(p->ntiles) * J.nmb * parts <= m2l_svd_slots(op->mt, fp32, cus)
+             : int64_t(p->ntiles) * J.nmb <= 2 * int64_t(cus);
   const size_t want = size_t(parts - 1) * part_bytes;
   bool split_oom = false;  // reported once the job below is consistent
   if (p->locx_bytes != want) {

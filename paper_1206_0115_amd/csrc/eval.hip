@@ -1224,15 +1224,6 @@ void launch_step(StepKind kind, int L, bool fp32, const JobDev* jobs, const Step
   FMM_HIP_CHECK(hipGetLastError());
 }
 
-// Where the forked schedule starts the near field: 0 = just before the M2L
-// launch, 1 = just after it, 2 = after the L2L levels, 3 = before the last
-// L2L level.  Measured (1M cube, order 7, compressed mixed mode, evaluate
-// only): after 6.84 ms, serial 6.90 ms, before 6.98 ms; later, with the
-// faster M2L: 1 5.24 ms, 2 5.23 ms, 3 5.21 ms (within the spread).
-#ifndef FMM_FORK_AFTER_M2L
-#define FMM_FORK_AFTER_M2L 1
-#endif
-
 namespace {
 // the step's timing events, if set, around a launch on stream s
 struct Timed {
@@ -1251,10 +1242,11 @@ struct Timed {
 
 // One plan: the step tables were built at plan time; every launch has one
 // block per item.  In the forked schedule the near field runs on the plan's
-// side stream, forked after the M2L launch and joined before the combine, so
-// it fills the GPU beside the L2L levels and L2P, which do not.  (Forked
-// earlier, its 64-thread blocks flood the GPU and delay P2M and M2M, and it
-// cannot share CUs with M2L, whose wavefronts hold the register files.)
+// side stream and is joined before the combine.  It starts after the M2L and
+// fills the GPU beside the L2L levels and L2P, which do not; or, where the
+// M2L is a single round of workgroups and leaves CUs or latency to fill
+// (near_early), before it.  (Forked earlier still, its blocks flood the GPU and
+// delay P2M and M2M.)
 void evaluate(fmm_plan_s* p, const double* q, double* phi, double* f, double* phi_n,
               double* f_n, double* phi_f, double* f_f, hipStream_t s) {
   const int L = p->order, h = p->height;
@@ -1325,7 +1317,8 @@ void evaluate(fmm_plan_s* p, const double* q, double* phi, double* f, double* ph
     if (mixed && p->tab_h[kTabCast].start[1] > 0)
       launch_step(kStepCast, L, true, J, p->tab_d + kTabCast, nullptr,
                   p->tab_h[kTabCast].start[1], s);
-    if (forked && !FMM_FORK_AFTER_M2L) fork_near();
+    const bool early = forked && !pipelined && p->near_early;
+    if (early) fork_near();
     if (pipelined) {
       if (p->ntiles > 0) {
         m2l_launch(kTabM2LCoarse, s);
@@ -1339,16 +1332,14 @@ void evaluate(fmm_plan_s* p, const double* q, double* phi, double* f, double* ph
       }
       loc_sum();
     }
-    if (forked && FMM_FORK_AFTER_M2L == 1) fork_near();
+    if (forked && !early) fork_near();
     {
       Timed t(FMM_TIME_L2L, s);
       for (int st = 0; st + 4 <= h; ++st) {
-        if (forked && FMM_FORK_AFTER_M2L == 3 && st + 4 == h) fork_near();
         launch_step(kStepL2L, L, false, J, p->tab_d + kTabL2L + st, nullptr,
                     p->tab_h[kTabL2L + st].start[1], s);
       }
     }
-    if (forked && (FMM_FORK_AFTER_M2L == 2 || (FMM_FORK_AFTER_M2L == 3 && h < 4))) fork_near();
     {
       Timed t(FMM_TIME_L2P, s);
       launch_step(p->job_h.l2p_sparse ? kStepL2PSparse : kStepL2P, L, false, J,

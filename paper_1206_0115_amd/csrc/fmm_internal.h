@@ -170,6 +170,8 @@ double m2l_item_flops(int mt);  // ... and the flops of one item at one far offs
 // multipoles and of the S V^T factors, so those are allocated that much longer)
 constexpr int kSvdPadChunks = 48;
 int m2l_svd_nt(int order, bool fp32, int64_t tile_parts, int cus);
+// workgroups of it that the device holds at once
+int64_t m2l_svd_slots(int mt, bool fp32, int cus);
 int m2l_svd_nmb(int mt, bool fp32, int nt);
 int m2l_svd_xs(int rmax_pad, bool fp32);
 size_t m2l_svd_lds_need(int order, bool fp32, int xs);
@@ -222,6 +224,7 @@ struct fmm_plan_s {
   int64_t active_slots = 0;        // sum over tiles of slots with a source
   int64_t m2l_groups = 0;          // 16-target groups at active slots
   int64_t m2l_groups_empty = 0;    // ... of them without a source
+  bool near_early = false;         // the forked near field starts beside the M2L
   bool m2l_gskip = false;          // the compressed M2L skips the empty groups
   int64_t pairs_by_kid[fmm::kOffsets] = {0};  // far pairs per packed operator
 

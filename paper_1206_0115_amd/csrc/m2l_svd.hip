@@ -580,10 +580,14 @@ static int svd_widest(int mt, bool fp32) {
 // fewest rounds in those units win (20,000 particles, height 4, order
 // 7: 64, 32, 16 columns 379, 238, 157 us; 60,000, height 5: 515, 608, 743).
 // Every column's sums are the same in each shape.
+int64_t m2l_svd_slots(int mt, bool fp32, int cus) {
+  return int64_t(mt <= (fp32 ? 16 : 8) ? 2 : 1) * std::max(1, cus);
+}
+
 int m2l_svd_nt(int order, bool fp32, int64_t tile_parts, int cus) {
   const int mt = svd_kc(order);
   const int widest = svd_widest(mt, fp32);
-  const int64_t slots = int64_t(mt <= (fp32 ? 16 : 8) ? 2 : 1) * std::max(1, cus);
+  const int64_t slots = m2l_svd_slots(mt, fp32, cus);
   int best = widest;
   double best_cost = 0.0, item = 1.0;
   for (int nt = widest; nt >= 1; nt /= 2, item *= mt <= 16 ? 0.8 : 0.62) {
