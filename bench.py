@@ -55,7 +55,7 @@ def rel(a, b):
 
 def m2l_source_hash():
     h = hashlib.sha256()
-    for f in ("m2l.hip", "eval.hip"):
+    for f in ("m2l.hip", "m2l_dev.h", "m2l_svd.hip", "eval.hip"):
         h.update(open(os.path.join(ROOT, "paper_1206_0115_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -296,7 +296,7 @@ def ingest_traffic(args):
         # one M2L launch per mode (the kernel the roofline times; the row
         # pass after it is a kernel of its own)
         m2l = [v for _, k, v in rows
-               if "m2l_kernel" in k or "m2l_svd_kernel" in k or "m2l_svd_ws_kernel" in k]
+               if "m2l_kernel" in k or "m2l_svd_kernel" in k]
         return COPY_BYTES / (cal * 1024.0), cal, m2l
 
     sf, calf, mf = scale_and_m2l(fetch)
@@ -797,7 +797,7 @@ def main():
     achieved = flops / m2l_s / 1e12
     peak = PEAK_TFLOPS["mixed" if precision.startswith("mixed") else "fp64"]
     roof = {"bound": "mfma",
-            "kernel": "m2l_svd_ws_kernel" if precision.endswith("svd") else "m2l_kernel",
+            "kernel": "m2l_svd_kernel" if precision.endswith("svd") else "m2l_kernel",
             "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
             "frac": round(achieved / peak, 4), "traffic": load_traffic(name, precision),
             "flops_per_launch": flops, "far_pairs": int(inf.far_pairs),

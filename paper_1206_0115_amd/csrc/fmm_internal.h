@@ -154,7 +154,7 @@ enum {
   kTabM2L = 2,   // one item per (M2L tile, M-block)
   kTabM2M = 3,   // + step s: parents at level h-2-s
   kTabL2L = 3 + kMaxHeight,  // + step s: children at level 3+s
-  kTabLocSum = 3 + 2 * kMaxHeight,  // M2L parts: one item per row of levels >= 2
+  kTabLocSum = 3 + 2 * kMaxHeight,  // M2L parts: kLocSumItem elements of levels >= 2 an item
   kTabM2LLeaf = 4 + 2 * kMaxHeight,    // kTabM2L's items of the leaf-level tiles
   kTabM2LCoarse = 5 + 2 * kMaxHeight,  // kTabM2L's items of the coarser levels
   kTabCount = 6 + 2 * kMaxHeight

@@ -21,8 +21,7 @@
 // they describe, so each rounding error is relative to its own coefficient;
 // summed as node values, the rounding errors are alike at every node and the
 // force, the gradient of the interpolant (L2P), multiplies their
-// high-degree part by up to l^2.  The loc-sum pass turns the coefficients
-// back into node values in FP64 (T3^-1: T_n(xb_m) along each dimension).
+// high-degree part by up to l^2.  The downward pass keeps the coefficients.
 // Mirroring a dimension maps T_n to (-1)^n T_n, so the signed permutations
 // act on coefficient rows as permutations with the sign (-1)^(sum of the
 // mirrored dimensions' degrees).
