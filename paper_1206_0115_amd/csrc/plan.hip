@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "device_util.h"
@@ -202,9 +203,9 @@ __device__ __host__ inline double root_side(const double* box) {
 // ITEMS particles a workgroup.  Every workgroup reduces the nb partial boxes
 // itself (at most 24 KiB, from L2), which saves a launch; the first also
 // writes the result to the head and clears the statistics.  All of them set
-// the tslots entries of the lookup tables to -1.  HIST: a workgroup is a tile
-// of the sort and also counts its first digit.
-template <int ITEMS, bool HIST>
+// the tslots entries of the lookup tables to -1.  D > 0: a workgroup is a tile
+// of the sort and also counts its first digit, of D values.
+template <int ITEMS, int D>
 __global__ __launch_bounds__(256) void keys_kernel(
     const double* __restrict__ pos, int64_t n, const double* __restrict__ part,
     const int* __restrict__ bad, int nb, int bits, uint64_t* __restrict__ keys,
@@ -212,9 +213,9 @@ __global__ __launch_bounds__(256) void keys_kernel(
     unsigned long long* __restrict__ stats, int* __restrict__ tables, int64_t tslots, int mask,
     int* __restrict__ hist) {
   __shared__ double red[6][4];
-  __shared__ int digit[256];
+  __shared__ int digit[D > 0 ? D : 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  digit[t] = 0;
+  for (int d = t; d < D; d += 256) digit[d] = 0;
   for (int64_t i = int64_t(blockIdx.x) * 256 + t; i < tslots; i += int64_t(gridDim.x) * 256)
     tables[i] = -1;
   double v[6];
@@ -264,16 +265,16 @@ __global__ __launch_bounds__(256) void keys_kernel(
     const uint64_t key = morton3(k3[0], k3[1], k3[2], bits);
     keys[i] = key;
     idx[i] = int(i);
-    if (HIST) atomicAdd(&digit[int(key) & mask], 1);
+    if (D > 0) atomicAdd(&digit[int(key) & mask], 1);
   }
-  if (HIST) {
+  if (D > 0) {
     __syncthreads();
-    hist[int64_t(blockIdx.x) * 256 + t] = digit[t];
+    for (int d = t; d < D; d += 256) hist[int64_t(blockIdx.x) * D + d] = digit[d];
   }
 }
 
 // ------------------------------------------------------- stable radix sort
-// LSD radix sort of (key, value) pairs, 8-bit digits.  Stability (equal keys
+// LSD radix sort of (key, value) pairs.  Stability (equal keys
 // keep input order) is what makes the permutation unique: ties are ordered by
 // input index.  Per pass: tile histograms, one exclusive scan over the
 // digit-major histogram, then a scatter that ranks equal digits in input
@@ -282,18 +283,21 @@ __global__ __launch_bounds__(256) void keys_kernel(
 // chain of IT ranked steps: 1,000 particles 11 -> 4.6 us a scatter) and 16 above.
 // Up to kRsSmall, where launches and latency are what a pass takes, the
 // histograms are tile-major, every scatter workgroup adds up the tiles'
-// counts itself (at most 256 KiB, from L2; 60,000 particles: 4 us, a scan by
+// counts itself (at most 512 KiB, from L2; 60,000 particles: 4 us, a scan by
 // one workgroup 16), and the first pass's counts come with the keys (steps of
 // 1,000, 20,000, 60,000 particles 245 -> 222, 380 -> 363, 1323 -> 1288 us).
+// There the digits have 9 bits where that saves a pass, i.e. in trees of height
+// 4 (plan of 20,000 particles 125 -> 109 us) and 7 (60,000: 189 -> 180), and 8
+// elsewhere (height 5, 60,000 particles: 135 us, and 139 in 9).
 constexpr int kRsThreads = 256;
 constexpr int64_t kRsSmall = 262144;
 
-template <int IT>
+template <int IT, int D>
 __global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(
     const uint64_t* __restrict__ keys, int64_t n, int shift, int mask,
     int ntiles, int* __restrict__ hist) {
-  __shared__ int h[256];
-  h[threadIdx.x] = 0;
+  __shared__ int h[D];
+  for (int d = threadIdx.x; d < D; d += kRsThreads) h[d] = 0;
   __syncthreads();
   const int64_t base = int64_t(blockIdx.x) * (kRsThreads * IT);
   for (int it = 0; it < IT; ++it) {
@@ -301,30 +305,37 @@ __global__ __launch_bounds__(kRsThreads) void radix_hist_kernel(
     if (i < n) atomicAdd(&h[int((keys[i] >> shift) & uint64_t(mask))], 1);
   }
   __syncthreads();
-  hist[IT == 4 ? int64_t(blockIdx.x) * 256 + threadIdx.x
-               : int64_t(threadIdx.x) * ntiles + blockIdx.x] = h[threadIdx.x];
+  for (int d = threadIdx.x; d < D; d += kRsThreads)
+    hist[IT == 4 ? int64_t(blockIdx.x) * D + d : int64_t(d) * ntiles + blockIdx.x] = h[d];
 }
 
-template <int IT>
+template <int IT, int D>
 __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
     const uint64_t* __restrict__ kin, const int* __restrict__ vin,
     uint64_t* __restrict__ kout, int* __restrict__ vout, int64_t n, int shift,
     int mask, int ntiles, const int* __restrict__ offs) {
-  __shared__ int base_d[256];
-  __shared__ int wcnt[kRsThreads / 64][256];
+  __shared__ int base_d[D];
+  __shared__ int wcnt[kRsThreads / 64][D];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t lt = (uint64_t(1) << lane) - 1;
   if (IT == 4) {
-    // smaller digits of all tiles, and this digit of the earlier ones
+    // smaller digits of all tiles, and this digit of the earlier ones; E
+    // adjacent digits a thread
+    constexpr int E = D / kRsThreads;
     __shared__ int wave_sum[kRsThreads / 64];
-    int before = 0, incl = 0;
+    int before[E], total[E], incl = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) before[e] = total[e] = 0;
 #pragma unroll 16
-    for (int b = 0; b < ntiles; ++b) {
-      const int c = offs[b * 256 + tid];
-      incl += c;
-      before += b < int(blockIdx.x) ? c : 0;
-    }
-    before -= incl;
+    for (int b = 0; b < ntiles; ++b)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int c = offs[int64_t(b) * D + E * tid + e];
+        total[e] += c;
+        before[e] += b < int(blockIdx.x) ? c : 0;
+      }
+#pragma unroll
+    for (int e = 0; e < E; ++e) incl += total[e];
     for (int o = 1; o < 64; o <<= 1) {
       const int v = __shfl_up(incl, o, 64);
       if (lane >= o) incl += v;
@@ -332,20 +343,25 @@ __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
     if (lane == 63) wave_sum[wave] = incl;
     __syncthreads();
     for (int w = 0; w < wave; ++w) incl += wave_sum[w];
-    base_d[tid] = before + incl;
+#pragma unroll
+    for (int e = E - 1; e >= 0; --e) {
+      incl -= total[e];
+      base_d[E * tid + e] = incl + before[e];
+    }
+    __syncthreads();
   } else {
     base_d[tid] = offs[int64_t(tid) * ntiles + blockIdx.x];
   }
   const int64_t tbase = int64_t(blockIdx.x) * (kRsThreads * IT);
   for (int it = 0; it < IT; ++it) {
-    for (int k = lane; k < 256; k += 64) wcnt[wave][k] = 0;
+    for (int k = lane; k < D; k += 64) wcnt[wave][k] = 0;
     const int64_t i = tbase + int64_t(it) * kRsThreads + tid;
     const bool valid = i < n;
     uint64_t key = valid ? kin[i] : 0;
     int val = valid ? vin[i] : 0;
     const int d = valid ? int((key >> shift) & uint64_t(mask)) : 0;
     uint64_t peers = __ballot(valid);
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < (D == 512 ? 9 : 8); ++b) {
       const bool bit = (d >> b) & 1;
       const uint64_t m = __ballot(bit);
       peers &= bit ? m : ~m;
@@ -354,14 +370,14 @@ __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
     __syncthreads();
     if (valid && rank == 0) wcnt[wave][d] = __popcll(peers);
     __syncthreads();
-    {
-      int run = base_d[tid];
+    for (int e = tid; e < D; e += kRsThreads) {
+      int run = base_d[e];
       for (int w = 0; w < kRsThreads / 64; ++w) {
-        int c = wcnt[w][tid];
-        wcnt[w][tid] = run;
+        int c = wcnt[w][e];
+        wcnt[w][e] = run;
         run += c;
       }
-      base_d[tid] = run;
+      base_d[e] = run;
     }
     __syncthreads();
     if (valid) {
@@ -373,26 +389,33 @@ __global__ __launch_bounds__(kRsThreads) void radix_scatter_kernel(
   }
 }
 
-// Passes of a sort by `bits` key bits.
-static int radix_passes(int64_t n, int bits) { return n <= 1 ? 0 : (bits + 7) / 8; }
+// Bits of a pass's digit, and passes, of a sort by `bits` key bits.
+static int radix_digit(int64_t n, int bits) {
+  return n <= kRsSmall && (bits + 8) / 9 < (bits + 7) / 8 ? 9 : 8;
+}
+static int radix_passes(int64_t n, int bits) {
+  return n <= 1 ? 0 : ceil_div(bits, radix_digit(n, bits));
+}
 
 // Sorts n pairs by the low `bits` bits of the key, from (k, v) through
 // (k2, v2) and back: after an odd number of passes the result is in the
-// second pair of buffers.  hist: 256 counts a tile (IT == 4: the first pass's).
-template <int IT>
+// second pair of buffers.  hist: D counts a tile (IT == 4: the first
+// pass's).
+template <int IT, int D>
 static void radix_sort(uint64_t* k, int* v, uint64_t* k2, int* v2, int64_t n, int bits,
                        hipStream_t s, std::vector<void*>& tmp, int* hist) {
   const int ntiles = ceil_div(n, kRsThreads * IT);
   for (int p = 0; p < radix_passes(n, bits); ++p) {
-    const int shift = 8 * p, db = std::min(8, bits - shift);
+    constexpr int digit = D == 512 ? 9 : 8;
+    const int shift = digit * p, db = std::min(digit, bits - shift);
     const int mask = (1 << db) - 1;
     if (IT != 4 || p > 0) {
-      radix_hist_kernel<IT><<<ntiles, kRsThreads, 0, s>>>(k, n, shift, mask, ntiles, hist);
+      radix_hist_kernel<IT, D><<<ntiles, kRsThreads, 0, s>>>(k, n, shift, mask, ntiles, hist);
       FMM_HIP_CHECK(hipGetLastError());
     }
     if (IT != 4) exclusive_scan<int>(hist, hist, int64_t(256) * ntiles, s, tmp);
-    radix_scatter_kernel<IT><<<ntiles, kRsThreads, 0, s>>>(k, v, k2, v2, n, shift, mask,
-                                                           ntiles, hist);
+    radix_scatter_kernel<IT, D><<<ntiles, kRsThreads, 0, s>>>(k, v, k2, v2, n, shift, mask,
+                                                              ntiles, hist);
     FMM_HIP_CHECK(hipGetLastError());
     std::swap(k, k2);
     std::swap(v, v2);
@@ -771,19 +794,25 @@ void build_plan(fmm_plan_s* p, const double* pos, hipStream_t s) {
     FMM_HIP_CHECK(hipMemsetAsync(tables, 0xff, sizeof(int) * tslots, s));
     fill = 0;
   }
+  const int digit = radix_digit(n, 3 * bits);
   int* hist = static_cast<int*>(
-      talloc(sizeof(int) * 256 * size_t(ceil_div(n, kRsThreads * (small ? 4 : 16)))));
+      talloc((sizeof(int) << digit) * size_t(ceil_div(n, kRsThreads * (small ? 4 : 16)))));
   if (small) {
-    keys_kernel<4 * kRsThreads, true><<<kb, 256, 0, s>>>(
-        pos, n, part, bad, nb, bits, k1, v1, head, stats, tables, fill,
-        (1 << std::min(8, 3 * bits)) - 1, hist);
-    FMM_HIP_CHECK(hipGetLastError());
-    radix_sort<4>(k1, v1, k2, v2, n, 3 * bits, s, tmp, hist);
+    const int mask = (1 << std::min(digit, 3 * bits)) - 1;
+    auto keys_and_sort = [&](auto d) {
+      constexpr int D = decltype(d)::value;
+      keys_kernel<4 * kRsThreads, D><<<kb, 256, 0, s>>>(pos, n, part, bad, nb, bits, k1, v1, head,
+                                                        stats, tables, fill, mask, hist);
+      FMM_HIP_CHECK(hipGetLastError());
+      radix_sort<4, D>(k1, v1, k2, v2, n, 3 * bits, s, tmp, hist);
+    };
+    if (digit == 9) keys_and_sort(std::integral_constant<int, 512>{});
+    else keys_and_sort(std::integral_constant<int, 256>{});
   } else {
-    keys_kernel<2048, false><<<kb, 256, 0, s>>>(pos, n, part, bad, nb, bits, k1, v1, head,
+    keys_kernel<2048, 0><<<kb, 256, 0, s>>>(pos, n, part, bad, nb, bits, k1, v1, head,
                                                 stats, tables, fill, 0, nullptr);
     FMM_HIP_CHECK(hipGetLastError());
-    radix_sort<16>(k1, v1, k2, v2, n, 3 * bits, s, tmp, hist);
+    radix_sort<16, 256>(k1, v1, k2, v2, n, 3 * bits, s, tmp, hist);
   }
 
   // --- sorted positions, cell counts of every level and child parity ---
