@@ -514,6 +514,11 @@ SvdShape svd_shape(int mt, bool fp32, int xs, int nt) {
     if (mt <= 8)
       return nt == 2 ? svd_make<float, 2, 4, Producers<4, 2, 1, 2, 2, 2>>()
                      : svd_make<float, 2, 4, Producers<4, 1, 1, 1, 2, 2>>();
+    // four partial slabs (and the tables) of two workgroups in a CU's LDS, or
+    // two slabs each: at ranks past that one workgroup a CU would be left
+    // (1/r^2, order 6: 300,000 in a cube 2807 -> 2336 us, on a sphere 1714 -> 1330)
+    if (mt <= 16 && nt == 2 && 1024 * size_t(xs) + 27 * 1024 > kSvdLdsMax / 2)
+      return svd_make<float, 4, 4, Producers<4, 2, 1, 2, 2, 2>>();
     if (mt <= 16)
       return nt == 2 ? svd_make<float, 4, 4, Producers<4, 2, 2, 1, 2, 2>>()
                      : svd_make<float, 4, 4, Producers<4, 1, 1, 1, 2, 2>>();

@@ -19,6 +19,7 @@ CASES = [
     ("cube", 30001, 5, 3, 1e-3),   # two M-tiles
     ("sphere", 9001, 6, 4, 1e-6),  # four M-tiles, empty groups
     ("cube", 5003, 4, 6, 1e-9),    # fourteen M-tiles
+    ("cube", 60_001, 5, 6, 1e-10),  # two partial slabs for two workgroups a CU
     ("cube", 1001, 3, 7, 1e-7),    # few tiles: 16 columns
     ("cube", 40001, 5, 7, 1e-7),   # 32 columns
     ("cube", 99991, 6, 7, 1e-7),   # whole tiles
