@@ -11,11 +11,14 @@
 // ia - 1 from the other; one barrier ends the iteration.
 //
 // A producer owns NJ of the item's 16-column N-tiles and, of the 16-row chunks
-// of the l^3 contraction, KG of the four K-groups (chunk % 4).  The FP32 sums
-// of a K-group run over its chunks in order and X = ((P0 + P1) + P2) + P3:
-// where a wavefront has several groups it adds them in registers, else the
-// partial slabs are added by the consumers, in that order, so every split
-// gives the same bits.
+// of the l^3 contraction, KG of the four K-groups (chunk % 4).  A K-group's
+// sum runs over its chunks in order, and X = ((P0 + P1) + P2) + P3 in FP32 and
+// (P0 + P1) + (P2 + P3) in FP64: where a wavefront has several groups it adds
+// in registers what that order allows, the rest are partial slabs added by
+// the consumers, so every split and width gives the same bits (a serving
+// batch takes one width for all its plans).  Pairs in FP64 leave two slabs
+// where a wavefront has two groups; a third would not fit the LDS at the
+// ranks that shape is for.
 //
 // What bounds it is latency and the order in which wavefronts get at the
 // matrix cores, not a memory rate: producers alone took 68% of the M2L's time
@@ -78,7 +81,7 @@ struct Producers {
   static_assert(NPW * NJ * KG == 4 * NT, "every N-tile and K-group once");
 };
 // Slabs of X per buffer: partial sums the producers cannot add in registers
-// in the order the FP32 sums are defined in, ((P0 + P1) + P2) + P3.
+// in the order X is defined in.
 constexpr int svd_slabs(bool fp32, int kg) { return kg == 4 ? 1 : kg == 2 ? (fp32 ? 3 : 2) : 4; }
 
 // Item `it` of the launch; false when its columns hold no target (the same
@@ -143,9 +146,9 @@ __device__ __forceinline__ void svd_produce(const JobDev* __restrict__ jobs,
   typedef typename Vec4<T>::type T4;
   constexpr bool F32 = sizeof(T) == 4;
   constexpr int NT = PC::NT, NJ = PC::NJ, D = PC::D, RP = PC::RP;
-  constexpr int NC = 16 * NT, KS = 4 / PC::KG, NS = svd_slabs(F32, PC::KG);
-  constexpr int KG = F32 ? PC::KG : 1;  // sums kept apart: the FP32 K-groups
+  constexpr int NC = 16 * NT, KG = PC::KG, NS = svd_slabs(F32, KG);
   static_assert(D % KG == 0, "a ring stage belongs to one K-group");
+  static_assert(F32 || KG <= 2, "four FP64 groups in registers are added in pairs");
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
   const unsigned lo = lane * unsigned(sizeof(T4));
   const int j0 = w % (NT / NJ) * NJ, s = w / (NT / NJ);
@@ -166,11 +169,10 @@ __device__ __forceinline__ void svd_produce(const JobDev* __restrict__ jobs,
     // the wavefront's chunks: positions u0 .. u0 + D - 1 of a ring turn are the
     // chunks turn(u0) + step(u); positions from nck on are read (the buffers
     // are padded by kSvdPadChunks) and not used
-    auto turn = [&](int u0) FMM_INLINE { return F32 ? u0 / KG * 4 + s * KG : u0 * KS + s; };
-    auto step = [](int u) FMM_INLINE { return F32 ? u / KG * 4 + u % KG : u * KS; };
+    auto turn = [&](int u0) FMM_INLINE { return u0 / KG * 4 + s * KG; };
+    auto step = [](int u) FMM_INLINE { return u / KG * 4 + u % KG; };
     static_assert(D + 4 * (D / KG) <= kSvdPadChunks, "padding");
-    const int nck = F32 ? KC / 4 * KG + min(max(KC % 4 - s * KG, 0), KG)
-                        : max(KC - s + KS - 1, 0) / KS;
+    const int nck = KC / 4 * KG + min(max(KC % 4 - s * KG, 0), KG);
     const int nckp = (max(nck, 1) + D - 1) / D * D;  // whole ring turns
     T4 rb[D][NJ], ra[D][RP];  // the ring
     // one stage of the turn that starts at b[] and a[]
@@ -294,8 +296,8 @@ __device__ __forceinline__ void svd_produce(const JobDev* __restrict__ jobs,
               if constexpr (KG == 4) {
                 put(0, ((x[0][jj][i] + x[1][jj][i]) + x[2][jj][i]) + x[3][jj][i]);
               } else if constexpr (KG == 2) {
-                if (s == 0) {
-                  put(0, x[0][jj][i] + x[1][jj][i]);
+                if (!F32 || s == 0) {
+                  put(s, x[0][jj][i] + x[1][jj][i]);
                 } else {
                   put(1, x[0][jj][i]);
                   put(2, x[1][jj][i]);
@@ -373,10 +375,15 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
           static_for<NT>([&](auto j) FMM_INLINE {
             bv[j] = T4{0, 0, 0, 0};
             if (GS && !((gon >> j) & 1)) return;
-            T4 v = *reinterpret_cast<const T4*>(X + 16 * j * XS + 16 * c);
-            static_for<NS - 1>([&](auto k) FMM_INLINE {
-              v += *reinterpret_cast<const T4*>(X + ((k + 1) * NC + 16 * j) * XS + 16 * c);
-            });
+            auto part = [&](int k) FMM_INLINE {
+              return *reinterpret_cast<const T4*>(X + (k * NC + 16 * j) * XS + 16 * c);
+            };
+            T4 v = part(0);
+            if constexpr (!F32 && NS == 4) {
+              v = (v + part(1)) + (part(2) + part(3));
+            } else {
+              static_for<NS - 1>([&](auto k) FMM_INLINE { v += part(k + 1); });
+            }
             bv[j] = v;
           });
           const bool more = c + 1 < nr;
@@ -584,7 +591,7 @@ static int svd_widest(int mt, bool fp32) {
 // 3, 30,000 at height 6 117 -> 107 us, 100,000 at height 7 317 -> 220), so the
 // fewest rounds in those units win (20,000 particles, height 4, order
 // 7: 64, 32, 16 columns 379, 238, 157 us; 60,000, height 5: 515, 608, 743).
-// Every column's sums are the same in each shape.
+// Every column's sums are the same in each shape, in both precisions.
 int64_t m2l_svd_slots(int mt, bool fp32, int cus) {
   return int64_t(mt <= (fp32 ? 16 : 8) ? 2 : 1) * std::max(1, cus);
 }
