@@ -135,8 +135,8 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
   J.has_far = h >= 3;
   J.modal = fp32 && h >= 3 ? 1 : 0;
   J.l2p_sparse = p->nleaf > 0 && p->n <= int64_t(kL2PSparseMax) * int64_t(p->nleaf) ? 1 : 0;
-  // compressed M2L split (targets are the cells of levels 2 .. h-1)
-  int parts = 1;
+  // M2L split (targets are the cells of levels 2 .. h-1)
+  int ranges = 1;
   const int64_t lrows = h >= 3 ? int64_t(p->ncell_total) - int64_t(p->lev[2].off) : 0;
   const size_t part_bytes = sizeof(double) * size_t(lrows) * op->ld;
   int cus = 0;
@@ -144,14 +144,14 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
   if (p->svd && h >= 3) {
     int items = 1, slots = 1;
     m2l_svd_ranges(p->order, fp32, J.xs, cus, &items, &slots);
-    parts = p->m2l_split > 0 ? p->m2l_split
-                             : auto_parts(int64_t(p->ntiles) * items, slots, part_bytes);
-    J.svd_nt = m2l_svd_nt(p->order, fp32, int64_t(p->ntiles) * parts, cus);
+    ranges = p->m2l_split > 0 ? p->m2l_split
+                              : auto_parts(int64_t(p->ntiles) * items, slots, part_bytes);
+    J.svd_nt = m2l_svd_nt(p->order, fp32, int64_t(p->ntiles) * ranges, cus);
     J.nmb = m2l_svd_nmb(op->mt, fp32, J.svd_nt);
   } else if (!p->svd && h >= 3 && p->W) {
-    parts = dense_parts(int64_t(p->ntiles) * J.nmb, op->mt, fp32, part_bytes, cus);
-    if (p->dense_parts_max > 0) parts = std::min(parts, p->dense_parts_max);
+    ranges = dense_parts(int64_t(p->ntiles) * J.nmb, op->mt, fp32, part_bytes, cus);
   }
+  int parts = !p->svd && p->dense_unsplit ? 1 : ranges;
   // The forked schedule's near field starts beside the M2L where that is one
   // round of workgroups (dense: of unsplit tiles) and leaves CUs idle, after
   // it elsewhere, where both would only take turns: evaluations, after and
@@ -175,11 +175,13 @@ void upload_job(fmm_plan_s* p, hipStream_t s) {
         p->locx_bytes = want;
       } catch (const FmmError&) {
         parts = 1;
+        if (p->svd) ranges = 1;
         split_oom = p->svd && p->m2l_split > 1;
       }
     }
   }
   p->m2l_parts = p->svd ? parts : 1;
+  J.m2l_ranges = ranges;
   J.m2l_parts = parts;
   J.locx_first = h >= 3 ? int64_t(p->lev[2].off) : 0;
   J.locx_rows = lrows;

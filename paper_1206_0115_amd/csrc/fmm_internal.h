@@ -250,7 +250,7 @@ struct fmm_plan_s {
   int* mutual_list = nullptr;      // leaves of the mutual pair lists (built on first use)
   int64_t mutual_off[2 * fmm::kMutualSlots + 1] = {0};  // list (slot 14 + k, colour c) at 2k + c
   int m2l_parts = 1;               // the compressed M2L's split in use (1: dense modes)
-  int dense_parts_max = 0;         // bound on the dense M2L's own split (0: none)
+  bool dense_unsplit = false;      // no LocX: one item takes a dense tile's ranges in turn
   double* LocX = nullptr;          // partial local expansions of parts 1..
   size_t locx_bytes = 0;
   hipStream_t side = nullptr;      // the near-field branch of the forked schedule

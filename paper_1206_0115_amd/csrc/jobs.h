@@ -47,10 +47,12 @@ struct JobDev {
   // leaves hold few particles on average: L2P spreads each particle's l^3
   // terms over a wavefront's lanes (l2p_sparse_kernel)
   int l2p_sparse;
-  // M2L split: each tile's far offsets in m2l_parts consecutive
-  // ranges, one work item each; part 0 writes Loc, part p > 0 the rows
-  // (p - 1) * locx_rows + (target row - locx_first) of LocX
-  int m2l_parts;
+  // M2L split: each tile's far offsets in m2l_ranges consecutive ranges, whose
+  // sums are added in range order, and m2l_parts work items: one a range
+  // (part 0 writes Loc, part p > 0 the rows (p - 1) * locx_rows +
+  // (target row - locx_first) of LocX), or, dense only, a single one that takes
+  // every range in turn, with the same results and no LocX
+  int m2l_ranges, m2l_parts;
   int leaf_tiles;  // M2L tiles of the leaf level (they come first)
   int64_t locx_first, locx_rows;
   double* LocX;

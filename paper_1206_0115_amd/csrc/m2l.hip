@@ -384,6 +384,13 @@ const OpSet* get_opset(int l, int kernel, hipStream_t s) {
 #define FMM_M2L_F64_PREFETCH_B 1
 #endif
 
+// A product rounded before it is added: a range's sum adds up to the same bits
+// from LocX (loc_sum_kernel) and from the accumulators.
+__device__ __forceinline__ double scaled(double sc, double v) {
+#pragma clang fp contract(off)
+  return sc * v;
+}
+
 template <typename T, int MTW, bool FOLD>
 __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
     const JobDev* __restrict__ jobs, const StepTab* __restrict__ tab) {
@@ -427,99 +434,105 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
     const T* __restrict__ Kp = FOLD ? reinterpret_cast<const T*>(J.kp32)
                                     : reinterpret_cast<const T*>(J.kp64);
 
-    T4 acc[MTW][4];
-    d4 acc64[FOLD ? MTW : 1][4];
-    for (int i = 0; i < MTW; ++i)
-      for (int j = 0; j < 4; ++j) {
-        acc[i][j] = T4{0, 0, 0, 0};
-        if (FOLD) acc64[FOLD ? i : 0][j] = d4{0, 0, 0, 0};
-      }
-
     const int nact = wuni(gld(J.tile_nact + tile));
-    const int ia0 = int(int64_t(part) * nact / parts), ia1 = int(int64_t(part + 1) * nact / parts);
     const unsigned char* act = J.tile_act + int64_t(tile) * kSlots;
     const unsigned char* gmask = J.tile_gmask + int64_t(tile) * kSlots;
     const int* srcb = J.tile_src + int64_t(tile) * kSlots * kTileN;
     const int* kidp = J.slot_kid + tl.parity * kSlots;
-
-    for (int ia = ia0; ia < ia1; ++ia) {
-      const int s = wuni(int(gld(act + ia)));
-      const int kid = wuni(gld(kidp + s));
-      // the 16-target groups with a source at this offset; the others'
-      // products are zero (a wavefront-uniform branch per group and chunk)
-      const int gm = wuni(int(gld(gmask + ia)));
-      const T* bptr[4];
-      for (int j = 0; j < 4; ++j)
-        bptr[j] = Wp + int64_t(gld(srcb + s * kTileN + 16 * j + c16)) * ld + 4 * g;
-      const T* aptr = Kp + (int64_t(kid) * MT + mt0) * KC * 256 + lane * 4;
-
-      // The A and B fragments are double-buffered one chunk ahead.  In FP64
-      // the B buffer costs a few spilled registers at MTW = 3 and still wins
-      // (36.8 vs 42.7 ms for the 1M-particle order-7 M2L on gfx950).
-      constexpr bool kPrefetchB = sizeof(T) == 4 || FMM_M2L_F64_PREFETCH_B;
-      T4 bv[4], av[MTW];
-      for (int j = 0; j < 4; ++j) bv[j] = gld(reinterpret_cast<const T4*>(bptr[j]));
-      for (int i = 0; i < MTW; ++i)
-        av[i] = i < nmt ? gld(reinterpret_cast<const T4*>(aptr + int64_t(i) * KC * 256))
-                        : T4{0, 0, 0, 0};
-      for (int c = 0; c < KC; ++c) {
-        T4 bn[kPrefetchB ? 4 : 1], an[MTW];
-        const bool more = c + 1 < KC;
-        if (!kPrefetchB && c > 0)
-          for (int j = 0; j < 4; ++j) bv[j] = gld(reinterpret_cast<const T4*>(bptr[j] + 16 * c));
-        if (more) {
-          if (kPrefetchB)
-            for (int j = 0; j < 4; ++j)
-              bn[kPrefetchB ? j : 0] = gld(reinterpret_cast<const T4*>(bptr[j] + 16 * (c + 1)));
-          for (int i = 0; i < MTW; ++i)
-            an[i] = i < nmt ? gld(reinterpret_cast<const T4*>(aptr + (int64_t(i) * KC + c + 1) * 256))
-                            : T4{0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (!((gm >> j) & 1)) continue;
-#pragma unroll
-          for (int st = 0; st < 4; ++st)
-#pragma unroll
-            for (int i = 0; i < MTW; ++i) acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
-        }
-        if (more) {
-          if (kPrefetchB)
-            for (int j = 0; j < 4; ++j) bv[j] = bn[kPrefetchB ? j : 0];
-          for (int i = 0; i < MTW; ++i) av[i] = an[i];
-        }
-      }
-      if (FOLD) {
-        for (int i = 0; i < MTW; ++i)
-          for (int j = 0; j < 4; ++j) {
-            for (int r = 0; r < 4; ++r) acc64[FOLD ? i : 0][j][r] += double(acc[i][j][r]);
-            acc[i][j] = T4{0, 0, 0, 0};
-          }
-      }
-    }
-
-    // D layout of the 16x16 outputs, column c16 in every lane group g: the
-    // FP32 instruction holds rows 4g+r in item r, the FP64 one rows 4r+g
-    // (both measured on gfx950).
     const double sc = J.scale[tl.level];
     const bool f64 = sizeof(T) == 8;
-    for (int j = 0; j < 4; ++j) {
-      const int col = 16 * j + c16;
-      if (col >= tl.count) continue;
-      double* out = m2l_out_row(J, part, gld(J.tgt + tl.first + col));
+    // the item's ranges: one, or every range of the tile in turn
+    const int ranges = J.m2l_ranges, per = ranges / parts;
+    for (int rg = part * per; rg < (part + 1) * per; ++rg) {
+      const int ia0 = int(int64_t(rg) * nact / ranges), ia1 = int(int64_t(rg + 1) * nact / ranges);
+      const bool first = rg == part * per;
+      T4 acc[MTW][4];
+      d4 acc64[FOLD ? MTW : 1][4];
+      for (int i = 0; i < MTW; ++i)
+        for (int j = 0; j < 4; ++j) {
+          acc[i][j] = T4{0, 0, 0, 0};
+          if (FOLD) acc64[FOLD ? i : 0][j] = d4{0, 0, 0, 0};
+        }
+      for (int ia = ia0; ia < ia1; ++ia) {
+        const int s = wuni(int(gld(act + ia)));
+        const int kid = wuni(gld(kidp + s));
+        // the 16-target groups with a source at this offset; the others'
+        // products are zero (a wavefront-uniform branch per group and chunk)
+        const int gm = wuni(int(gld(gmask + ia)));
+        const T* bptr[4];
+        for (int j = 0; j < 4; ++j)
+          bptr[j] = Wp + int64_t(gld(srcb + s * kTileN + 16 * j + c16)) * ld + 4 * g;
+        const T* aptr = Kp + (int64_t(kid) * MT + mt0) * KC * 256 + lane * 4;
+
+        // The A and B fragments are double-buffered one chunk ahead.  In FP64
+        // the B buffer costs a few spilled registers at MTW = 3 and still wins
+        // (36.8 vs 42.7 ms for the 1M-particle order-7 M2L on gfx950).
+        constexpr bool kPrefetchB = sizeof(T) == 4 || FMM_M2L_F64_PREFETCH_B;
+        T4 bv[4], av[MTW];
+        for (int j = 0; j < 4; ++j) bv[j] = gld(reinterpret_cast<const T4*>(bptr[j]));
+        for (int i = 0; i < MTW; ++i)
+          av[i] = i < nmt ? gld(reinterpret_cast<const T4*>(aptr + int64_t(i) * KC * 256))
+                          : T4{0, 0, 0, 0};
+        for (int c = 0; c < KC; ++c) {
+          T4 bn[kPrefetchB ? 4 : 1], an[MTW];
+          const bool more = c + 1 < KC;
+          if (!kPrefetchB && c > 0)
+            for (int j = 0; j < 4; ++j) bv[j] = gld(reinterpret_cast<const T4*>(bptr[j] + 16 * c));
+          if (more) {
+            if (kPrefetchB)
+              for (int j = 0; j < 4; ++j)
+                bn[kPrefetchB ? j : 0] = gld(reinterpret_cast<const T4*>(bptr[j] + 16 * (c + 1)));
+            for (int i = 0; i < MTW; ++i)
+              an[i] = i < nmt ? gld(reinterpret_cast<const T4*>(aptr + (int64_t(i) * KC + c + 1) * 256))
+                              : T4{0, 0, 0, 0};
+          }
 #pragma unroll
-      for (int i = 0; i < MTW; ++i) {
-        if (i >= nmt) continue;  // constant trip count keeps acc[] in registers
-        const int base = 16 * (mt0 + i);
-        if (f64) {
-          for (int r = 0; r < 4; ++r)
-            gst(out + base + 4 * r + g,
-                sc * (FOLD ? acc64[FOLD ? i : 0][j][r] : double(acc[i][j][r])));
-        } else {
-          d4 v;
-          for (int r = 0; r < 4; ++r)
-            v[r] = sc * (FOLD ? acc64[FOLD ? i : 0][j][r] : double(acc[i][j][r]));
-          gst(reinterpret_cast<d4*>(out + base + 4 * g), v);
+          for (int j = 0; j < 4; ++j) {
+            if (!((gm >> j) & 1)) continue;
+#pragma unroll
+            for (int st = 0; st < 4; ++st)
+#pragma unroll
+              for (int i = 0; i < MTW; ++i) acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
+          }
+          if (more) {
+            if (kPrefetchB)
+              for (int j = 0; j < 4; ++j) bv[j] = bn[kPrefetchB ? j : 0];
+            for (int i = 0; i < MTW; ++i) av[i] = an[i];
+          }
+        }
+        if (FOLD) {
+          for (int i = 0; i < MTW; ++i)
+            for (int j = 0; j < 4; ++j) {
+              for (int r = 0; r < 4; ++r) acc64[FOLD ? i : 0][j][r] += double(acc[i][j][r]);
+              acc[i][j] = T4{0, 0, 0, 0};
+            }
+        }
+      }
+
+      // D layout of the 16x16 outputs, column c16 in every lane group g: the
+      // FP32 instruction holds rows 4g+r in item r, the FP64 one rows 4r+g
+      // (both measured on gfx950).
+      for (int j = 0; j < 4; ++j) {
+        const int col = 16 * j + c16;
+        if (col >= tl.count) continue;
+        double* out = m2l_out_row(J, part, gld(J.tgt + tl.first + col));
+#pragma unroll
+        for (int i = 0; i < MTW; ++i) {
+          if (i >= nmt) continue;  // constant trip count keeps acc[] in registers
+          const int base = 16 * (mt0 + i);
+          if (f64) {
+            for (int r = 0; r < 4; ++r) {
+              double* const o = out + base + 4 * r + g;
+              const double v = scaled(sc, FOLD ? acc64[FOLD ? i : 0][j][r] : double(acc[i][j][r]));
+              gst(o, first ? v : gld(o) + v);
+            }
+          } else {
+            d4* const o = reinterpret_cast<d4*>(out + base + 4 * g);
+            d4 v;
+            for (int r = 0; r < 4; ++r)
+              v[r] = scaled(sc, FOLD ? acc64[FOLD ? i : 0][j][r] : double(acc[i][j][r]));
+            gst(o, first ? v : gld(o) + v);
+          }
         }
       }
     }

@@ -243,8 +243,9 @@ bool fmm_server_s::admit() {
       continue;
     }
     if (size_t(p->bytes) > budget && !p->svd && p->job_h.m2l_parts > 1) {
-      // the split's partial sums are optional: never a reason to refuse
-      p->dense_parts_max = 1;
+      // the split's partial sums are optional, with the same results: never a
+      // reason to refuse
+      p->dense_unsplit = true;
       upload_job(p, plan_stream);
     }
     r->bytes = int64_t(p->bytes);
