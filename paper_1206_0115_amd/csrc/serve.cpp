@@ -227,26 +227,35 @@ bool fmm_server_s::admit() {
       pending.pop_front();
       ++planning;
     }
-    // the caller's inputs are ready on the device before the plan reads them
-    FMM_HIP_CHECK(hipStreamWaitEvent(plan_stream, r->inputs, 0));
-    fmm_plan_s* p = fmm_plan_stream(r->pos, r->n, r->h, r->order, plan_stream);
-    int rc = p ? fmm_plan_set_precision(p, r->prec) : last_error_code();
-    if (rc == FMM_OK && !p) rc = FMM_ERR_HIP;
-    const std::string err = rc == FMM_OK ? std::string() : std::string(fmm_last_error());
+    // a failure from here on ends the request, which is in no queue now
+    fmm_plan_s* p = nullptr;
+    int rc = FMM_OK;
+    std::string err;
+    try {
+      // the caller's inputs are ready on the device before the plan reads them
+      FMM_HIP_CHECK(hipStreamWaitEvent(plan_stream, r->inputs, 0));
+      p = fmm_plan_stream(r->pos, r->n, r->h, r->order, plan_stream);
+      rc = p ? fmm_plan_set_precision(p, r->prec) : last_error_code();
+      if (rc == FMM_OK && !p) rc = FMM_ERR_HIP;
+      if (rc != FMM_OK) {
+        err = fmm_last_error();
+      } else if (size_t(p->bytes) > budget && !p->svd && p->job_h.m2l_parts > 1) {
+        // the split's partial sums are optional, with the same results: never a
+        // reason to refuse
+        p->dense_unsplit = true;
+        upload_job(p, plan_stream);
+      }
+    } catch (...) {
+      current_failure(rc, err);
+    }
     std::lock_guard<std::mutex> lk(mu);
     --planning;
     cv_launch.notify_all();
-    if (!p || rc != FMM_OK) {
+    if (rc != FMM_OK) {
       if (p) fmm_release(p);
       finish(r, rc, err);
       any = true;
       continue;
-    }
-    if (size_t(p->bytes) > budget && !p->svd && p->job_h.m2l_parts > 1) {
-      // the split's partial sums are optional, with the same results: never a
-      // reason to refuse
-      p->dense_unsplit = true;
-      upload_job(p, plan_stream);
     }
     r->bytes = int64_t(p->bytes);
     if (size_t(r->bytes) > budget) {
