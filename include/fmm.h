@@ -415,7 +415,9 @@ void fmm_trim_cache(void);
  * batch's launch sequence is captured once as a hipGraph and replayed with
  * new work tables.  Up to two batches run at once, each on its own stream:
  * requests that arrive while a batch runs are planned meanwhile and start as
- * soon as they are admitted, beside it on the device.  A request's results
+ * soon as they are admitted, beside it on the device.  Beside the plans each
+ * running batch may hold up to a 32nd of the budget, at most 1 GiB, of
+ * workspace that only makes small dense plans faster.  A request's results
  * are bit-identical to fmm_evaluate on the same inputs.
  */
 typedef struct fmm_server_s* fmm_server_t;

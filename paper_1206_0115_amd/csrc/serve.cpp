@@ -40,6 +40,11 @@ constexpr int kBuffers = 2;
 // requests that arrived with them, but no longer than this, so that a burst
 // shares launches and a lone request starts almost at once.
 constexpr double kBatchWindowS = 0.002;
+// Partial sums of a batch's dense plans (m2l_ranges): admitted plans hold none,
+// so that what fits the budget does not depend on them; a batch's plans take
+// theirs from its buffer's workspace, of at most this share of the budget and
+// this size, and run without (with the same results) where it is used up.
+constexpr size_t kPartialShare = 32, kPartialMax = size_t(1) << 30;
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
@@ -103,6 +108,8 @@ struct TableBuf {
   void* pinned = nullptr;
   void* dev = nullptr;
   hipStream_t stream = nullptr;  // the batches of this buffer run here
+  void* partial = nullptr;    // the batch's partial sums
+  size_t partial_bytes = 0;
   hipEvent_t last = nullptr;  // completion of the batch that last read it
   bool busy = false;
 };
@@ -124,7 +131,7 @@ const size_t kTableBytes = kTabsOff + sizeof(StepTab) * kMaxSteps;
 
 struct fmm_server_s {
   int device = 0;
-  size_t budget = 0;
+  size_t budget = 0, partial_max = 0;
   int max_active = 0;
   hipStream_t plan_stream = nullptr;
   fmm::TableBuf buf[fmm::kBuffers];
@@ -157,6 +164,7 @@ struct fmm_server_s {
   bool admit();
   bool launch_batch();
   void launch_on(int bi, const std::vector<fmm::Request*>& reqs);
+  void split_dense(fmm::TableBuf& B, const std::vector<fmm::Request*>& reqs);
   void finish(fmm::Request* r, int status, const std::string& err = std::string());
 };
 
@@ -235,16 +243,10 @@ bool fmm_server_s::admit() {
       // the caller's inputs are ready on the device before the plan reads them
       FMM_HIP_CHECK(hipStreamWaitEvent(plan_stream, r->inputs, 0));
       p = fmm_plan_stream(r->pos, r->n, r->h, r->order, plan_stream);
+      if (p) p->dense_unsplit = true;  // see kPartialMax
       rc = p ? fmm_plan_set_precision(p, r->prec) : last_error_code();
       if (rc == FMM_OK && !p) rc = FMM_ERR_HIP;
-      if (rc != FMM_OK) {
-        err = fmm_last_error();
-      } else if (size_t(p->bytes) > budget && !p->svd && p->job_h.m2l_parts > 1) {
-        // the split's partial sums are optional, with the same results: never a
-        // reason to refuse
-        p->dense_unsplit = true;
-        upload_job(p, plan_stream);
-      }
+      if (rc != FMM_OK) err = fmm_last_error();
     } catch (...) {
       current_failure(rc, err);
     }
@@ -324,6 +326,36 @@ bool fmm_server_s::launch_batch() {
   return true;
 }
 
+// One item a range for the batch's dense plans, as far as the workspace goes.
+void fmm_server_s::split_dense(TableBuf& B, const std::vector<Request*>& reqs) {
+  std::vector<std::pair<JobDev*, size_t>> at;
+  size_t want = 0;
+  for (Request* r : reqs) {
+    JobDev& J = r->plan->job_h;
+    if (r->plan->svd || J.m2l_ranges < 2) continue;
+    const size_t b = sizeof(double) * size_t(J.m2l_ranges - 1) * size_t(J.locx_rows * J.ld);
+    if (want + align256(b) > partial_max) continue;
+    at.push_back({&J, want});
+    want += align256(b);
+  }
+  if (want > B.partial_bytes) {
+    dev_free(B.partial);
+    B.partial = nullptr;
+    B.partial_bytes = 0;
+    try {
+      B.partial = dev_alloc(want);
+    } catch (const FmmError&) {
+      partial_max = want / 2;  // no room: not asked for again
+      return;
+    }
+    B.partial_bytes = want;
+  }
+  for (auto& a : at) {
+    a.first->LocX = reinterpret_cast<double*>(static_cast<char*>(B.partial) + a.second);
+    a.first->m2l_parts = a.first->m2l_ranges;
+  }
+}
+
 void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
   TableBuf& B = buf[bi];
   hipStream_t exec_stream = B.stream;
@@ -336,6 +368,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
   CallDev* calls = reinterpret_cast<CallDev*>(host + kCallsOff);
   StepTab* tabs = reinterpret_cast<StepTab*>(host + kTabsOff);
   const int nj = int(reqs.size());
+  split_dense(B, reqs);
   for (int j = 0; j < nj; ++j) {
     jobs[j] = reqs[j]->plan->job_h;
     calls[j] = CallDev{reqs[j]->q, reqs[j]->phi, reqs[j]->f, nullptr, nullptr, nullptr, nullptr};
@@ -584,6 +617,7 @@ fmm_server_t fmm_server_create(size_t hbm_budget_bytes, int max_active) {
   try {
     FMM_HIP_CHECK(hipGetDevice(&s->device));
     s->budget = hbm_budget_bytes;
+    s->partial_max = std::min(kPartialMax, hbm_budget_bytes / kPartialShare);
     s->max_active = max_active;
     FMM_HIP_CHECK(hipStreamCreateWithFlags(&s->plan_stream, hipStreamNonBlocking));
     for (int i = 0; i < kBuffers; ++i) {
@@ -736,6 +770,7 @@ void fmm_server_destroy(fmm_server_t s) {
   }
   for (int i = 0; i < kBuffers; ++i) {
     if (s->buf[i].last) (void)hipEventDestroy(s->buf[i].last);
+    dev_free(s->buf[i].partial);
     (void)hipHostFree(s->buf[i].pinned);
     (void)hipFree(s->buf[i].dev);
     (void)hipStreamDestroy(s->buf[i].stream);

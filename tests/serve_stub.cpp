@@ -141,6 +141,21 @@ int main(int, char** argv) {
     partial_bytes = 128;
     fail_upload = 1;
     ends(fmm_server_create(150, 4), true);
+  } else if (what == "beside") {  // two plans fit the budget without their partial sums
+    partial_bytes = 20;
+    hold = true;
+    fmm_server_t s = fmm_server_create(2 * plan_bytes, 4);
+    const int64_t a = submit(s);
+    fmm_request_stats st{};
+    if (!soon([&] { return fmm_server_poll(s, a, &st) == 0 && st.batch >= 0; }))
+      end(false, "first request not launched");
+    const int64_t b = submit(s);
+    if (!soon([&] { return fmm_server_poll(s, b, &st) == 0 && st.batch >= 0; }))
+      end(false, "second request not launched beside the first");
+    hold = false;
+    const bool good = fmm_server_wait(s, a, &st) == FMM_OK && fmm_server_wait(s, b, &st) == FMM_OK;
+    fmm_server_destroy(s);
+    end(good && plans == 0, "both done");
   } else if (what == "wait") {
     fail_wait = 1;
     ends(fmm_server_create(150, 4), false);

@@ -1,6 +1,7 @@
 """The serving loop's host code over a stand-in for the HIP runtime and the
 plans (``serve_stub.cpp``): a step that fails ends its own request, releases
-its plan and leaves the server running."""
+its plan and leaves the server running; partial sums that a dense plan could
+do without keep no request from running beside others."""
 import os
 import shutil
 import subprocess
@@ -27,4 +28,9 @@ def stub(tmp_path_factory):
 @pytest.mark.parametrize("what", ["upload", "wait", "precision"])
 def test_failed_step_ends_its_request(stub, what):
     r = subprocess.run([stub, what], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_partial_sums_keep_no_request_waiting(stub):
+    r = subprocess.run([stub, "beside"], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
