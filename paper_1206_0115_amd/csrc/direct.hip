@@ -49,15 +49,22 @@ struct Sums {
   double ph, fx, fy, fz;
 };
 
-// One pair, x - x_j = (dx, dy, dz) at squared distance r2 > 0 (finite).
+// One pair, x - x_j = (dx, dy, dz) at squared distance r2 > 0.
 // v_rsq_f64 and v_rcp_f64 are good to about 2^-24; one third-order step
 // (Halley's iteration for the root, the cubic Neumann sum for the
-// reciprocal) leaves an error below 2^-70 before rounding.
-template <int P>
+// reciprocal) leaves an error below 2^-70 before rounding.  Where r2 or 1/r2
+// overflows the sums are not finite, and SAFE takes division and root instead
+// (an infinite 1/r^2 of a very close pair, zeros at an infinite distance, NaN in
+// the direction of an infinite difference).
+template <int P, bool SAFE>
 __device__ __forceinline__ void add_pair(double dx, double dy, double dz, double r2, double q,
                                          Sums& a) {
   double pot, g;
-  if (P == 2) {
+  if (SAFE) {
+    const double ir2 = 1.0 / r2;
+    pot = P == 2 ? q * ir2 : q * (1.0 / sqrt(r2));
+    g = (P == 2 ? 2.0 * pot : pot) * ir2;
+  } else if (P == 2) {
     const double y = __builtin_amdgcn_rcp(r2);
     const double e = fma(-r2, y, 1.0);
     const double ir2 = fma(y, fma(e, e, e), y);
@@ -91,18 +98,41 @@ __device__ __forceinline__ Sources load_sources(const double* __restrict__ pos,
   return s;
 }
 
-// Sources j0 .. j0 + cnt - 1 added to the lane's sums, skipping pairs at zero
-// or NaN distance and, at an infinite one, adding the zero that 1/r gives.
-template <int P>
-__device__ __forceinline__ void add_checked(const double* __restrict__ pos,
-                                            const double* __restrict__ q, int64_t j0, int cnt,
-                                            double xi, double yi, double zi, Sums& a) {
+// Whether a lane's sums hold a NaN or an infinity (the same in every lane).
+__device__ __forceinline__ bool not_finite(const Sums& a) {
+  const double v = (a.ph + a.fx) + (a.fy + a.fz);
+  return __any(!(fabs(v) < INFINITY));
+}
+
+__device__ __forceinline__ void add_sums(Sums& a, const Sums& b) {
+  a.ph += b.ph;
+  a.fx += b.fx;
+  a.fy += b.fy;
+  a.fz += b.fz;
+}
+
+// Sums over sources j0 .. j0 + cnt - 1 but for pairs at zero or NaN distance.
+template <int P, bool SAFE>
+__device__ __forceinline__ Sums sum_pairs(const double* __restrict__ pos,
+                                          const double* __restrict__ q, int64_t j0, int cnt,
+                                          double xi, double yi, double zi) {
+  Sums a = {0.0, 0.0, 0.0, 0.0};
   for (int e = 0; e < cnt; ++e) {
     const int64_t j = j0 + e;
     const double dx = xi - pos[3 * j], dy = yi - pos[3 * j + 1], dz = zi - pos[3 * j + 2];
     const double r2 = (dx * dx + dy * dy) + dz * dz;
-    if (r2 > 0.0 && r2 < INFINITY) add_pair<P>(dx, dy, dz, r2, q[j], a);
+    if (r2 > 0.0) add_pair<P, SAFE>(dx, dy, dz, r2, q[j], a);
   }
+  return a;
+}
+
+template <int P>
+__device__ __forceinline__ Sums sum_checked(const double* __restrict__ pos,
+                                            const double* __restrict__ q, int64_t j0, int cnt,
+                                            double xi, double yi, double zi) {
+  Sums a = sum_pairs<P, false>(pos, q, j0, cnt, xi, yi, zi);
+  if (not_finite(a)) a = sum_pairs<P, true>(pos, q, j0, cnt, xi, yi, zi);
+  return a;
 }
 
 template <int P>
@@ -114,7 +144,9 @@ __device__ __forceinline__ Sums sum_range(const double* __restrict__ pos,
   if (j1 - j0 >= kDirBlock) {
     Sources cur = load_sources(pos, q, j0);
     for (; b + kDirBlock <= j1; b += kDirBlock) {
-      const Sums before = a;
+      // a block's sums start from zero: one that is not finite tells of this
+      // block's pairs alone
+      Sums s = {0.0, 0.0, 0.0, 0.0};
       for (int e = 0; e < kDirBlock; e += kDirGroup) {
         // the next group's loads are in flight while this one is computed
         // (past the range's end: its last group again, not used).  Scalar
@@ -130,20 +162,18 @@ __device__ __forceinline__ Sums sum_range(const double* __restrict__ pos,
         for (int u = 0; u < kDirGroup; ++u) {
           const double dx = xi - cur.p[3 * u], dy = yi - cur.p[3 * u + 1],
                        dz = zi - cur.p[3 * u + 2];
-          add_pair<P>(dx, dy, dz, (dx * dx + dy * dy) + dz * dz, cur.q[u], a);
+          add_pair<P, false>(dx, dy, dz, (dx * dx + dy * dy) + dz * dz, cur.q[u], s);
         }
         cur = next;
       }
-      // a pair at zero, NaN or infinite distance left a NaN or an infinity
-      // (the target itself does, once): that block again, with the checks
-      const double v = (a.ph + a.fx) + (a.fy + a.fz);
-      if (__any(!(fabs(v) < INFINITY))) {
-        a = before;
-        add_checked<P>(pos, q, b, kDirBlock, xi, yi, zi, a);
-      }
+      // a pair at zero, NaN, infinite or vanishing distance left a NaN or an
+      // infinity (the target itself does, once): that block again, with the
+      // checks
+      if (not_finite(s)) s = sum_checked<P>(pos, q, b, kDirBlock, xi, yi, zi);
+      add_sums(a, s);
     }
   }
-  add_checked<P>(pos, q, b, int(j1 - b), xi, yi, zi, a);
+  add_sums(a, sum_checked<P>(pos, q, b, int(j1 - b), xi, yi, zi));
   return a;
 }
 
