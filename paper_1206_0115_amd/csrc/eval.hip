@@ -1161,12 +1161,12 @@ __global__ __launch_bounds__(256) void cast_kernel(const JobDev* __restrict__ jo
   }
 
 void launch_m2l_step(int order, bool fp32, const JobDev* jobs, const StepTab* tab, int grid,
-                     hipStream_t s);
+                     hipStream_t s, int form);
 void launch_m2l_svd_step(int order, bool fp32, const JobDev* jobs, const StepTab* tab, int grid,
                          int xs, int nt, hipStream_t s, bool gskip);
 
 void launch_step(StepKind kind, int L, bool fp32, const JobDev* jobs, const StepTab* tab,
-                 const CallDev* calls, int grid, hipStream_t s, int xs, int nt, bool gskip) {
+                 const CallDev* calls, int grid, hipStream_t s, int xs, int nt, int form) {
   const unsigned g = unsigned(grid);
   switch (kind) {
     case kStepGather:
@@ -1191,10 +1191,10 @@ void launch_step(StepKind kind, int L, bool fp32, const JobDev* jobs, const Step
       loc_sum_kernel<<<g, 256, 0, s>>>(jobs, tab);
       break;
     case kStepM2L:
-      launch_m2l_step(L, fp32, jobs, tab, grid, s);
+      launch_m2l_step(L, fp32, jobs, tab, grid, s, form);
       break;
     case kStepM2LSvd:
-      launch_m2l_svd_step(L, fp32, jobs, tab, grid, xs, nt, s, gskip);
+      launch_m2l_svd_step(L, fp32, jobs, tab, grid, xs, nt, s, form != kM2LFull);
       break;
     case kStepL2L:
 #define L2L_CALL(LL) l2l_kernel<LL><<<g, kTransThreads, l2l_lds_bytes(LL), s>>>(jobs, tab)
@@ -1279,10 +1279,13 @@ void evaluate(fmm_plan_s* p, const double* q, double* phi, double* f, double* ph
   };
   if (forked && h < 3) fork_near();
   const StepKind m2l_kind = p->svd ? kStepM2LSvd : kStepM2L;
+  const int m2l_form = p->job_h.m2l_parts < p->job_h.m2l_ranges       ? kM2LRanges
+                       : (p->svd ? p->m2l_gskip : p->dense_gskip) ? kM2LSkip
+                                                                  : kM2LFull;
   auto m2l_launch = [&](int tab, hipStream_t st) {
     if (p->tab_h[tab].start[1] > 0)
       launch_step(m2l_kind, L, mixed, J, p->tab_d + tab, nullptr, p->tab_h[tab].start[1], st,
-                  p->job_h.xs, p->job_h.svd_nt, p->m2l_gskip);
+                  p->job_h.xs, p->job_h.svd_nt, m2l_form);
   };
   auto loc_sum = [&]() {
     if (p->tab_h[kTabLocSum].start[1] > 0) {

@@ -226,6 +226,7 @@ struct fmm_plan_s {
   int64_t m2l_groups_empty = 0;    // ... of them without a source
   bool near_early = false;         // the forked near field starts beside the M2L
   bool m2l_gskip = false;          // the compressed M2L skips the empty groups
+  bool dense_gskip = false;        // ... and the dense one
   int64_t pairs_by_kid[fmm::kOffsets] = {0};  // far pairs per packed operator
 
   // evaluation buffers

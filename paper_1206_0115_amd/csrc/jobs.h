@@ -142,13 +142,16 @@ __device__ inline int step_find(const StepTab& t, int item) {
 enum StepKind { kStepGather, kStepP2M, kStepM2M, kStepCast, kStepM2L, kStepL2L, kStepL2P,
                 kStepP2P, kStepCombine, kStepM2LSvd, kStepLocSum, kStepL2PSparse,
                 kStepP2PSelf };
-// gskip: the compressed M2L skips the 16-target groups without a source at
-// an offset (plans whose tiles have many, fmm_info.m2l_group_skip).
+// form: whether the M2L skips the 16-target groups without a source at an
+// offset (plans whose tiles have many: fmm_info.m2l_group_skip in the compressed
+// modes, fmm_plan_s::dense_gskip in the dense ones), and, dense, whether some
+// item takes several ranges (m2l_ranges).
+enum M2LForm { kM2LFull = 0, kM2LSkip = 1, kM2LRanges = 2 };
 // xs, nt: the compressed M2L's LDS row stride and N-tiles per item; nt: the
 // near field's wavefronts per leaf (p2p_waves).
 void launch_step(StepKind kind, int order, bool fp32, const JobDev* jobs, const StepTab* tab,
                  const CallDev* calls, int grid, hipStream_t s, int xs = 0, int nt = 0,
-                 bool gskip = false);
+                 int form = kM2LFull);
 
 // Wavefronts per target leaf of the near field, by the plan's particles and
 // leaves.

@@ -373,8 +373,11 @@ const OpSet* get_opset(int l, int kernel, hipStream_t s) {
 // 7), so what a small plan lacks is items: the job's m2l_parts cuts each
 // tile's offsets into ranges, one item each (4,000 particles, height 4,
 // order 5: evaluation 2250 -> 210 us; the 1M cube, last round: 38.2 -> 34.3
-// ms), and 16-target groups without a source at an offset are skipped (the
-// last tiles of a parity, the coarse levels, points on surfaces).
+// ms).  GS: 16-target groups without a source at an offset are skipped (the
+// last tiles of a parity, the coarse levels, points on surfaces), for plans
+// with many (dense_gskip); otherwise a K-step takes all accumulators in turn.
+// Only the form for items of several ranges loops over them: the loop costs
+// small items 2% (60,000 particles, height 5, order 4 mixed: 224 and 228 us).
 // Build-time tuning of the dense kernel: wavefronts per SIMD the register
 // allocation must allow, and whether FP64 double-buffers the B fragments.
 #ifndef FMM_M2L_WAVES_PER_SIMD
@@ -391,10 +394,11 @@ __device__ __forceinline__ double scaled(double sc, double v) {
   return sc * v;
 }
 
-template <typename T, int MTW, bool FOLD>
+template <typename T, int MTW, bool FOLD, int FORM>
 __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
     const JobDev* __restrict__ jobs, const StepTab* __restrict__ tab) {
   typedef typename Vec4<T>::type T4;
+  constexpr bool GS = FORM != kM2LFull;
   const int total = step_total(*tab);
   const int wave = wuni(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int g = lane >> 4, c16 = lane & 15;
@@ -439,13 +443,12 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
     const unsigned char* gmask = J.tile_gmask + int64_t(tile) * kSlots;
     const int* srcb = J.tile_src + int64_t(tile) * kSlots * kTileN;
     const int* kidp = J.slot_kid + tl.parity * kSlots;
-    const double sc = J.scale[tl.level];
-    const bool f64 = sizeof(T) == 8;
     // the item's ranges: one, or every range of the tile in turn
-    const int ranges = J.m2l_ranges, per = ranges / parts;
-    for (int rg = part * per; rg < (part + 1) * per; ++rg) {
-      const int ia0 = int(int64_t(rg) * nact / ranges), ia1 = int(int64_t(rg + 1) * nact / ranges);
-      const bool first = rg == part * per;
+    const int ranges = J.m2l_ranges;
+    const int rg1 = FORM == kM2LRanges && parts == 1 ? ranges : part + 1;
+    for (int rg = part; rg < rg1; ++rg) {
+      const int ia0 = rg * nact / ranges, ia1 = (rg + 1) * nact / ranges;
+      const bool first = FORM != kM2LRanges || rg == part;
       T4 acc[MTW][4];
       d4 acc64[FOLD ? MTW : 1][4];
       for (int i = 0; i < MTW; ++i)
@@ -456,9 +459,9 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
       for (int ia = ia0; ia < ia1; ++ia) {
         const int s = wuni(int(gld(act + ia)));
         const int kid = wuni(gld(kidp + s));
-        // the 16-target groups with a source at this offset; the others'
+        // GS: the 16-target groups with a source at this offset; the others'
         // products are zero (a wavefront-uniform branch per group and chunk)
-        const int gm = wuni(int(gld(gmask + ia)));
+        const int gm = GS ? wuni(int(gld(gmask + ia))) : 0xf;
         const T* bptr[4];
         for (int j = 0; j < 4; ++j)
           bptr[j] = Wp + int64_t(gld(srcb + s * kTileN + 16 * j + c16)) * ld + 4 * g;
@@ -486,13 +489,24 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
               an[i] = i < nmt ? gld(reinterpret_cast<const T4*>(aptr + (int64_t(i) * KC + c + 1) * 256))
                               : T4{0, 0, 0, 0};
           }
+          if constexpr (GS) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (!((gm >> j) & 1)) continue;
+            for (int j = 0; j < 4; ++j) {
+              if (!((gm >> j) & 1)) continue;
+#pragma unroll
+              for (int st = 0; st < 4; ++st)
+#pragma unroll
+                for (int i = 0; i < MTW; ++i)
+                  acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
+            }
+          } else {
 #pragma unroll
             for (int st = 0; st < 4; ++st)
 #pragma unroll
-              for (int i = 0; i < MTW; ++i) acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
+              for (int i = 0; i < MTW; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                  acc[i][j] = mfma16x16x4(av[i][st], bv[j][st], acc[i][j]);
           }
           if (more) {
             if (kPrefetchB)
@@ -512,6 +526,8 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
       // D layout of the 16x16 outputs, column c16 in every lane group g: the
       // FP32 instruction holds rows 4g+r in item r, the FP64 one rows 4r+g
       // (both measured on gfx950).
+      const double sc = J.scale[tl.level];
+      const bool f64 = sizeof(T) == 8;
       for (int j = 0; j < 4; ++j) {
         const int col = 16 * j + c16;
         if (col >= tl.count) continue;
@@ -539,13 +555,18 @@ __global__ __launch_bounds__(256, FMM_M2L_WAVES_PER_SIMD) void m2l_kernel(
   }
 }
 
-template <typename T, bool FOLD>
+template <typename T, bool FOLD, int FORM>
 static void launch_mtw(int mtw, const JobDev* jobs, const StepTab* tab, int grid, hipStream_t s) {
   switch (mtw) {
-    case 1: m2l_kernel<T, 1, FOLD><<<grid, 256, 0, s>>>(jobs, tab); break;
-    case 2: m2l_kernel<T, 2, FOLD><<<grid, 256, 0, s>>>(jobs, tab); break;
-    case 3: m2l_kernel<T, 3, FOLD><<<grid, 256, 0, s>>>(jobs, tab); break;
-    default: m2l_kernel<T, 4, FOLD><<<grid, 256, 0, s>>>(jobs, tab); break;
+    case 1: {
+      // up to order 4 the skip costs full tiles nothing (200,000, height 6, mixed:
+      // order 3 550 us, and 577 without, order 4 1138 and 1131)
+      constexpr int F = FORM == kM2LFull ? kM2LSkip : FORM;
+      m2l_kernel<T, 1, FOLD, F><<<grid, 256, 0, s>>>(jobs, tab);
+      break;
+    }
+    case 2: m2l_kernel<T, 2, FOLD, FORM><<<grid, 256, 0, s>>>(jobs, tab); break;
+    default: m2l_kernel<T, 3, FOLD, FORM><<<grid, 256, 0, s>>>(jobs, tab); break;
   }
 }
 
@@ -575,13 +596,18 @@ double m2l_item_flops(int mt) { return 2.0 * kTileN * (64.0 * m2l_mtw(mt)) * (16
 
 // Every job in `tab` must have the same order (same packed operator shape).
 void launch_m2l_step(int order, bool fp32, const JobDev* jobs, const StepTab* tab, int grid,
-                     hipStream_t s) {
+                     hipStream_t s, int form) {
   const int l3 = order * order * order;
   const int mtw = m2l_mtw((l3 + 15) / 16);
-  if (fp32)
-    launch_mtw<float, true>(mtw, jobs, tab, grid, s);
-  else
-    launch_mtw<double, false>(mtw, jobs, tab, grid, s);
+#define M2L_CALL(F)                                              \
+  if (fp32) launch_mtw<float, true, F>(mtw, jobs, tab, grid, s); \
+  else launch_mtw<double, false, F>(mtw, jobs, tab, grid, s)
+  switch (form) {
+    case kM2LFull: M2L_CALL(kM2LFull); break;
+    case kM2LSkip: M2L_CALL(kM2LSkip); break;
+    default: M2L_CALL(kM2LRanges); break;
+  }
+#undef M2L_CALL
   FMM_HIP_CHECK(hipGetLastError());
 }
 

@@ -969,6 +969,15 @@ void build_plan(fmm_plan_s* p, const double* pos, hipStream_t s) {
   // plans whose tiles leave many 16-target groups without a source at an
   // offset (points on surfaces) take the compressed M2L that skips them
   p->m2l_gskip = p->m2l_groups > 0 && 10 * p->m2l_groups_empty >= p->m2l_groups;
+  // The dense M2L skips a group by a branch between its MFMAs, which costs full
+  // tiles up to 5% (200,000 particles, height 6, 1% of the tiles' groups
+  // without a source, ms skipping and not: order 10 mixed 155.6 and 149.1, fp64
+  // 284.8 and 273.2, order 8 mixed 42.2 and 40.2) and pays where they are more:
+  // 8% (60,000, height 5) fp64 order 8 8.95 and 9.39, order 9 17.7 and 18.8,
+  // order 10 37.3 and 36.4; 28% (200,000 on a sphere, height 7) order 6 6.8 and
+  // 8.1.  Of all four groups of a tile, those past its targets included.
+  p->dense_gskip = 20 * (4 * p->active_slots - (p->m2l_groups - p->m2l_groups_empty)) >=
+                   4 * p->active_slots;
 }
 
 // ------------------------------------------------------ mutual pair lists

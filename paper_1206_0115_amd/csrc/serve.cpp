@@ -101,7 +101,7 @@ struct Launch {
   bool fp32;
   int xs;  // LDS row stride of the compressed M2L
   int nt;  // ... and its N-tiles per item; the near field's wavefronts per leaf
-  bool gskip;  // compressed M2L: skip the 16-target groups without a source
+  int form;  // M2LForm
 };
 
 struct TableBuf {
@@ -377,7 +377,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
   std::vector<Launch> seq;
   std::string key;
   auto add = [&](StepKind kind, int order, bool fp32, auto want, auto items, auto level,
-                 bool gskip = false) {
+                 int form = kM2LFull) {
     StepTab& t = tabs[seq.size()];
     std::memset(&t, 0, sizeof(t));
     int tot = 0, xs = 0, nt = 0;
@@ -399,9 +399,9 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
     if (seq.size() + 1 >= size_t(kMaxSteps)) throw FmmError{FMM_ERR_HIP, "batch step table full"};
     if (kind != kStepM2LSvd) xs = 0;
     if (kind != kStepM2LSvd && kind != kStepP2P) nt = 0;
-    seq.push_back({kind, order, fp32, xs, nt, gskip});
+    seq.push_back({kind, order, fp32, xs, nt, form});
     key += std::to_string(int(kind)) + ":" + std::to_string(order) + (fp32 ? "f" : "d") + ":" +
-           std::to_string(xs) + ":" + std::to_string(nt) + (gskip ? "g" : "") + ";";
+           std::to_string(xs) + ":" + std::to_string(nt) + ":" + std::to_string(form) + ";";
   };
   auto all_ = [](Request*) { return true; };
   auto lvl0 = [](Request*) { return 0; };
@@ -433,7 +433,8 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
           [&](Request* r) { return r->h - 2 - s; });
   add(kStepCast, 0, true, [&](Request* r) { return far(r) && mixed(r); },
       [](Request* r) { return int(r->plan->tab_h[kTabCast].start[1]); }, lvl0);
-  // dense, then compressed; the compressed plans that skip empty 16-target
+  // dense (skipping empty 16-target groups, whatever the plans), then
+  // compressed; the compressed plans that skip empty 16-target
   // groups (points on surfaces) in launches of their own.  The jobs of a
   // compressed launch take the item width that suits their tiles together
   // (every width gives a plan the same results)
@@ -447,7 +448,12 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
             return far(r) && r->order == L && mixed(r) == (f32 != 0) && svd(r) == (cmp != 0) &&
                    (cmp == 0 || r->plan->m2l_gskip == (gs != 0));
           };
-          if (cmp) {
+          int form = gs ? kM2LSkip : kM2LFull;
+          if (!cmp) {
+            form = kM2LSkip;
+            for (int j = 0; j < nj; ++j)
+              if (want(reqs[j]) && jobs[j].m2l_parts < jobs[j].m2l_ranges) form = kM2LRanges;
+          } else {
             int64_t tile_parts = 0;
             for (int j = 0; j < nj; ++j)
               if (want(reqs[j])) tile_parts += int64_t(jobs[j].ntiles) * jobs[j].m2l_parts;
@@ -463,7 +469,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
                 const JobDev& J = jobs[std::find(reqs.begin(), reqs.end(), r) - reqs.begin()];
                 return J.ntiles * J.nmb * J.m2l_parts;
               },
-              lvl0, gs != 0);
+              lvl0, form);
         }
   // partial sums of plans that split their M2L back into Loc
   add(kStepLocSum, 0, false, [&](Request* r) { return far(r) && r->plan->job_h.m2l_parts > 1; },
@@ -501,7 +507,7 @@ void fmm_server_s::launch_on(int bi, const std::vector<Request*>& reqs) {
     FMM_HIP_CHECK(hipMemcpyAsync(B.dev, B.pinned, kTableBytes, hipMemcpyHostToDevice, exec_stream));
     for (size_t i = 0; i < seq.size(); ++i)
       launch_step(seq[i].kind, seq[i].order, seq[i].fp32, jobs_d, tabs_d + i, calls_d,
-                  persistent_grid(seq[i].kind), exec_stream, seq[i].xs, seq[i].nt, seq[i].gskip);
+                  persistent_grid(seq[i].kind), exec_stream, seq[i].xs, seq[i].nt, seq[i].form);
     FMM_HIP_CHECK(hipStreamEndCapture(exec_stream, &g));
     hipGraphExec_t ge = nullptr;
     FMM_HIP_CHECK(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));

@@ -95,7 +95,7 @@ void upload_job(fmm_plan_s* p, hipStream_t) {
   p->bytes = plan_bytes + (split ? partial_bytes : 0);
 }
 void launch_step(StepKind, int, bool, const JobDev*, const StepTab*, const CallDev*, int,
-                 hipStream_t, int, int, bool) {}
+                 hipStream_t, int, int, int) {}
 int p2p_waves(int64_t, int64_t) { return 1; }
 int m2l_svd_nt(int, bool, int64_t, int) { return 1; }
 int m2l_svd_nmb(int, bool, int) { return 1; }
