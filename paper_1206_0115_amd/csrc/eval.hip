@@ -537,9 +537,9 @@ __global__ __launch_bounds__(64) void l2p_sparse_kernel(const JobDev* __restrict
 // particles is not the launch's tail.  The vector units bound large plans:
 // 18 instructions (FP64) or 17 (FP32) a pair and the reciprocal (square) root.
 // Near field, one wavefront a leaf with a lane per target before, and now:
-// FP64 20,000 particles, height 4 114 -> 53 us, 300,000, height 5 976 -> 532,
-// 1M, height 6 1009 -> 722; FP32 200,000 on a sphere, height 6 215 -> 134, 10M,
-// height 8 11.6 -> 10.5 ms.
+// FP64 20,000 particles, height 4 109 -> 39 us, 300,000, height 5 910 -> 484,
+// 1M, height 6 1015 -> 722, 500,000 on a sphere, height 8 (3 a leaf) 188 -> 173;
+// FP32 200,000 on a sphere, height 6 215 -> 134, 10M, height 8 11.6 -> 10.5 ms.
 constexpr int kSelfSlot = 13;  // the near-list slot of the target leaf itself
 constexpr double kFarAway = 1e30;
 typedef double src4 __attribute__((ext_vector_type(4)));  // x, y, z, q of one source
@@ -715,19 +715,27 @@ __device__ __forceinline__ void p2p_leaf_f64(const JobDev& J, int a, P2PLds<W>& 
   }
   __syncthreads();
   const int total = wuni(L.pre[27]), nself = wuni(L.pre[1]);
-  // batches of target pairs: the fewest passes, batches / splits, of one to
-  // four (more where a batch would exceed the threads)
+  // batches of target pairs: the fewest passes of one to four (more where a
+  // batch would exceed the threads), a batch itself costing about kBatch; small
+  // leaves, whose time is what surrounds the passes, take one without the
+  // choice, and no more splits than sources (20,000 at height 7: 39 us choosing
+  // by the passes alone, 24 so)
+  constexpr float kBatch = 6.f;
   const int pairs = (nt + 1) / 2, b0 = (pairs + T - 1) / T;
-  int nb = 0, K = 0;
-  float best = 0.f;
-  for (int B = b0; B < b0 + 4; ++B) {
-    const int n = (pairs + B - 1) / B, k = T / n;
-    const float cost = float(B) / float(k);
-    if (K == 0 || cost < 0.99f * best) {
-      nb = n;
-      K = k;
-      best = cost;
+  int nb = pairs, K = 1;
+  if (b0 > 1 || float(total) * (1.f / float(T / pairs) - float(pairs) / T) > kBatch) {
+    float best = 0.f;
+    for (int B = b0; B < b0 + 4; ++B) {
+      const int n = (pairs + B - 1) / B, k = T / n;
+      const float cost = float(B) * (float(total) / float(k) + kBatch);
+      if (B == b0 || cost < 0.99f * best) {
+        nb = n;
+        K = k;
+        best = cost;
+      }
     }
+  } else {
+    K = min(T / pairs, total);
   }
   const int k = tid / nb, t = tid - k * nb;
   for (int tb = 0; tb < pairs; tb += nb) {
@@ -752,6 +760,7 @@ __device__ __forceinline__ void p2p_leaf_f64(const JobDev& J, int a, P2PLds<W>& 
       p2p_run<KP, true, W>(J, L, total, nself, K, on ? k : 0, tg, acc);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
+      if (r == 1 && pairs + tb >= nt) break;  // no second targets
       __syncthreads();  // the sources, or the first targets' sums, are read
       L.red[0][tid] = acc[r].ph;
       L.red[1][tid] = acc[r].fx;
@@ -999,11 +1008,12 @@ __global__ __launch_bounds__(64 * W) void p2p_f32_kernel(const JobDev* __restric
 // Wavefronts a leaf.  Few leaves need many to fill the GPU and to hide each
 // other's latency, large ones share the staging among four; below 16
 // particles a leaf the wavefronts of a group would mostly wait.  Near field
-// with 1, 4, 16 wavefronts, us: FP64, 64 leaves of 16 25, 24, 14; 512 of 39
-// 101, 53, 64; 4,096 of 73 626, 532, 766; 32,768 of 30 722, 857, -; 218,039
-// of 2 420, 1590, -; FP32, 64 of 16 27, 13, 12; 512 of 39 89, 30, 32; 4,586 of
-// 44 202, 134, 266; 4,096 of 15 39, 46, -; 32,768 of 30 537, 572, 1304; 77,828
-// of 128 10715, 10345, 17246.
+// with 1, 4, 16 wavefronts, us: FP64, 64 leaves of 16 23, 12, 13; 512 of 39
+// 98, 40, 42; 4,096 of 73 573, 454, 538; 4,096 of 15 47, 50, 143; 32,768 of 30
+// 673, 701, 1499; 218,039 of 2 335, 1241, 5604; FP32, 64 of 16 24, 14, 12; 512
+// of 39 74, 35, 34; 4,096 of 73 514, 454, 676; 4,096 of 15 41, 46, 116; 32,768
+// of 30 515, 586, 1247; 218,039 of 2 529, 1325, 5550; 77,828 of 128 10715,
+// 10345, 17246.
 int p2p_waves(int64_t n, int64_t nleaf) {
   if (nleaf <= 256) return 16;
   if (nleaf <= 1024) return 4;
