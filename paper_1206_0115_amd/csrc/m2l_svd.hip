@@ -13,12 +13,13 @@
 // A producer owns NJ of the item's 16-column N-tiles and, of the 16-row chunks
 // of the l^3 contraction, KG of the four K-groups (chunk % 4).  A K-group's
 // sum runs over its chunks in order, and X = ((P0 + P1) + P2) + P3 in FP32 and
-// (P0 + P1) + (P2 + P3) in FP64: where a wavefront has several groups it adds
+// (P0 + P2) + (P1 + P3) in FP64: where a wavefront has several groups it adds
 // in registers what that order allows, the rest are partial slabs added by
 // the consumers, so every split and width gives the same bits (a serving
 // batch takes one width for all its plans).  Pairs in FP64 leave two slabs
 // where a wavefront has two groups; a third would not fit the LDS at the
-// ranks that shape is for.
+// ranks that shape is for.  They are two chunks apart, so that a contraction
+// of two chunks (order 3) still feeds both wavefronts.
 //
 // What bounds it is latency and the order in which wavefronts get at the
 // matrix cores, not a memory rate: producers alone took 68% of the M2L's time
@@ -146,7 +147,7 @@ __device__ __forceinline__ void svd_produce(const JobDev* __restrict__ jobs,
   typedef typename Vec4<T>::type T4;
   constexpr bool F32 = sizeof(T) == 4;
   constexpr int NT = PC::NT, NJ = PC::NJ, D = PC::D, RP = PC::RP;
-  constexpr int NC = 16 * NT, KG = PC::KG, NS = svd_slabs(F32, KG);
+  constexpr int NC = 16 * NT, KG = PC::KG, KS = 4 / KG, NS = svd_slabs(F32, KG);
   static_assert(D % KG == 0, "a ring stage belongs to one K-group");
   static_assert(F32 || KG <= 2, "four FP64 groups in registers are added in pairs");
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
@@ -169,10 +170,11 @@ __device__ __forceinline__ void svd_produce(const JobDev* __restrict__ jobs,
     // the wavefront's chunks: positions u0 .. u0 + D - 1 of a ring turn are the
     // chunks turn(u0) + step(u); positions from nck on are read (the buffers
     // are padded by kSvdPadChunks) and not used
-    auto turn = [&](int u0) FMM_INLINE { return u0 / KG * 4 + s * KG; };
-    auto step = [](int u) FMM_INLINE { return u / KG * 4 + u % KG; };
+    auto turn = [&](int u0) FMM_INLINE { return F32 ? u0 / KG * 4 + s * KG : u0 * KS + s; };
+    auto step = [](int u) FMM_INLINE { return F32 ? u / KG * 4 + u % KG : u * KS; };
     static_assert(D + 4 * (D / KG) <= kSvdPadChunks, "padding");
-    const int nck = KC / 4 * KG + min(max(KC % 4 - s * KG, 0), KG);
+    const int nck = F32 ? KC / 4 * KG + min(max(KC % 4 - s * KG, 0), KG)
+                        : max(KC - s + KS - 1, 0) / KS;
     const int nckp = (max(nck, 1) + D - 1) / D * D;  // whole ring turns
     T4 rb[D][NJ], ra[D][RP];  // the ring
     // one stage of the turn that starts at b[] and a[]
@@ -380,7 +382,7 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
             };
             T4 v = part(0);
             if constexpr (!F32 && NS == 4) {
-              v = (v + part(1)) + (part(2) + part(3));
+              v = (v + part(2)) + (part(1) + part(3));
             } else {
               static_for<NS - 1>([&](auto k) FMM_INLINE { v += part(k + 1); });
             }
