@@ -80,6 +80,7 @@ template <int NPW_, int NT_, int NJ_, int KG_, int D_, int RP_>
 struct Producers {
   static constexpr int NPW = NPW_, NT = NT_, NJ = NJ_, KG = KG_, D = D_, RP = RP_;
   static_assert(NPW * NJ * KG == 4 * NT, "every N-tile and K-group once");
+  static_assert(RP <= 5, "the rest of a rank's passes");
 };
 // Slabs of X per buffer: partial sums the producers cannot add in registers
 // in the order X is defined in.
@@ -251,6 +252,8 @@ __device__ __forceinline__ void svd_produce(const JobDev* __restrict__ jobs,
           auto mul = [&](auto u) FMM_INLINE {
             if (np == RP) mul_n(u, std::integral_constant<int, RP>{});
             else if (RP == 2 || np == 1) mul_n(u, std::integral_constant<int, 1>{});
+            else if (RP > 3 && np == 2) mul_n(u, std::integral_constant<int, 2>{});
+            else if (RP > 4 && np == 3) mul_n(u, std::integral_constant<int, 3>{});
             else mul_n(u, std::integral_constant<int, RP - 1>{});
           };
           int u0 = 0;
@@ -327,7 +330,8 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
   constexpr bool F32 = sizeof(T) == 4;
   constexpr int NT = PC::NT, NC = 16 * NT, NS = svd_slabs(F32, PC::KG);
   // U fragments in flight; a divisor of MTW, so that a ring stage is an M-tile
-  constexpr int RD = MTW % 4 == 0 ? (F32 && NT == 4 && MTW == 8 ? 2 : 4) : MTW % 3 == 0 ? 3 : MTW;
+  // (two where eight M-tiles' accumulators leave no registers for more)
+  constexpr int RD = MTW % 4 == 0 ? (MTW == 8 && (!F32 || NT == 4) ? 2 : 4) : MTW % 3 == 0 ? 3 : MTW;
   static_assert(MTW % RD == 0, "ring");
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
   const unsigned lo = lane * unsigned(sizeof(T4));
@@ -353,18 +357,31 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
     bool folded = false;
     svd_fill<NT, GS>(I, meta, srct);
     const int fold_every = wuni(J.fold_every);
+    // GS, order 10 in FP64: the next offset from a on at which an N-tile of the
+    // item has a source, so that the ring does not read the fragments of those
+    // without (100,000 on a sphere, height 7: M2L 24.8 -> 23.6 ms; at low orders
+    // the chain of table reads costs more: order 3 212 -> 230 us)
+    constexpr bool SKIP = GS && !F32 && MTW == 8;
+    auto next_on = [&](int a) FMM_INLINE {
+      if (SKIP)
+        while (a < na && !((wuni(meta[a].nr_nst) >> (24 + I.col0 / 16)) & ((1 << NT) - 1))) ++a;
+      return a;
+    };
+    int cur = next_on(0);
     T4 ring[RD];
-    if (nmt > 0 && na > 0) {
-      const int nr = wuni(meta[0].nr_nst) & 0xffff;
-      const T* const a2 = P2 + wuni(meta[0].off) + int64_t(mt0) * nr * 256;
+    if (nmt > 0 && cur < na) {
+      const int nr = wuni(meta[cur].nr_nst) & 0xffff;
+      const T* const a2 = P2 + wuni(meta[cur].off) + int64_t(mt0) * nr * 256;
       static_for<RD>([&](auto i) FMM_INLINE {
         ring[i] = frag(a2 + int64_t(min(int(i), nmt - 1)) * nr * 256, lo);
       });
     }
     for (int ia = 0; ia <= na; ++ia) {
-      if (ia > 0 && nmt > 0) {
+      const int ic = ia - 1;
+      if (ia > 0 && nmt > 0 && (!SKIP || ic == cur)) {
         // phase 2 of offset ia - 1 from the buffer the producers filled
-        const int ic = ia - 1, inx = min(ia, na - 1);
+        cur = next_on(ia);
+        const int inx = cur < na ? cur : ic;  // past the last offset: itself again
         const int nrs = wuni(meta[ic].nr_nst);
         const int nr = nrs & 0xffff, nst = (nrs >> 16) & 0xff;  // rank chunks; K-steps of the last
         const int gon = nrs >> (24 + I.col0 / 16);
@@ -413,6 +430,8 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
                              : an + min(i + RD - MTW, nmt - 1) * sn, lo);
           }
         }
+      }
+      if (ia > 0 && nmt > 0) {
         if (F32 && ((ic + 1) % fold_every == 0 || ic == na - 1)) {
           // fold into this item's rows of Loc (scaled; the first fold
           // stores, later ones add): no other workgroup touches these rows
@@ -567,7 +586,10 @@ SvdShape svd_shape(int mt, bool fp32, int xs, int nt) {
   if (w <= 4) return svd_make<double, 4, 8, Producers<4, 1, 1, 1, 2, 2>>();
   if (w <= 6) return svd_make<double, 6, 8, Producers<4, 1, 1, 1, 2, 2>>();
   if (w == 7) return svd_make<double, 7, 8, Producers<4, 1, 1, 1, 2, 3>>();
-  return svd_make<double, 8, 8, Producers<4, 1, 1, 1, 2, 3>>();
+  // order 10: with 16 columns a pass over the contraction gathers them again,
+  // so five rank tiles a pass and one chunk ahead (100,000 particles, height 6,
+  // M2L ms: 34.6; six 37.1, four 39.1; two chunks ahead, four 40.3, three 41.7)
+  return svd_make<double, 8, 8, Producers<4, 1, 1, 1, 1, 5>>();
 }
 
 size_t svd_lds(const SvdShape& sh, int xs, bool fp32, bool staged) {
