@@ -22,9 +22,9 @@
 // of two chunks (order 3) still feeds both wavefronts.
 //
 // What bounds it is latency and the order in which wavefronts get at the
-// matrix cores, not a memory rate: producers alone took 68% of the M2L's time
-// and consumers alone 59%, at half of the MFMA rate together (order 7).  So
-// both roles read ahead through a ring of fragments that is never drained,
+// matrix cores, not a memory rate: without reading ahead across offsets the
+// matrix cores were busy half of the time and wavefronts waited 40-55% of
+// theirs (order 7).  So both roles read ahead through a ring of fragments that is never drained,
 // D chunks (producers) or RD fragments (consumers), across passes, offsets
 // and the barrier; every load is unconditional (past the last chunk it reads
 // on into padding, past the last offset it repeats it), so that a wait is for
@@ -646,12 +646,12 @@ int m2l_svd_nmb(int mt, bool fp32, int nt) {
 // columns start 16 bytes apart modulo the LDS banks.
 int m2l_svd_xs(int rmax_pad, bool fp32) { return rmax_pad + (fp32 ? 4 : 2); }
 
-// The rule of the offset ranges, and of the ranks that are refused.  Where a
-// tile's ranges begin and end decides the order of the FP32 sums, and a
-// rank's refusal is part of the interface, so both follow the item shape
-// they were set with (32 FP32 or 16 FP64 columns, whole FP32 tiles or 32
-// FP64 columns at orders 7 to 9 where four partial slabs fit the LDS),
-// whatever shape runs.
+// The rule of the offset ranges, and of the ranks that are refused.  Both
+// follow the item shape they were set with (32 FP32 or 16 FP64 columns, whole
+// FP32 tiles or 32 FP64 columns at orders 7 to 9 where four partial slabs fit
+// the LDS), whatever shape runs: a rank's refusal is part of the interface,
+// and ranges that stay where they are keep the order of the FP32 sums.  The
+// latter is a choice; ranges by the shape that runs are not tried yet.
 static int range_nt(int mt, bool fp32, int xs) {
   const int base = fp32 ? 2 : 1, full = 2 * base;
   const size_t need = size_t(2) * 4 * 16 * full * xs * (fp32 ? 4 : 8) + kSvdMetaBytes;

@@ -32,8 +32,9 @@
 namespace fmm {
 namespace {
 
-// Launches per batch: up to 53 per order present (two per tree level for
-// M2M and L2L, fourteen M2L forms, P2M, two L2P forms) and six more.
+// Launches per batch: up to 45 per order present (18 levels of M2M and of L2L,
+// six M2L launches, P2M, two L2P forms) and ten more (near field by precision
+// and width, gather, cast, partial sums, combine).
 constexpr int kMaxSteps = 704;
 constexpr int kBuffers = 2;
 // Batching window: admitted requests wait for the planner to finish the
