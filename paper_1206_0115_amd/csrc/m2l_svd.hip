@@ -331,7 +331,7 @@ __device__ __forceinline__ void svd_consume(const JobDev* __restrict__ jobs,
   constexpr int NT = PC::NT, NC = 16 * NT, NS = svd_slabs(F32, PC::KG);
   // U fragments in flight; a divisor of MTW, so that a ring stage is an M-tile
   // (two where eight M-tiles' accumulators leave no registers for more)
-  constexpr int RD = MTW % 4 == 0 ? (MTW == 8 && (!F32 || NT == 4) ? 2 : 4) : MTW % 3 == 0 ? 3 : MTW;
+  constexpr int RD = MTW % 4 == 0 ? (MTW == 8 && (F32 ? NT == 4 : PC::RP > 3) ? 2 : 4) : MTW % 3 == 0 ? 3 : MTW;
   static_assert(MTW % RD == 0, "ring");
   const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
   const unsigned lo = lane * unsigned(sizeof(T4));
@@ -587,8 +587,12 @@ SvdShape svd_shape(int mt, bool fp32, int xs, int nt) {
   if (w <= 6) return svd_make<double, 6, 8, Producers<4, 1, 1, 1, 2, 2>>();
   if (w == 7) return svd_make<double, 7, 8, Producers<4, 1, 1, 1, 2, 3>>();
   // order 10: with 16 columns a pass over the contraction gathers them again,
-  // so five rank tiles a pass and one chunk ahead (100,000 particles, height 6,
-  // M2L ms: 34.6; six 37.1, four 39.1; two chunks ahead, four 40.3, three 41.7)
+  // so five rank tiles a pass and one chunk ahead where the ranks fill them
+  // (100,000 particles, height 6, M2L ms at ranks up to 112: 36.7, and 42.6 with
+  // three tiles and two chunks ahead; up to 80 30.2 and 33.7, up to 64 26.2 and
+  // 28.6), three at ranks up to 48 (20.9, and 21.9 with five; up to 32 15.6 and
+  // 18.5)
+  if (xs <= m2l_svd_xs(48, false)) return svd_make<double, 8, 8, Producers<4, 1, 1, 1, 2, 3>>();
   return svd_make<double, 8, 8, Producers<4, 1, 1, 1, 1, 5>>();
 }
 

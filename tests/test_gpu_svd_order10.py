@@ -1,5 +1,5 @@
-"""The compressed M2L at order 10 in FP64, whose producers take five rank tiles
-a pass and whose consumers, on surfaces, pass over offsets without a source:
+"""The compressed M2L at order 10 in FP64, whose producers take three rank tiles
+a pass at ranks up to 48 and five above, and whose consumers, on surfaces, pass over offsets without a source:
 ranks of one tile up to the largest, i.e. every rest of a pass, against the
 dense FP64 path within ten times the tolerance."""
 import pytest
@@ -17,6 +17,8 @@ def rel(a, b):
 @pytest.mark.parametrize("kind,n,h,eps", [
     ("cube", 1501, 3, 1e-1),    # one or two tiles
     ("cube", 1501, 3, 1e-4),
+    ("cube", 1501, 3, 1e-7),    # three tiles
+    ("cube", 1501, 3, 1e-8),    # four
     ("cube", 20_011, 5, 1e-10),  # the most, several passes
     ("sphere", 9001, 6, 1e-4),
     ("sphere", 9001, 6, 1e-10),
