@@ -679,7 +679,11 @@ void m2l_svd_ranges(int order, bool fp32, int xs, int cus, int* items, int* slot
 void launch_m2l_svd_step(int order, bool fp32, const JobDev* jobs, const StepTab* tab, int grid,
                          int xs, int nt, hipStream_t s, bool gskip) {
   const SvdShape sh = svd_shape(svd_kc(order), fp32, xs, nt);
-  int staged = svd_lds(sh, xs, fp32, true) <= kSvdLdsMax ? 1 : 0;
+  // the source rows in LDS where they fit, and not at the cost of a CU's second
+  // workgroup (FP64 order 5 at ranks up to 64: 60,000 on a sphere, height 6, M2L
+  // 787 us staged, 600 not; at ranks that leave room for both staged is ahead)
+  const bool two = sh.ncw == 4 && svd_lds(sh, xs, fp32, false) <= kSvdLdsMax / 2;
+  int staged = svd_lds(sh, xs, fp32, true) <= kSvdLdsMax / (two ? 2 : 1) ? 1 : 0;
   const size_t lds = svd_lds(sh, xs, fp32, staged != 0);
   void* args[] = {&jobs, &tab, &staged};
   FMM_HIP_CHECK(hipLaunchKernel(sh.fn[gskip ? 1 : 0], dim3(grid), dim3(64 * (sh.npw + sh.ncw)),
