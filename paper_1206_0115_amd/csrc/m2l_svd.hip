@@ -530,7 +530,7 @@ int svd_kc(int order) { return (order * order * order + 15) / 16; }
 // KG = 1 are ahead of 64-column ones (60,000 particles, order 12: 6.3 against
 // 7.7).  FP64 with KG = 1 needs four slabs of 32 columns: where they do not
 // fit the LDS, KG = 2.
-SvdShape svd_shape(int mt, bool fp32, int xs, int nt) {
+SvdShape svd_shape(int mt, bool fp32, int xs, int nt, bool gskip) {
   const int mb = (mt + 63) / 64;
   const int w = (mt + 8 * mb - 1) / (8 * mb);
   // whether four partial slabs of 64 FP32 or 32 FP64 columns fit the LDS
@@ -554,6 +554,11 @@ SvdShape svd_shape(int mt, bool fp32, int xs, int nt) {
       if (w <= 3 && four) return svd_make<float, 3, 8, Producers<4, 4, 4, 1, 2, 2>>();
       if (w <= 4 && four) return svd_make<float, 4, 8, Producers<4, 4, 2, 2, 4, 2>>();
       if (w <= 4) return svd_make<float, 4, 8, Producers<4, 4, 1, 4, 4, 2>>();
+      // order 9: at ranks up to 48 full tiles are faster with two groups a
+      // wavefront (300,000, height 6, tolerance 1e-7: M2L 7.07 -> 6.72 ms),
+      // surfaces not (300,000, height 7: 3.84 -> 4.00), nor higher ranks
+      if (w <= 6 && !gskip && xs <= m2l_svd_xs(48, true))
+        return svd_make<float, 6, 8, Producers<4, 4, 2, 2, 4, 2>>();
       if (w <= 6) return svd_make<float, 6, 8, Producers<4, 4, 1, 4, 4, 2>>();
       return svd_make<float, 8, 8, Producers<4, 4, 1, 4, 4, 2>>();
     }
@@ -642,7 +647,7 @@ int m2l_svd_nt(int order, bool fp32, int64_t tile_parts, int cus) {
 }
 
 int m2l_svd_nmb(int mt, bool fp32, int nt) {
-  const SvdShape sh = svd_shape(mt, fp32, 0, nt);
+  const SvdShape sh = svd_shape(mt, fp32, 0, nt, false);
   return (mt + sh.ncw * sh.mtw - 1) / (sh.ncw * sh.mtw) * (4 / nt);
 }
 
@@ -678,7 +683,7 @@ void m2l_svd_ranges(int order, bool fp32, int xs, int cus, int* items, int* slot
 
 void launch_m2l_svd_step(int order, bool fp32, const JobDev* jobs, const StepTab* tab, int grid,
                          int xs, int nt, hipStream_t s, bool gskip) {
-  const SvdShape sh = svd_shape(svd_kc(order), fp32, xs, nt);
+  const SvdShape sh = svd_shape(svd_kc(order), fp32, xs, nt, gskip);
   // the source rows in LDS where they fit, and not at the cost of a CU's second
   // workgroup (FP64 order 5 at ranks up to 64: 60,000 on a sphere, height 6, M2L
   // 787 us staged, 600 not; at ranks that leave room for both staged is ahead)
