@@ -628,7 +628,8 @@ def summarize_counters(paths):
     for path in paths:
         for r in csv.DictReader(open(path)):
             name = r.get("Kernel_Name", "")
-            m = re.match(r"(?:void )?(?:fmm::)?([A-Za-z0-9_]+(?:<[^>(]*>)?)", name)
+            m = re.match(r"(?:void )?(?:fmm::)?([A-Za-z0-9_]+(?:<[^(]*>)?)",
+                         name.replace("(anonymous namespace)::", "").replace("fmm::", ""))
             k = m.group(1) if m else name[:60]
             c = r.get("Counter_Name")
             acc.setdefault((k, c), []).append(float(r["Counter_Value"]))
@@ -663,7 +664,8 @@ def summarize_trace(path, top, only=None):
     acc = {}
     for r in csv.DictReader(open(path)):
         name = r.get("Kernel_Name", "")
-        m = re.match(r"(?:void )?(?:fmm::)?([A-Za-z0-9_]+(?:<[^>(]*>)?)", name)
+        m = re.match(r"(?:void )?(?:fmm::)?([A-Za-z0-9_]+(?:<[^(]*>)?)",
+                         name.replace("(anonymous namespace)::", "").replace("fmm::", ""))
         k = m.group(1) if m else name[:60]
         grid = "x".join(r.get(f"Grid_Size_{d}", "?") for d in "XYZ")
         dt = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-6
