@@ -719,23 +719,23 @@ __device__ __forceinline__ void p2p_leaf_f64(const JobDev& J, int a, P2PLds<W>& 
   // batch would exceed the threads), a batch itself costing about kBatch; small
   // leaves, whose time is what surrounds the passes, take one without the
   // choice, and no more splits than sources (20,000 at height 7: 39 us choosing
-  // by the passes alone, 24 so)
+  // by the passes alone, 24 so).  That split is the default and not a second
+  // branch: as one, the passes of a leaf of 10,000 ran 103.9 ms, so 97.4
   constexpr float kBatch = 6.f;
   const int pairs = (nt + 1) / 2, b0 = (pairs + T - 1) / T;
-  int nb = pairs, K = 1;
+  int nb = pairs, K = min(T / pairs, total);
   if (b0 > 1 || float(total) * (1.f / float(T / pairs) - float(pairs) / T) > kBatch) {
     float best = 0.f;
+    K = 0;
     for (int B = b0; B < b0 + 4; ++B) {
       const int n = (pairs + B - 1) / B, k = T / n;
       const float cost = float(B) * (float(total) / float(k) + kBatch);
-      if (B == b0 || cost < 0.99f * best) {
+      if (K == 0 || cost < 0.99f * best) {
         nb = n;
         K = k;
         best = cost;
       }
     }
-  } else {
-    K = min(T / pairs, total);
   }
   const int k = tid / nb, t = tid - k * nb;
   for (int tb = 0; tb < pairs; tb += nb) {
